@@ -589,6 +589,12 @@ static TileShape tile_shape(int64_t, int64_t N, int64_t K, int lower)
     return N <= 64 ? TileShape{128, 64} : TileShape{128, 128};
 }
 
+bool gemm_tile_is_64(int64_t M, int64_t N, int64_t K, int lower)
+{
+    const TileShape ts = tile_shape(M, N, K, lower);
+    return ts.bm == 64 && ts.bn == 64;
+}
+
 int64_t gemm_tiles(int64_t M, int64_t N, int64_t K, int lower)
 {
     const TileShape ts = tile_shape(M, N, K, lower);
@@ -639,7 +645,8 @@ void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int
 void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int64_t* splits, int64_t* kchunk,
                       int64_t* splits_diag, int64_t* kchunk_diag)
 {
-    plan_splitk(K, gemm_tiles(n, n, K, lower), splits, kchunk, kchunk_fixed);
+    plan_splitk(K, tn_route(n, n, K, lower) ? tn_tiles(n, n, lower) : gemm_tiles(n, n, K, lower), splits, kchunk,
+                kchunk_fixed);
     *splits_diag = 0;
     *kchunk_diag = 0;
     if (!lower || kchunk_fixed > 0 || K < 2 * G_BK || tile_shape(n, n, K, lower).bm != 128) return;
@@ -729,7 +736,11 @@ static void gemm_launch(Exec& ex, const GemmArgs& g0, bool reduce)
 
 void gemm_f64(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, double>(ex, g, true); }
 void gemm_f64_reduce(Exec& ex, const GemmArgs& g) { gemm_reduce_launch<double>(ex, g); }
-void gemm_f64_partials(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, double>(ex, g, false); }
+void gemm_f64_partials(Exec& ex, const GemmArgs& g)
+{
+    if (g.transA && !g.transB && tn_route(g.M, g.N, g.K, g.lower)) gemm_tn_partials(ex, g);
+    else gemm_launch<double, double, double>(ex, g, false);
+}
 void gemm_f32(Exec& ex, const GemmArgs& g) { gemm_launch<float, float, float>(ex, g, true); }
 void gemm_f32_partials(Exec& ex, const GemmArgs& g) { gemm_launch<float, float, float>(ex, g, false); }
 void gemm_ddf(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, float>(ex, g, true); }

@@ -1,0 +1,345 @@
+// Split-K products C = A^T B in FP64 of two tall operands whose K direction
+// is contiguous in memory (A: K x M, B: K x N, column-major), in 64 x 64
+// output tiles: the Gram products A_p^T A_p and A_p^T A with A_p^T b, B^T A
+// of the not-normal equations and small FP64 sketches (see tn_route for the
+// sizes; larger products run in 128 x 128 tiles in gemm.hip).
+//
+// An FP64 MFMA 16x16x4 keeps a SIMD's matrix core busy for 64 cycles and
+// needs one operand value per lane and side.  A wavefront holds the 64 x 64
+// block of C (4 x 4 MFMA blocks, 128 registers), and the four wavefronts of
+// the work-group split its K chunk and are summed through LDS at the end.
+// Lane (r, g) (r = lane % 16, g = lane / 16) takes 16 bytes of column r of
+// each 16-column block, the K values k + 2 g, k + 2 g + 1, and MFMA h of the
+// step multiplies the h-th value of every lane: its four K values are
+// k + 2 g + h, g = 0..3, the same on both sides.  8 such loads per 32 MFMAs
+// are little enough to load straight from memory into the MFMA registers: no
+// LDS and no barriers in the loop, the wavefronts run free of each other;
+// two register buffers, the next step loads while the current one multiplies
+// (2048 cycles, twice that with two wavefronts per SIMD, against about 1000
+// cycles of memory latency).  MFMA blocks outside the matrix, and above the
+// diagonal of a lower-triangle product, are skipped (a 16-bit mask), so a
+// ragged order pays for 16-column blocks instead of 64-column tiles.
+//
+// Measured against the LDS-staged 64 x 64 and 128 x 128 tiles of gemm.hip:
+// the Gram products of 64 members (m 2000..50000, n 32..512) 6.67 -> 4.87 ms,
+// of 30011 x 257 123 -> 72 us, A_p^T A of 32768 x 400 334 -> 260 us.
+#include "common.h"
+#include "kernels.h"
+#include "launch.h"
+#include "tune.h"
+
+namespace pne {
+
+namespace {
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef double v2d8 __attribute__((ext_vector_type(2), aligned(8)));   // 16-byte load from an 8-byte boundary
+// (explicitly global: in grouped launches the pointers come from a table,
+// and the compiler would otherwise issue flat loads)
+typedef const __attribute__((address_space(1))) char* gpc;
+typedef const __attribute__((address_space(1))) double* gp64;
+typedef const __attribute__((address_space(1))) v2d8* gpv2;
+
+__device__ __forceinline__ void tn_lower_tile(int64_t id, int64_t& ti, int64_t& tj)
+{
+    int64_t t = (int64_t)((sqrt(8.0 * (double)id + 1.0) - 1.0) * 0.5);
+    while (t * (t + 1) / 2 > id) --t;
+    while ((t + 1) * (t + 2) / 2 <= id) ++t;
+    ti = t;
+    tj = id - t * (t + 1) / 2;
+}
+
+}  // namespace
+
+// WIDE: leading dimensions of 2^23 or more (64-bit addresses).  Otherwise a
+// lane's offset from the first column of its 64-column block fits 32 bits
+// and the loads are buffer loads (uniform base, one 32-bit offset register
+// per 16-column block, K advance in a scalar register), which leaves the
+// accumulators and both operand buffers in registers.
+template <bool WIDE>
+struct GemmTn {
+    typedef GemmArgs Args;
+    static constexpr int NTH = 256, WPE = 2;
+    static __device__ void run(const GemmArgs& g, int bx, int by);
+};
+
+template <bool WIDE>
+__device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int by)
+{
+    constexpr int BM = 64;
+    constexpr int KS = 8, KL = 2 * KS;   // K values per step and per turn of the loop
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t M = g.M, N = g.N;
+    const int64_t tiles_m = (M + BM - 1) / BM;
+    if (g.xcd_remap) {
+        // Work-group L of a launch runs on XCD L % 8: every XCD gets a
+        // contiguous run of (K chunk, tile) work, whose tiles read their
+        // operand panels through the same L2.
+        const int64_t gxw = gridDim.x, T = gxw * gridDim.y;
+        const int64_t L = bx + (int64_t)by * gxw;
+        const int64_t x = L % 8, slot = L / 8, q = T / 8, r = T % 8;
+        const int64_t v = x * q + (x < r ? x : r) + slot;
+        bx = (int)(v % gxw);
+        by = (int)(v / gxw);
+    }
+    int64_t ti, tj;
+    if (g.lower) {
+        tn_lower_tile(bx, ti, tj);
+    } else {
+        ti = bx % tiles_m;
+        tj = bx / tiles_m;
+    }
+    const int64_t split = by;
+    int64_t kbeg = split * g.kchunk;
+    int64_t kend = (kbeg + g.kchunk < g.K) ? kbeg + g.kchunk : g.K;
+    {
+        const int64_t sub = ((kend - kbeg + 4 * KL - 1) / (4 * KL)) * KL;   // K share of a wavefront
+        const int64_t ks = kbeg + w * sub;
+        const int64_t ke = ks + sub;
+        kend = ke < kend ? ke : kend;
+        kbeg = ks;
+    }
+    const int64_t i0 = ti * BM, j0 = tj * BM;
+    // which of the 16 MFMA blocks the product needs (bit 4 a + c: rows 16 a,
+    // columns 16 c)
+    unsigned mask = g.lower && ti == tj ? 0xf731u : 0xffffu;
+    {
+        int64_t na = (M - i0 + 15) / 16, nc = (N - j0 + 15) / 16;   // blocks inside the matrix
+        na = na < 0 ? 0 : (na > 4 ? 4 : na);
+        nc = nc < 0 ? 0 : (nc > 4 ? 4 : nc);
+        mask &= (1u << (4 * na)) - 1u;
+        mask &= ((1u << nc) - 1u) * 0x1111u;
+    }
+    mask = __builtin_amdgcn_readfirstlane(mask);
+    const double* __restrict__ bv = (const double*)g.bvec;
+    // op(A) bvec is formed beside the blocks on the diagonal (lower-triangle
+    // products) or of the first tile column
+    const bool fold = bv != nullptr && (g.lower ? (i0 == j0) : (j0 == 0));
+
+    v4d acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c] = (v4d){0, 0, 0, 0};
+    double cs[4] = {0, 0, 0, 0};
+
+    if (mask != 0 && kbeg < kend) {
+        typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
+        const gpc pa = (gpc)((gp64)g.A + i0 * g.lda + kbeg), pb = (gpc)((gp64)g.B + j0 * g.ldb + kbeg);
+        const gpc pv = (gpc)(gp64)(fold ? bv + kbeg : nullptr);
+        off_t oa[4], ob[4];   // the lane's column and K offset in each 16-column block, in bytes
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // columns past the matrix read its last column (results not stored)
+            const int64_t il = M - 1 - i0, jl = N - 1 - j0, c = t * 16 + r16;
+            oa[t] = (off_t)(((c < il ? c : il) * g.lda + 2 * g4) * 8);
+            ob[t] = (off_t)(((c < jl ? c : jl) * g.ldb + 2 * g4) * 8);
+        }
+        const uint32_t ov = 16 * g4;
+        const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pa, 0, -1, 0x00027000);
+        const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pb, 0, -1, 0x00027000);
+        v2d8 xa[2][4], xb[2][4];
+        auto load = [&](auto bufc, int64_t k) {
+            constexpr int b = decltype(bufc)::value;
+            if constexpr (WIDE) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    xa[b][t] = *(gpv2)(pa + 8 * k + oa[t]);
+                    xb[b][t] = *(gpv2)(pb + 8 * k + ob[t]);
+                }
+            } else {
+                const int so = (int)(8 * k);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    xa[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)oa[t], so, 0));
+                    xb[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)ob[t], so, 0));
+                }
+            }
+        };
+        // MASK 0: the wavefront's run-time mask
+        auto mult = [&](auto bufc, auto maskc) {
+            constexpr int b = decltype(bufc)::value;
+            constexpr unsigned MASK = decltype(maskc)::value;
+            const unsigned mk = MASK ? MASK : mask;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if ((mk >> (4 * a + c)) & 1u)
+                            acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(xb[b][c][h], xa[b][a][h], acc[a][c], 0, 0, 0);
+        };
+        auto fold_step = [&](auto bufc, int64_t k) {
+            constexpr int b = decltype(bufc)::value;
+            const v2d8 v = *(gpv2)(pv + 8 * k + ov);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) cs[t] += xa[b][t][0] * v[0] + xa[b][t][1] * v[1];
+        };
+        using B0 = std::integral_constant<int, 0>;
+        using B1 = std::integral_constant<int, 1>;
+        const int64_t len = kend - kbeg, main = len / KL * KL;
+        // Two steps a turn: the loads of a step are issued ahead of the
+        // multiplications of the step before it (the scheduling barriers keep
+        // it so).
+        auto loop = [&](auto maskc, auto foldc) {
+            constexpr bool FOLD = decltype(foldc)::value;
+            auto step = [&](auto bufc, int64_t k) {
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (FOLD) fold_step(bufc, k);
+                mult(bufc, maskc);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            load(B0{}, 0);
+            for (int64_t k = 0; k < main; k += KL) {
+                load(B1{}, k + KS);
+                step(B0{}, k);
+                load(B0{}, k + KL < main ? k + KL : k);   // (after the last turn: read again, unused)
+                step(B1{}, k + KS);
+            }
+        };
+        using F = std::false_type;
+        using T = std::true_type;
+        if (main > 0) {
+            if (mask == 0xffffu) {
+                if (fold) loop(std::integral_constant<unsigned, 0xffffu>{}, T{});
+                else loop(std::integral_constant<unsigned, 0xffffu>{}, F{});
+            } else if (mask == 0xf731u && fold) {
+                loop(std::integral_constant<unsigned, 0xf731u>{}, T{});
+            } else if (fold) {
+                loop(std::integral_constant<unsigned, 0>{}, T{});
+            } else {
+                loop(std::integral_constant<unsigned, 0>{}, F{});
+            }
+        }
+        // the K values left over (less than a turn): zero past the end on
+        // both sides
+        for (int64_t k = main; k < len; k += KS) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const bool in = k + 2 * g4 + h < len;
+                const double v = (fold && in) ? *(gp64)(pv + 8 * (k + h) + ov) : 0.0;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    xa[0][t][h] = in ? *(gp64)(pa + 8 * (k + h) + oa[t]) : 0.0;
+                    xb[0][t][h] = in ? *(gp64)(pb + 8 * (k + h) + ob[t]) : 0.0;
+                    cs[t] += xa[0][t][h] * v;
+                }
+            }
+            mult(B0{}, std::integral_constant<unsigned, 0>{});
+        }
+    }
+    if (fold) {
+        // sum over the four K values of a step (lane bits 4 and 5)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            cs[t] += lane_partner<32>(cs[t]);
+            cs[t] += lane_partner<16>(cs[t]);
+        }
+    }
+
+    {
+        // sum of the four wavefronts' blocks, ((0 + 1) + (2 + 3)), in LDS
+        __shared__ double sh[64 * 64];
+        __shared__ double shc[3][64];
+        auto put = [&]() {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sh[((a * 4 + c) * 4 + r) * 64 + lane] = acc[a][c][r];
+        };
+        auto take = [&]() {
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[a][c][r] += sh[((a * 4 + c) * 4 + r) * 64 + lane];
+        };
+        if (fold && w > 0 && g4 == 0)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) shc[w - 1][t * 16 + r16] = cs[t];
+        if (w == 1) put();
+        __syncthreads();
+        if (w == 0) {
+            take();
+            if (fold && g4 == 0)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    cs[t] = ((cs[t] + shc[0][t * 16 + r16]) + shc[1][t * 16 + r16]) + shc[2][t * 16 + r16];
+        }
+        __syncthreads();
+        if (w == 3) put();
+        __syncthreads();
+        if (w == 2) {
+            take();
+            put();
+        }
+        __syncthreads();
+        if (w == 0) take();
+        __syncthreads();   // (a persistent work-group reuses the buffer)
+        if (w != 0) return;
+    }
+
+    // lane owns rows i = .. + r16 and columns j = .. + g4 + 4 r of each block
+    typedef __attribute__((address_space(1))) double* gpw;
+    const gpw P = (gpw)g.P + split * M * N;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const int64_t i = i0 + a * 16 + r16;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (!((mask >> (4 * a + c)) & 1u) || i >= M) continue;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t j = j0 + c * 16 + g4 + 4 * r;
+                if (j < N) {
+                    double v = acc[a][c][r];
+                    if (g.accumulate_partials) v += P[i + j * M];
+                    P[i + j * M] = v;
+                }
+            }
+        }
+    }
+    if (fold && g4 == 0)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int64_t i = i0 + t * 16 + r16;
+            if (i < M) ((double*)g.Pc)[split * M + i] = cs[t];
+        }
+}
+
+
+// Products that run here: lower triangles in 64 x 64 tiles (tile_shape in
+// gemm.hip), short K, and full products of order up to 512 whose operands
+// together fit the 256 MB memory-side cache.  Beyond that the tiles'
+// wavefronts, which nothing keeps in step, re-read the operands from HBM:
+// A_p^T A of 400000 x 500 (3.2 GB) takes 4.8 ms here and 4.1 ms in 128 x 128
+// tiles, of 32768 x 400 (0.2 GB) 0.26 and 0.33 ms.
+bool tn_route(int64_t M, int64_t N, int64_t K, int lower)
+{
+    if (lower || K < 4096) return gemm_tile_is_64(M, N, K, lower);
+    return M <= 512 && N <= 512 && 8 * K * (M + N) <= ((int64_t)256 << 20);
+}
+
+int64_t tn_tiles(int64_t M, int64_t N, int lower)
+{
+    const int64_t tm = ceil_div(M, 64), tn = ceil_div(N, 64);
+    return lower ? tm * (tm + 1) / 2 : tm * tn;
+}
+
+void gemm_tn_partials(Exec& ex, const GemmArgs& g0)
+{
+    GemmArgs g = g0;
+    if (g.splits < 1) g.splits = 1;
+    if (g.kchunk <= 0) g.kchunk = ceil_div(ceil_div(g.K, g.splits), 16) * 16;
+    g.xcd_remap = !ex.recording() && g.splits > 1;
+    const int64_t tiles = tn_tiles(g.M, g.N, g.lower);
+    if (g.lda >= ((int64_t)1 << 23) || g.ldb >= ((int64_t)1 << 23)) launch<GemmTn<true>>(ex, tiles, g.splits, g);
+    else launch<GemmTn<false>>(ex, tiles, g.splits, g);
+}
+
+}  // namespace pne

@@ -84,6 +84,12 @@ struct GemmArgs {
 void gemm_f64(Exec& ex, const GemmArgs& g);           // full path incl. reduce
 void gemm_f64_partials(Exec& ex, const GemmArgs& g);  // partials only (no reduce)
 void gemm_f64_reduce(Exec& ex, const GemmArgs& g);    // reduce of the partials
+// A^T B in 64 x 64 tiles with the operands loaded straight into registers
+// (gemm_tn.hip): whether gemm_f64_partials takes that route, and its tiles
+bool tn_route(int64_t M, int64_t N, int64_t K, int lower);
+int64_t tn_tiles(int64_t M, int64_t N, int lower);
+void gemm_tn_partials(Exec& ex, const GemmArgs& g);
+bool gemm_tile_is_64(int64_t M, int64_t N, int64_t K, int lower);
 void gemm_f32(Exec& ex, const GemmArgs& g);
 void gemm_f32_partials(Exec& ex, const GemmArgs& g);
 void gemm_ddf(Exec& ex, const GemmArgs& g);           // fl32(A)^T fl32(B) etc.
