@@ -75,6 +75,12 @@ struct Buffers {
 // on 16-byte boundaries (16-byte loads in its products).
 int64_t ap_ld(int64_t m) { return (m + 1) & ~(int64_t)1; }
 
+// Where the packed R of the A R^{-1} step goes: the block-inverse arrays,
+// which are written later (dinv1 and dinv2 are adjacent: 1 KiB n), as long as
+// it fits them, else the shared scratch (at least the Gram partials, 8 n^2
+// bytes; the packing takes about 4 n^2 + 384 n).
+double* trsm_pack(const Buffers& b, int64_t n) { return n <= 128 ? b.dinv1 : (double*)b.scratch; }
+
 size_t scratch_bytes(const Problem& p, int sk, int qr)
 {
     size_t b = p.sketch_kind == 1 ? srft_workspace_bytes(p.m, p.n, srft_prec(sk))
@@ -253,7 +259,7 @@ void run_gram(Exec& ex, const Problem& p, const double* dA, const double* db, co
     const int hpne = p.hpne;
     ex.stage(ST_TRSM);
     const int64_t ldap = ap_ld(m);
-    trsm_right_upper(ex, m, n, dA, lda, b.R, n, b.Ap, ldap);
+    trsm_right_upper(ex, m, n, dA, lda, b.R, n, b.Ap, ldap, trsm_pack(b, n));
     mark(ex, PH_TRSM);
     ex.stage(ST_GRAM);
     int64_t splits, kc, sd, kcd;

@@ -1,7 +1,7 @@
 // Column-major MFMA GEMM for the FP64 (and FP32) contractions of the path:
-// the off-diagonal updates of the blocked A R_s^{-1}, the Gram products
-// A_p^T A_p / A_p^T A with A_p^T b, the trailing updates of the blocked
-// Cholesky, LU and Householder QR, and the FP64 sketch product.
+// the large Gram products A_p^T A_p / A_p^T A with A_p^T b (smaller ones:
+// gemm_tn.hip), the trailing updates of the blocked Cholesky and LU, and the
+// FP64 sketch product.
 //
 // C = alpha op(A) op(B) + beta Cin on 128 x BN output tiles (BN = 64 or 128),
 // 256 threads = 2 x 2 waves, MFMA 16x16x4 (v_mfma_f64_16x16x4f64 or
@@ -571,8 +571,7 @@ __device__ void GemmReduce<TC>::run(const GemmReduceArgs& a, int bx, int)
 }
 
 // Output tile of a product.  64 x 64 when K is short (the tall products of
-// A R^-1, the Cholesky and LU updates: three work-groups per CU and the finer
-// grid beat the higher reuse of larger tiles).  Long-K products: lower
+// Cholesky and LU updates: three work-groups per CU and the finer grid beat the higher reuse of larger tiles).  Long-K products: lower
 // triangles 64 x 64 up to order 512 (128-wide tiles would spend a large
 // share of their work on padding) and 128 x 128 above; others 128 x 128, or
 // 128 x 64 for N <= 64.

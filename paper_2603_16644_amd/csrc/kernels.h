@@ -106,16 +106,12 @@ void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int
                       int64_t* splits_diag, int64_t* kchunk_diag);
 
 // ---------------------------------------------------------------- TRSM / factorizations
-// Ap = A R^{-1}, R upper n x n (FP64), blocked substitution.
+// Ap = A R^{-1}, R upper n x n (FP64), blocked substitution; Ap 16-byte
+// aligned with an even leading dimension.  pack: scratch of
+// trsm_pack_bytes(n).
+size_t trsm_pack_bytes(int64_t n);
 void trsm_right_upper(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, const double* R,
-                      int64_t ldr, double* Ap, int64_t ldap);
-// row-parallel substitution on a block of <= 64 columns: X := X R^{-1}
-// (R upper, TL = false) or X := X L^{-T} (L lower, TL = true); element
-// (i, c) of X at X[i*rs + c*cs]; UNIT: unit diagonal.  With Xin the input is
-// read from Xin[i*rs + c*cs_in] (X is then output only).
-template <typename T, bool TL, bool UNIT>
-void trsm_leaf(Exec& ex, int64_t m, int w, T* X, int64_t rs, int64_t cs, const T* Rb, int64_t ldr,
-               const T* Xin = nullptr, int64_t cs_in = 0);
+                      int64_t ldr, double* Ap, int64_t ldap, double* pack);
 // Cholesky (lower, in place) of the n x n matrix C; info word gets 2000+k.
 // Dinv (dinv_elems(n) values) receives the inverses of the 64 x 64 diagonal
 // blocks of L in the layout of inv_diag_blocks.

@@ -1,158 +1,352 @@
 // A_p = A R_s^{-1} in FP64 (Algorithm 1, "Solve A_p = A R_s^{-1}", after
-// R_s is promoted to double).  Recursive right-side substitution (the first
-// reads of each column come from A, the results go to A_p); for
-// R = [R11 R12; 0 R22]
-//   A_p(:, 1) := A_p(:, 1) R11^{-1}               (recursively)
-//   A_p(:, 2) -= A_p(:, 1) R12                    (MFMA GEMM, gemm.hip)
-//   A_p(:, 2) := A_p(:, 2) R22^{-1}               (recursively)
-// down to blocks of 64 columns, finished by row-parallel substitution.
-// The second step keeps one row per lane in registers and runs the plain
-// forward substitution y_j = (t_j - sum_{k<j} y_k R_kj) / R_jj with the
-// 64 x 64 diagonal block broadcast from LDS.  The same leaf serves the
-// Cholesky panel (X L^T = C, TRANS_LOWER).
+// R_s is promoted to double): block forward substitution
+//   X_J = (A_J - sum_{I<J} X_I R_IJ) R_JJ^{-1}
+// with every row of A handled by one wavefront from its first column to its
+// last, in one launch.
+//
+// A wavefront owns 16 rows.  Its block of X sits in the accumulators of the
+// FP64 MFMA 16x16x4: lane (r, g) (r = lane % 16, g = lane / 16) holds row r,
+// register q of a 16-column block holds column g + 4 q.  Register q is at the
+// same time exactly what an MFMA wants as its operand for the K values
+// 4 q + g, so a finished block of X multiplies into the later ones straight
+// from the accumulators, without a trip through LDS or memory.  Columns are
+// taken in panels of up to 8 blocks (128 columns, 64 registers, which leaves
+// room for three wavefronts per SIMD); a panel first subtracts the products
+// with all earlier columns of X (read back from A_p by the lane that wrote
+// them), then is solved block by block.
+//
+// Inside a block of 16 columns the substitution goes by groups of four: two
+// MFMAs each, one with the inverse of the 4 x 4 diagonal block of R and one
+// that removes the group from the columns right of it.  (An inverse of four
+// columns changes rounding only, like the reciprocal of a pivot.)
+//
+// R is packed once (TrsmPack) in the order in which the MFMAs read it, with
+// the sign changed.  The four wavefronts of a work-group (64 rows) share each
+// 16-row strip of it through LDS, double-buffered, one barrier per strip: a
+// strip is 32 MFMAs (2048 cycles) per wavefront.  HBM traffic is A once, X
+// once and (n / 128 - 1) / 2 re-reads of X; the recursion of products and
+// 64-column leaves this replaces read and wrote the right part of the matrix
+// at every level (7.9 GB fetched at 100000 x 1000).
+//
+// Bound: FP64 MFMA (and, where the work-groups of 64 rows fill the machine's
+// 768 places badly, its last round: 1563 work-groups at 100000 rows).
+// Measured, recursion -> this: 1000 x 100 86 -> 21 us, 30011 x 257 250 -> 104
+// us, 32768 x 400 0.39 -> 0.17 ms, 400000 x 500 3.9 -> 2.3 ms, 100000 x 1000
+// 3.25 -> 2.38 ms, 1000000 x 2000 96 -> 73 ms (55 TFLOP/s), 64 members of
+// m 2000..50000, n 32..512 9.5 -> 5.5 ms.  Panels of 12 and 16 blocks with two
+// wavefronts per SIMD spilled registers (2.75 and 3.2 ms at 100000 x 1000; 8
+// blocks with two wavefronts 2.50); a reload from scratch memory waits for
+// every load in flight, so the loops must be free of them.
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
 
 namespace pne {
 
-constexpr int LEAF = 64;
+namespace {
 
-struct TrsmLeafArgs {
-    int64_t m;
-    int w;
-    void* X;
-    int64_t rs, cs;
-    const void* Rb;
-    int64_t ldr;
-    const void* Xin;   // input (element (i, c) at Xin[i*rs + c*cs_in]); null: X in place
-    int64_t cs_in;
-};
-template <typename T, bool TRANS_LOWER, bool UNIT, int NT>
-struct TrsmLeaf {
-    typedef TrsmLeafArgs Args;
-    static constexpr int NTH = NT, WPE = 0;
-    static __device__ void run(const TrsmLeafArgs& a, int bx, int by);
-};
-template <typename T, bool TRANS_LOWER, bool UNIT, int NT>
-__device__ void TrsmLeaf<T, TRANS_LOWER, UNIT, NT>::run(const TrsmLeafArgs& a, int bx, int)
+constexpr int TB16 = 16;                 // columns per block
+constexpr int PANEL = 8;                 // blocks per panel (at most)
+constexpr int BLK = 256;                 // doubles of a packed 16 x 16 block
+constexpr int DTAB = 512;                // doubles of a diagonal table
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef const __attribute__((address_space(1))) double* gp64;
+typedef __attribute__((address_space(1))) double* gw64;
+typedef const __attribute__((address_space(1))) char* gpc;
+typedef __attribute__((address_space(1))) char* gwc;
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+__host__ __device__ inline int64_t pack_block(int64_t nblk, int64_t kb, int64_t jb)
 {
-    const int64_t m = a.m, rs = a.rs, cs = a.cs, ldr = a.ldr;
-    const int w = a.w;
-    T* __restrict__ X = (T*)a.X;
-    const T* __restrict__ Xi = a.Xin ? (const T*)a.Xin : X;
-    const int64_t csi = a.Xin ? a.cs_in : cs;
-    const T* __restrict__ Rb = (const T*)a.Rb;
-    // Rs[c * 64 + j] = R(c, j) for c < j (TRANS_LOWER: L(j, c)): row c of the
-    // block contiguous, so the update of step c reads consecutive entries;
-    // rd[c] = 1 / R(c, c)
-    __shared__ __attribute__((aligned(16))) T Rs[LEAF * LEAF];
-    __shared__ T rd[LEAF];
-    for (int e = threadIdx.x; e < LEAF * LEAF; e += NT) {
-        const int c = e / LEAF, j = e % LEAF;
-        T v = 0;
-        if (j < w && c <= j) v = TRANS_LOWER ? Rb[j + (int64_t)c * ldr] : Rb[c + (int64_t)j * ldr];
-        if (c == j) {
-            if (UNIT || c >= w) v = (T)1;
-            rd[c] = (T)1 / v;
+    return kb * nblk - kb * (kb - 1) / 2 + (jb - kb);
+}
+
+}  // namespace
+
+size_t trsm_pack_bytes(int64_t n)
+{
+    const int64_t q = ceil_div(n, TB16);
+    return (size_t)(q * (q + 1) / 2 * BLK + q * DTAB) * sizeof(double);
+}
+
+// Packed R: block (kb, jb), jb >= kb, at pack_block(..) * BLK:
+//   [p][lane][h] = -R(16 kb + 4 (2 p + h) + g, 16 jb + r)
+// (K step 2 p + h, h = 0, 1: 16 bytes per lane); then the table of every
+// diagonal block, [q][lane][2]: the operand of group q's inverse, entry
+// (k = g, column r) of the 4 x 4 inverse in the rows 4 q .. 4 q + 3 of the
+// result and 0 elsewhere, and the operand of its update,
+// -R(16 b + 4 q + g, 16 b + r) for r >= 4 q + 4 and 0 elsewhere.  Rows and
+// columns past n act as the identity.
+struct TrsmPack {
+    struct Args {
+        int64_t n;
+        const double* R;
+        int64_t ldr;
+        double* out;
+    };
+    static constexpr int NTH = 256, WPE = 0;
+    static __device__ void run(const Args& a, int bx, int by)
+    {
+        const int64_t n = a.n, nblk = (n + TB16 - 1) / TB16;
+        const int64_t kb = by, jb = kb + bx;
+        if (jb >= nblk) return;
+        const gp64 R = (gp64)a.R;
+        const gw64 out = (gw64)a.out;
+        auto rel = [&](int64_t i, int64_t j) -> double {
+            return (i < n && j < n) ? R[i + j * a.ldr] : (i == j ? 1.0 : 0.0);
+        };
+        const int t = threadIdx.x;
+        {
+            const int h = t & 1, lane = (t >> 1) & 63, p = t >> 7;
+            const int64_t i = TB16 * kb + 4 * (2 * p + h) + (lane >> 4), j = TB16 * jb + (lane & 15);
+            out[pack_block(nblk, kb, jb) * BLK + t] = -rel(i, j);
         }
-        Rs[e] = v;
-    }
-    __syncthreads();
-    const int64_t i = (int64_t)bx * NT + threadIdx.x;
-    if (i >= m) return;
-    T x[LEAF];
+        if (jb != kb) return;
+        const gw64 tab = out + nblk * (nblk + 1) / 2 * BLK + kb * DTAB;
+        const int lane = t & 63, q = t >> 6, r = lane & 15, g = lane >> 4;
+        const int64_t b0 = TB16 * kb + 4 * q;
+        double inv = 0.0;
+        const int c = r - 4 * q;
+        if (c >= 0 && c < 4 && g <= c) {
+            // column c of the inverse by back substitution, entry g
+            double y[4];
 #pragma unroll
-    for (int c = 0; c < LEAF; ++c) x[c] = (c < w) ? Xi[i * rs + c * csi] : (T)0;
-    // column-oriented substitution: once y_c is final it is stored and
-    // removed from every later entry (the stores then overlap the rest of
-    // the work); y_j still accumulates its terms in the order k = 0, 1, ...
+            for (int k = 3; k >= 0; --k) {
+                double s = k == c ? 1.0 : 0.0;
 #pragma unroll
-    for (int c = 0; c < LEAF; ++c) {
-        if (c < w) {
-            if (!UNIT) x[c] = x[c] * rd[c];
-            X[i * rs + c * cs] = x[c];   // final: stored while the later columns are formed
+                for (int l = k + 1; l < 4; ++l)
+                    if (l <= c) s -= rel(b0 + k, b0 + l) * y[l];
+                y[k] = k <= c ? s / rel(b0 + k, b0 + k) : 0.0;
+            }
 #pragma unroll
-            for (int j = c + 1; j < LEAF; ++j) x[j] -= x[c] * Rs[c * LEAF + j];
+            for (int k = 0; k < 4; ++k)
+                if (k == g) inv = y[k];
         }
+        tab[t * 2] = inv;
+        tab[t * 2 + 1] = r >= 4 * q + 4 ? -rel(b0 + g, TB16 * kb + r) : 0.0;
     }
-}
+};
 
-template <typename T, bool TL, bool UNIT>
-void trsm_leaf(Exec& ex, int64_t m, int w, T* X, int64_t rs, int64_t cs, const T* Rb, int64_t ldr,
-               const T* Xin, int64_t cs_in)
-{
-    if (m <= 0) return;
-    const TrsmLeafArgs a{m, w, X, rs, cs, Rb, ldr, Xin, cs_in};
-    // short panels (factorizations) use one wavefront per work-group to
-    // spread over more compute units
-    if (m < 16384) launch<TrsmLeaf<T, TL, UNIT, 64>>(ex, ceil_div(m, 64), 1, a);
-    else launch<TrsmLeaf<T, TL, UNIT, 256>>(ex, ceil_div(m, 256), 1, a);
-}
-template void trsm_leaf<double, true, false>(Exec&, int64_t, int, double*, int64_t, int64_t, const double*, int64_t,
-                                             const double*, int64_t);
-template void trsm_leaf<float, true, false>(Exec&, int64_t, int, float*, int64_t, int64_t, const float*, int64_t,
-                                            const float*, int64_t);
-template void trsm_leaf<double, true, true>(Exec&, int64_t, int, double*, int64_t, int64_t, const double*, int64_t,
-                                            const double*, int64_t);
-template void trsm_leaf<double, false, false>(Exec&, int64_t, int, double*, int64_t, int64_t, const double*, int64_t,
-                                              const double*, int64_t);
+struct TrsmArgs {
+    int64_t m, n;
+    const double* A;
+    int64_t lda;
+    const double* pack;
+    double* X;         // 16-byte aligned, ldx even
+    int64_t ldx;
+};
+// WIDE: leading dimensions of 2^26 or more (64-bit lane offsets)
+template <bool WIDE>
+struct TrsmRows {
+    typedef TrsmArgs Args;
+    static constexpr int NTH = 256, WPE = 3;
+    static __device__ void run(const TrsmArgs& a, int bx, int);
+};
 
-// Blocks of at most 128 columns: the two 64-column halves are finished by
-// the leaf with a 64-deep GEMM in between.  The input comes from src (the
-// original A, or A_p itself once updated) and the result goes to Ap.
-static void trsm_base(Exec& ex, int64_t m, int64_t n, const double* src, int64_t lds, const double* R,
-                      int64_t ldr, double* Ap, int64_t ldap, uint32_t& step)
+template <bool WIDE>
+__device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, int)
 {
-    ex.iter(step++);
-    const int w1 = n < LEAF ? (int)n : LEAF;
-    trsm_leaf<double, false, false>(ex, m, w1, Ap, 1, ldap, R, ldr, src, lds);
-    if (n > LEAF) {
-        GemmArgs h{};
-        h.M = m; h.N = n - LEAF; h.K = LEAF;
-        h.A = Ap; h.lda = ldap; h.transA = 0;
-        h.B = R + LEAF * ldr; h.ldb = ldr; h.transB = 0;
-        h.alpha = -1.0; h.beta = 1.0;
-        h.Cin = src + LEAF * lds; h.ldcin = lds;
-        h.C = Ap + LEAF * ldap; h.ldc = ldap;
-        h.splits = 1;
-        gemm_f64(ex, h);
-        trsm_leaf<double, false, false>(ex, m, (int)(n - LEAF), Ap + LEAF * ldap, 1, ldap,
-                                        R + LEAF + LEAF * ldr, ldr, nullptr, 0);
+    __shared__ __attribute__((aligned(16))) v2d sr[2][PANEL * BLK / 2];
+    __shared__ __attribute__((aligned(16))) v2d sd[2][DTAB / 2];
+    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int w = tid >> 6;
+    const int64_t m = a.m, n = a.n, nblk = (n + TB16 - 1) / TB16;
+    // uniform first row of the work-group and the lane's row below it (rows
+    // past the matrix read its last row and are not stored)
+    const int64_t i0 = (int64_t)bx * 64;
+    const int row = w * 16 + r16;
+    const bool in = i0 + row < m;
+    const int ic = in ? row : (int)(m - 1 - i0);
+    typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
+    const off_t oi = (off_t)(ic * 8), lda8 = (off_t)(a.lda * 8), ldx8 = (off_t)(a.ldx * 8);
+    const off_t ox = oi + g4 * ldx8;
+    const gpc Ab = (gpc)((gp64)a.A + i0);
+    const gwc Xb = (gwc)((gw64)a.X + i0);
+    // X(row, 4 j4 + g)
+    auto xat = [&](int64_t j4) { return (gw64)(Xb + j4 * (a.ldx * 32) + ox); };
+    const gpc pk = (gpc)(gp64)a.pack;
+    const gpc tabs = pk + nblk * (nblk + 1) / 2 * (BLK * 8);
+    // panels of equal width
+    const int64_t np = (nblk + PANEL - 1) / PANEL, pw = (nblk + np - 1) / np;
+
+    // strip of the work: panel (first block lp0, lnb blocks) and block row lkb
+    // of R; strips lkb < lp0 come before the panel's own
+    int64_t lp0 = 0, lkb = 0;            // strip that is loaded next
+    int lnb = (int)(pw < nblk ? pw : nblk);
+    v4i vs[PANEL / 2], vd;               // a strip: up to 16 blocks of 128 16-byte entries, a diagonal table
+    const int vo = tid * 16;
+    // (buffer loads: the range check puts zeros past the strip's end without
+    // a branch, so the loads stay in flight across the multiplications)
+    auto fetch = [&]() {
+        const bool live = lp0 < nblk;
+        const int64_t j0 = lkb < lp0 ? lp0 : lkb;   // (own strips start at the diagonal)
+        const gpc src = pk + (live ? pack_block(nblk, lkb, j0) * (BLK * 8) : 0);
+        const int bytes = live ? (int)(lp0 + lnb - j0) * (BLK * 8) : 0;
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)src, 0, bytes, 0x00027000);
+#pragma unroll
+        for (int q = 0; q < PANEL / 2; ++q)
+            vs[q] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, vo + 4096 * q, 0, 0));
+        const gpc dsrc = tabs + (live ? lkb * (DTAB * 8) : 0);
+        const auto rd = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)dsrc, 0, live ? DTAB * 8 : 0, 0x00027000);
+        vd = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rd, vo, 0, 0));
+    };
+    auto advance = [&]() {
+        if (++lkb == lp0 + lnb) {
+            lp0 += lnb;
+            lnb = (int)(nblk - lp0 < pw ? nblk - lp0 : pw);
+            lkb = 0;
+        }
+    };
+    int buf = 0;
+    auto put = [&](int b) {
+#pragma unroll
+        for (int q = 0; q < PANEL / 2; ++q) sr[b][tid + 256 * q] = __builtin_bit_cast(v2d, vs[q]);
+        sd[b][tid] = __builtin_bit_cast(v2d, vd);
+    };
+    // begin of a strip: its data is in LDS buffer `buf` after the barrier;
+    // the next strip goes into the other one and the one after it is loaded
+    auto turn = [&]() {
+        __syncthreads();
+        put(buf ^ 1);
+        advance();
+        fetch();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch();
+    put(0);
+    advance();
+    fetch();
+
+    v4d acc[PANEL];
+    for (int64_t p0 = 0; p0 < nblk;) {
+        const int nb = (int)(nblk - p0 < pw ? nblk - p0 : pw);
+        // columns of A
+#pragma unroll
+        for (int c = 0; c < PANEL; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // (columns past n read the last one and are not stored)
+                const int64_t j = TB16 * (p0 + c) + 4 * q, jl = n - 1 - j;
+                acc[c][q] = jl >= 0 ? *(gp64)(Ab + j * (a.lda * 8) + ((g4 < jl ? g4 : (int)jl) * lda8 + oi)) : 0.0;
+            }
+        // blocks C0 .. C1 - 1 of the panel minus X times a strip that starts at
+        // block C0; the operands of the next block read
+        // from LDS while one multiplies
+        auto strip_mult = [&](const v2d* s, auto& x, auto c0c, auto c1c) {
+            constexpr int C0 = decltype(c0c)::value, C1 = decltype(c1c)::value;
+            v2d f[2][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) f[0][e] = s[e * 64 + lane];
+#pragma unroll
+            for (int c = C0; c < C1; ++c) {
+                const int b = (c - C0) & 1;
+                if (c + 1 < C1)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) f[b ^ 1][e] = s[((c + 1 - C0) * 2 + e) * 64 + lane];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[b][p][h], x[2 * p + h], acc[c], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // products with the earlier panels; NG groups of four blocks
+        auto outer = [&](auto ngc) {
+            constexpr int NG = decltype(ngc)::value;
+            double xn[4], xc[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xn[q] = *xat(q);
+            for (int64_t kb = 0; kb < p0; ++kb) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xc[q] = xn[q];
+                const int64_t kn = kb + 1 < p0 ? kb + 1 : kb;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xn[q] = *xat(4 * kn + q);
+                turn();
+                strip_mult(sr[buf], xc, std::integral_constant<int, 0>{}, std::integral_constant<int, 4 * NG>{});
+                buf ^= 1;
+            }
+        };
+        if (p0 > 0) {
+            if (nb > 4) outer(std::integral_constant<int, 2>{});
+            else outer(std::integral_constant<int, 1>{});
+        }
+        // the panel's own triangle
+        auto own = [&](auto bc) {
+            constexpr int B = decltype(bc)::value;
+            if (B >= nb) return;
+            turn();
+            v4d t = acc[B];
+            const v2d* d = sd[buf];
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2]) ||
+                                                             !isfinite(t[3])) != 0, 0)) {
+                // a non-finite entry: the zeros of the inverses must not
+                // carry it into the columns left of it
+#pragma unroll 1
+                for (int q = 0; q < 4; ++q) {
+                    const v2d f = d[q * 64 + lane];
+                    const double tq = q == 0 ? t[0] : q == 1 ? t[1] : q == 2 ? t[2] : t[3];
+                    double x = 0.0;
+                    for (int k = 0; k < 4; ++k) {
+                        const double tk = __shfl(tq, 16 * k + r16);
+                        const double ik = __shfl(f[0], 16 * k + 4 * q + g4);
+                        if (k <= g4) x += tk * ik;
+                    }
+                    const v4d u = __builtin_amdgcn_mfma_f64_16x16x4f64(f[1], x, t, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[e] = e == q ? x : (e > q ? u[e] : t[e]);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v2d f = d[q * 64 + lane];
+                    const v4d y = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0], t[q], (v4d){0, 0, 0, 0}, 0, 0, 0);
+                    t[q] = y[q];
+                    if (q < 3) {
+                        // (only the columns right of the group are taken)
+                        const v4d u = __builtin_amdgcn_mfma_f64_16x16x4f64(f[1], y[q], t, 0, 0, 0);
+#pragma unroll
+                        for (int e = q + 1; e < 4; ++e) t[e] = u[e];
+                    }
+                }
+            }
+            acc[B] = t;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t j4 = 4 * (p0 + B) + q;
+                if (in && 4 * j4 + g4 < n) *xat(j4) = t[q];
+            }
+            // the blocks right of it, up to the next multiple of four past nb
+            // (the strip starts at its diagonal block, zeros past its end)
+            const v2d* s = sr[buf] + BLK / 2;
+            using C0 = std::integral_constant<int, B + 1>;
+            if (nb > 4) strip_mult(s, t, C0{}, std::integral_constant<int, 8>{});
+            else if (B < 3) strip_mult(s, t, C0{}, std::integral_constant<int, B < 3 ? 4 : B + 1>{});
+            buf ^= 1;
+        };
+        own(std::integral_constant<int, 0>{});
+        own(std::integral_constant<int, 1>{});
+        own(std::integral_constant<int, 2>{});
+        own(std::integral_constant<int, 3>{});
+        own(std::integral_constant<int, 4>{});
+        own(std::integral_constant<int, 5>{});
+        own(std::integral_constant<int, 6>{});
+        own(std::integral_constant<int, 7>{});
+        p0 += nb;
     }
-}
-
-// Recursive halving, X = [X1 X2], R = [R11 R12; 0 R22]:
-//   X1 = A1 R11^{-1};  X2 = (A2 - X1 R12) R22^{-1}.
-// The off-diagonal products are large GEMMs (K = n/2, n/4, ...), which run
-// far closer to the MFMA peak than a sweep of 128-column blocks would.
-static void trsm_rec(Exec& ex, int64_t m, int64_t n, const double* src, int64_t lds, const double* R,
-                     int64_t ldr, double* Ap, int64_t ldap, uint32_t& step)
-{
-    if (n <= 2 * LEAF) {
-        trsm_base(ex, m, n, src, lds, R, ldr, Ap, ldap, step);
-        return;
-    }
-    const int64_t n1 = ceil_div(n / 2, LEAF) * LEAF;
-    trsm_rec(ex, m, n1, src, lds, R, ldr, Ap, ldap, step);
-    ex.iter(step++);
-    GemmArgs g{};
-    g.M = m; g.N = n - n1; g.K = n1;
-    g.A = Ap; g.lda = ldap; g.transA = 0;
-    g.B = R + n1 * ldr; g.ldb = ldr; g.transB = 0;
-    g.alpha = -1.0; g.beta = 1.0;
-    g.Cin = src + n1 * lds; g.ldcin = lds;
-    g.C = Ap + n1 * ldap; g.ldc = ldap;
-    g.splits = 1;
-    gemm_f64(ex, g);
-    trsm_rec(ex, m, n - n1, Ap + n1 * ldap, ldap, R + n1 + n1 * ldr, ldr, Ap + n1 * ldap, ldap, step);
 }
 
 void trsm_right_upper(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, const double* R,
-                      int64_t ldr, double* Ap, int64_t ldap)
+                      int64_t ldr, double* Ap, int64_t ldap, double* pack)
 {
-    uint32_t step = 0;
-    trsm_rec(ex, m, n, A, lda, R, ldr, Ap, ldap, step);
+    const int64_t nblk = ceil_div(n, TB16);
+    launch<TrsmPack>(ex, nblk, nblk, TrsmPack::Args{n, R, ldr, pack});
+    const TrsmArgs t{m, n, A, lda, pack, Ap, ldap};
+    if (lda >= ((int64_t)1 << 26) || ldap >= ((int64_t)1 << 26)) launch<TrsmRows<true>>(ex, ceil_div(m, 64), 1, t);
+    else launch<TrsmRows<false>>(ex, ceil_div(m, 64), 1, t);
 }
 
 }  // namespace pne

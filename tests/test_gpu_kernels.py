@@ -48,3 +48,52 @@ def test_gram_register_tiles(pne, hpne, m, n, lda):
     sel = np.ones((n, n), bool) if hpne else np.tril(np.ones((n, n), bool))
     assert np.all(np.abs(Cg.cpu().numpy() - C)[sel] <= (tol * (np.abs(A).T @ np.abs(A)))[sel])
     assert np.all(np.abs(cg.cpu().numpy() - c) <= tol * (np.abs(A).T @ np.abs(b)))
+
+
+def well_conditioned_r(n, rng):
+    """Upper triangular with a diagonal in [1, 2] and small entries above it."""
+    return np.triu(rng.standard_normal((n, n)), 1) * (0.5 / np.sqrt(n)) + np.diag(1.0 + rng.random(n))
+
+
+@pytest.mark.parametrize("m,n,lda", [
+    (1, 1, 1), (16, 16, 16), (65, 17, 65), (63, 63, 64), (1000, 100, 1001),   # blocks, rows past the tile
+    (300, 128, 301), (300, 129, 300),             # one panel; two, packed R in the shared scratch
+    (1000, 257, 1001), (777, 385, 777),           # panels of 6 and 7 blocks, odd column starts
+    (1000, 3, 1 << 26),                           # 64-bit lane offsets
+])
+def test_right_substitution(pne, m, n, lda):
+    """A_p = A R^{-1} seen through C = A_p^T A_p.  Substitution in blocks
+    gives |dA_p| <= (n + 16) u |A_p| |R| |R^{-1}| elementwise (16: the group
+    inverses), the product another m u |A_p|^T |A_p|; the reference on the
+    host errs by no more."""
+    from scipy.linalg import solve_triangular
+    rng = np.random.default_rng(91 + m + n)
+    A = rng.standard_normal((m, n))
+    b = rng.standard_normal(m)
+    R = well_conditioned_r(n, rng)
+    Cg, cg, _, info = pne.pne_gram(dev(A, lda), torch.from_numpy(b).cuda(), dev(R))
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    Ap = solve_triangular(R, A.T, trans="T", lower=False).T
+    G = np.abs(Ap) @ np.abs(R) @ np.abs(np.linalg.inv(R))
+    aAp = np.abs(Ap)
+    tol = 2 * ((n + 16) * U * (G.T @ aAp + aAp.T @ G) + m * U * (aAp.T @ aAp))
+    sel = np.tril(np.ones((n, n), bool))
+    assert np.all((np.abs(Cg.cpu().numpy() - Ap.T @ Ap) <= tol)[sel])
+    tolc = 2 * ((n + 16) * U * (G.T @ np.abs(b)) + m * U * (aAp.T @ np.abs(b)))
+    assert np.all(np.abs(cg.cpu().numpy() - Ap.T @ b) <= tolc)
+
+
+@pytest.mark.parametrize("col", [0, 2, 5, 15, 16, 40])
+@pytest.mark.parametrize("val", [float("nan"), float("inf")])
+def test_right_substitution_nonfinite_column(pne, col, val):
+    """A non-finite entry of A reaches the columns of A_p from its own on, and
+    none to the left of it."""
+    m, n = 200, 48
+    rng = np.random.default_rng(3)
+    A = rng.standard_normal((m, n))
+    A[77, col] = val
+    R = well_conditioned_r(n, rng)
+    Cg, _, _, _ = pne.pne_gram(dev(A), torch.zeros(m, dtype=torch.float64, device="cuda"), dev(R))
+    d = np.diag(Cg.cpu().numpy())
+    assert np.all(np.isfinite(d[:col])) and not np.any(np.isfinite(d[col:]))
