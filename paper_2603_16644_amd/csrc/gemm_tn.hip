@@ -59,7 +59,7 @@ __device__ __forceinline__ void tn_lower_tile(int64_t id, int64_t& ti, int64_t& 
 template <bool WIDE>
 struct GemmTn {
     typedef GemmArgs Args;
-    static constexpr int NTH = 256, WPE = 2;
+    static constexpr int NTH = 256, WPE = WIDE ? 1 : 2;   // (64-bit addresses: 440 registers)
     static __device__ void run(const GemmArgs& g, int bx, int by);
 };
 
@@ -100,6 +100,9 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
         kend = ke < kend ? ke : kend;
         kbeg = ks;
     }
+    // (into scalar registers, where the buffer descriptors have to be)
+    ti = __builtin_amdgcn_readfirstlane((int)ti);
+    tj = __builtin_amdgcn_readfirstlane((int)tj);
     const int64_t i0 = ti * BM, j0 = tj * BM;
     // which of the 16 MFMA blocks the product needs (bit 4 a + c: rows 16 a,
     // columns 16 c)
@@ -125,17 +128,21 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
     double cs[4] = {0, 0, 0, 0};
 
     if (mask != 0 && kbeg < kend) {
-        typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
         const gpc pa = (gpc)((gp64)g.A + i0 * g.lda + kbeg), pb = (gpc)((gp64)g.B + j0 * g.ldb + kbeg);
         const gpc pv = (gpc)(gp64)(fold ? bv + kbeg : nullptr);
-        off_t oa[4], ob[4];   // the lane's column and K offset in each 16-column block, in bytes
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            // columns past the matrix read its last column (results not stored)
-            const int64_t il = M - 1 - i0, jl = N - 1 - j0, c = t * 16 + r16;
-            oa[t] = (off_t)(((c < il ? c : il) * g.lda + 2 * g4) * 8);
-            ob[t] = (off_t)(((c < jl ? c : jl) * g.ldb + 2 * g4) * 8);
-        }
+        // last column of each operand's 64 (columns past the matrix read it;
+        // results not stored), and the lane's column and K offset in each
+        // 16-column block, in bytes
+        const int ila = (int)(M - 1 - i0 < 63 ? M - 1 - i0 : 63), ilb = (int)(N - 1 - j0 < 63 ? N - 1 - j0 : 63);
+        const uint32_t lda8 = (uint32_t)(g.lda * 8), ldb8 = (uint32_t)(g.ldb * 8);
+        auto oa = [&](int t) {
+            const int c = t * 16 + r16;
+            return ((uint64_t)(c < ila ? c : ila) * g.lda + 2 * g4) * 8;
+        };
+        auto ob = [&](int t) {
+            const int c = t * 16 + r16;
+            return ((uint64_t)(c < ilb ? c : ilb) * g.ldb + 2 * g4) * 8;
+        };
         const uint32_t ov = 16 * g4;
         const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pa, 0, -1, 0x00027000);
         const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pb, 0, -1, 0x00027000);
@@ -145,15 +152,22 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
             if constexpr (WIDE) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    xa[b][t] = *(gpv2)(pa + 8 * k + oa[t]);
-                    xb[b][t] = *(gpv2)(pb + 8 * k + ob[t]);
+                    xa[b][t] = *(gpv2)(pa + 8 * k + oa(t));
+                    xb[b][t] = *(gpv2)(pb + 8 * k + ob(t));
                 }
             } else {
+                // (column offsets formed anew from an opaque lane index:
+                // kept in registers they would cost the last eight)
                 const int so = (int)(8 * k);
+                int r = r16;
+                asm volatile("" : "+v"(r));
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    xa[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)oa[t], so, 0));
-                    xb[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)ob[t], so, 0));
+                    const int c = t * 16 + r, ca = c < ila ? c : ila, cb = c < ilb ? c : ilb;
+                    xa[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            ra, (int)((uint32_t)ca * lda8 + 16 * g4), so, 0));
+                    xb[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            rb, (int)((uint32_t)cb * ldb8 + 16 * g4), so, 0));
                 }
             }
         };
@@ -173,6 +187,7 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
         };
         auto fold_step = [&](auto bufc, int64_t k) {
             constexpr int b = decltype(bufc)::value;
+            if (!fold) return;
             const v2d8 v = *(gpv2)(pv + 8 * k + ov);
 #pragma unroll
             for (int t = 0; t < 4; ++t) cs[t] += xa[b][t][0] * v[0] + xa[b][t][1] * v[1];
@@ -207,10 +222,8 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
                 else loop(std::integral_constant<unsigned, 0xffffu>{}, F{});
             } else if (mask == 0xf731u && fold) {
                 loop(std::integral_constant<unsigned, 0xf731u>{}, T{});
-            } else if (fold) {
-                loop(std::integral_constant<unsigned, 0>{}, T{});
             } else {
-                loop(std::integral_constant<unsigned, 0>{}, F{});
+                loop(std::integral_constant<unsigned, 0>{}, T{});
             }
         }
         // the K values left over (less than a turn): zero past the end on
@@ -222,8 +235,8 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
                 const double v = (fold && in) ? *(gp64)(pv + 8 * (k + h) + ov) : 0.0;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    xa[0][t][h] = in ? *(gp64)(pa + 8 * (k + h) + oa[t]) : 0.0;
-                    xb[0][t][h] = in ? *(gp64)(pb + 8 * (k + h) + ob[t]) : 0.0;
+                    xa[0][t][h] = in ? *(gp64)(pa + 8 * (k + h) + oa(t)) : 0.0;
+                    xb[0][t][h] = in ? *(gp64)(pb + 8 * (k + h) + ob(t)) : 0.0;
                     cs[t] += xa[0][t][h] * v;
                 }
             }

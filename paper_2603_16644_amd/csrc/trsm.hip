@@ -151,7 +151,8 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
     __shared__ __attribute__((aligned(16))) v2d sd[2][DTAB / 2];
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int w = tid >> 6;
-    const int64_t m = a.m, n = a.n, nblk = (n + TB16 - 1) / TB16;
+    const int64_t m = a.m, n = a.n;
+    const int nblk = (int)((n + TB16 - 1) / TB16);
     // uniform first row of the work-group and the lane's row below it (rows
     // past the matrix read its last row and are not stored)
     const int64_t i0 = (int64_t)bx * 64;
@@ -166,35 +167,38 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
     // X(row, 4 j4 + g)
     auto xat = [&](int64_t j4) { return (gw64)(Xb + j4 * (a.ldx * 32) + ox); };
     const gpc pk = (gpc)(gp64)a.pack;
-    const gpc tabs = pk + nblk * (nblk + 1) / 2 * (BLK * 8);
-    // panels of equal width
-    const int64_t np = (nblk + PANEL - 1) / PANEL, pw = (nblk + np - 1) / np;
+    const gpc tabs = pk + (int64_t)nblk * (nblk + 1) / 2 * (BLK * 8);
+    // panels of equal width (in a scalar register, like everything the buffer
+    // descriptors below are made from)
+    const int np = (nblk + PANEL - 1) / PANEL, pw = __builtin_amdgcn_readfirstlane((nblk + np - 1) / np);
 
     // strip of the work: panel (first block lp0, lnb blocks) and block row lkb
     // of R; strips lkb < lp0 come before the panel's own
-    int64_t lp0 = 0, lkb = 0;            // strip that is loaded next
-    int lnb = (int)(pw < nblk ? pw : nblk);
+    int lp0 = 0, lkb = 0;                // strip that is loaded next
+    int lnb = pw < nblk ? pw : nblk;
     v4i vs[PANEL / 2], vd;               // a strip: up to 16 blocks of 128 16-byte entries, a diagonal table
     const int vo = tid * 16;
     // (buffer loads: the range check puts zeros past the strip's end without
     // a branch, so the loads stay in flight across the multiplications)
     auto fetch = [&]() {
         const bool live = lp0 < nblk;
-        const int64_t j0 = lkb < lp0 ? lp0 : lkb;   // (own strips start at the diagonal)
-        const gpc src = pk + (live ? pack_block(nblk, lkb, j0) * (BLK * 8) : 0);
-        const int bytes = live ? (int)(lp0 + lnb - j0) * (BLK * 8) : 0;
+        const int j0 = lkb < lp0 ? lp0 : lkb;   // (own strips start at the diagonal)
+        const int first = __builtin_amdgcn_readfirstlane(live ? (int)pack_block(nblk, lkb, j0) : 0);
+        const int bytes = __builtin_amdgcn_readfirstlane(live ? (lp0 + lnb - j0) * (BLK * 8) : 0);
+        const gpc src = pk + (int64_t)first * (BLK * 8);
         const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)src, 0, bytes, 0x00027000);
 #pragma unroll
         for (int q = 0; q < PANEL / 2; ++q)
             vs[q] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rs, vo + 4096 * q, 0, 0));
-        const gpc dsrc = tabs + (live ? lkb * (DTAB * 8) : 0);
-        const auto rd = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)dsrc, 0, live ? DTAB * 8 : 0, 0x00027000);
+        const int dk = __builtin_amdgcn_readfirstlane(live ? lkb : 0);
+        const gpc dsrc = tabs + (int64_t)dk * (DTAB * 8);
+        const auto rd = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)dsrc, 0, DTAB * 8, 0x00027000);
         vd = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rd, vo, 0, 0));
     };
     auto advance = [&]() {
         if (++lkb == lp0 + lnb) {
             lp0 += lnb;
-            lnb = (int)(nblk - lp0 < pw ? nblk - lp0 : pw);
+            lnb = nblk - lp0 < pw ? nblk - lp0 : pw;
             lkb = 0;
         }
     };
@@ -219,15 +223,15 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
     fetch();
 
     v4d acc[PANEL];
-    for (int64_t p0 = 0; p0 < nblk;) {
-        const int nb = (int)(nblk - p0 < pw ? nblk - p0 : pw);
+    for (int p0 = 0; p0 < nblk;) {
+        const int nb = nblk - p0 < pw ? nblk - p0 : pw;
         // columns of A
 #pragma unroll
         for (int c = 0; c < PANEL; ++c)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 // (columns past n read the last one and are not stored)
-                const int64_t j = TB16 * (p0 + c) + 4 * q, jl = n - 1 - j;
+                const int64_t j = (int64_t)TB16 * (p0 + c) + 4 * q, jl = n - 1 - j;
                 acc[c][q] = jl >= 0 ? *(gp64)(Ab + j * (a.lda * 8) + ((g4 < jl ? g4 : (int)jl) * lda8 + oi)) : 0.0;
             }
         // blocks C0 .. C1 - 1 of the panel minus X times a strip that starts at
@@ -253,26 +257,22 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // products with the earlier panels; NG groups of four blocks
-        auto outer = [&](auto ngc) {
-            constexpr int NG = decltype(ngc)::value;
+        // products with the earlier panels (with two panels or more each has
+        // more than four blocks, but for the last)
+        if (p0 > 0) {
             double xn[4], xc[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) xn[q] = *xat(q);
-            for (int64_t kb = 0; kb < p0; ++kb) {
+            for (int kb = 0; kb < p0; ++kb) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) xc[q] = xn[q];
-                const int64_t kn = kb + 1 < p0 ? kb + 1 : kb;
+                const int kn = kb + 1 < p0 ? kb + 1 : kb;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) xn[q] = *xat(4 * kn + q);
                 turn();
-                strip_mult(sr[buf], xc, std::integral_constant<int, 0>{}, std::integral_constant<int, 4 * NG>{});
+                strip_mult(sr[buf], xc, std::integral_constant<int, 0>{}, std::integral_constant<int, PANEL>{});
                 buf ^= 1;
             }
-        };
-        if (p0 > 0) {
-            if (nb > 4) outer(std::integral_constant<int, 2>{});
-            else outer(std::integral_constant<int, 1>{});
         }
         // the panel's own triangle
         auto own = [&](auto bc) {
@@ -284,10 +284,15 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2]) ||
                                                              !isfinite(t[3])) != 0, 0)) {
                 // a non-finite entry: the zeros of the inverses must not
-                // carry it into the columns left of it
+                // carry it into the columns left of it.  (The lane index is
+                // made opaque so that nothing of this rare branch is kept in
+                // registers outside it.)
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                const int r16 = ln & 15, g4 = ln >> 4;
 #pragma unroll 1
                 for (int q = 0; q < 4; ++q) {
-                    const v2d f = d[q * 64 + lane];
+                    const v2d f = d[q * 64 + ln];
                     const double tq = q == 0 ? t[0] : q == 1 ? t[1] : q == 2 ? t[2] : t[3];
                     double x = 0.0;
                     for (int k = 0; k < 4; ++k) {
@@ -316,7 +321,7 @@ __device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, i
             acc[B] = t;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int64_t j4 = 4 * (p0 + B) + q;
+                const int64_t j4 = 4 * (int64_t)(p0 + B) + q;
                 if (in && 4 * j4 + g4 < n) *xat(j4) = t[q];
             }
             // the blocks right of it, up to the next multiple of four past nb
