@@ -283,24 +283,21 @@ void run_gram(Exec& ex, const Problem& p, const double* dA, const double* db, co
     mark(ex, PH_GRAM_REDUCE);
 }
 
-// Cholesky (PNE) or LU with partial pivoting (HPNE) of C in place, then the
-// inverses of the 64 x 64 diagonal blocks the triangular solves use.
+// Cholesky (PNE; L into the shared scratch, which is free from here on, and
+// L^T) or LU with partial pivoting (HPNE) of C in place, then the inverses of
+// the 64 x 64 diagonal blocks the triangular solves use.
 void run_factor(Exec& ex, const Problem& p, const Buffers& b, int32_t* dinfo)
 {
     const int64_t n = p.n;
     const int hpne = p.hpne;
     ex.stage(ST_FACTOR);
     if (hpne) lu_factor(ex, n, b.C, n, b.piv, dinfo);
-    else cholesky<double>(ex, n, b.C, n, dinfo, b.dinv1);
+    else cholesky64(ex, n, b.C, n, (double*)b.scratch, n, b.Lt, n, b.dinv1, nullptr, 0.0, dinfo);
     ex.stage(ST_FACTOR_INV);
-    if (hpne) {
-        inv_diag_blocks<double>(ex, n, b.C, n, 1, 0, 1, b.dinv1);
-        inv_diag_blocks<double>(ex, n, b.C, n, 0, 0, 0, b.dinv2);
-    } else {
-        inv_diag_blocks<double>(ex, n, b.R, n, 0, 0, 0, b.dinv2);
-        transpose_f64(ex, n, n, b.C, n, b.Lt, n);
-        transpose_dinv(ex, n, b.dinv1, b.dinv1t);
-    }
+    const double* L = hpne ? b.C : (const double*)b.scratch;
+    const InvTriMat lo{L, n, 1, hpne ? 1 : 0, b.dinv1, hpne ? nullptr : b.dinv1t};
+    const InvTriMat up{hpne ? b.C : b.R, n, 0, 0, b.dinv2, nullptr};
+    inv_diag64(ex, n, lo, &up);
     mark(ex, PH_FACTOR);
 }
 
@@ -315,7 +312,7 @@ pne_status run_solve(Exec& ex, const Problem& p, const double* dA, const double*
     run_factor(ex, p, b, dinfo);
     ex.stage(ST_SOLVE);
     if (hpne) lu_solve_lb(ex, n, b.C, n, b.piv, b.dinv1, b.dinv2, b.c, dx, b.flags, dinfo);
-    else pne_solve_lb(ex, n, b.C, n, b.dinv1, b.Lt, b.dinv1t, b.R, n, b.dinv2, b.c, dx, b.t, b.flags, dinfo);
+    else pne_solve_lb(ex, n, (double*)b.scratch, n, b.dinv1, b.Lt, b.dinv1t, b.R, n, b.dinv2, b.c, dx, b.t, b.flags, dinfo);
     mark(ex, PH_SOLVE);
     ex.stage(ST_REFINE);
     for (int k = 0; k < p.refine; ++k) {
@@ -323,7 +320,7 @@ pne_status run_solve(Exec& ex, const Problem& p, const double* dA, const double*
         residual(ex, m, n, dA, lda, db, dx, b.r);
         gemv_t(ex, m, n, b.Ap, ap_ld(m), b.r, b.y, b.gv);
         if (hpne) lu_solve_lb(ex, n, b.C, n, b.piv, b.dinv1, b.dinv2, b.y, b.d, b.flags, dinfo);
-        else pne_solve_lb(ex, n, b.C, n, b.dinv1, b.Lt, b.dinv1t, b.R, n, b.dinv2, b.y, b.d, b.t, b.flags, dinfo);
+        else pne_solve_lb(ex, n, (double*)b.scratch, n, b.dinv1, b.Lt, b.dinv1t, b.R, n, b.dinv2, b.y, b.d, b.t, b.flags, dinfo);
         axpy_update(ex, n, dx, b.d);
     }
     ex.stage(ST_FINISH);
@@ -925,7 +922,7 @@ pne_status pne_gram(int64_t m, int64_t n, const double* dA, int64_t lda, const d
     copy_f64(ex, n, n, dR, ldr, b.R, n);
     run_gram(ex, p, dA, db, b);
     if (factor) run_factor(ex, p, b, dinfo);
-    copy_f64(ex, n, n, b.C, n, dC, ldc);
+    copy_f64(ex, n, n, factor && !hpne ? (double*)b.scratch : b.C, n, dC, ldc);
     copy_f64(ex, n, 1, b.c, n, dc, n);
     if (factor && hpne) copy_i32(ex, n, b.piv, dpiv);
     return hipGetLastError() == hipSuccess ? PNE_OK : PNE_EHIP;

@@ -233,7 +233,7 @@ int condest_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, do
     gemm_ddf(ex, g);
     launch<Norm1Sym>(ex, 1, 1, Norm1Sym::Args{n, G, n, g1});
     ex.stage(ST_CONDEST_FACTOR);
-    cholesky<float>(ex, n, G, n, info, DL);
+    cholesky_f32(ex, n, G, n, info, DL);
     ex.stage(ST_CONDEST_EST);
     launch<Hager>(ex, 1, 1, Hager::Args{n, G, n, DL, g1, info, dk0, dchoice, 0});
     return launch_status(ex);

@@ -112,11 +112,27 @@ void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int
 size_t trsm_pack_bytes(int64_t n);
 void trsm_right_upper(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, const double* R,
                       int64_t ldr, double* Ap, int64_t ldap, double* pack);
-// Cholesky (lower, in place) of the n x n matrix C; info word gets 2000+k.
-// Dinv (dinv_elems(n) values) receives the inverses of the 64 x 64 diagonal
-// blocks of L in the layout of inv_diag_blocks.
-template <typename T>
-void cholesky(Exec& ex, int64_t n, T* C, int64_t ldc, int32_t* info, T* Dinv);
+// Cholesky of the n x n matrix C (lower triangle read, destroyed): L (ldl;
+// null: not wanted) and L^T (ldt) written, info word gets 2000+k.  tab:
+// scratch of dinv_elems(n) values.  tau > 0: pivots below tau C_kk are raised
+// to it and nothing is reported; gd: scratch of n values.
+void cholesky64(Exec& ex, int64_t n, double* C, int64_t ldc, double* L, int64_t ldl, double* Lt, int64_t ldt,
+                double* tab, double* gd, double tau, int32_t* info);
+// Inverses of the 64 x 64 diagonal blocks of a triangular matrix into D and
+// their transposes into Dt (dinv_elems(n) values each; either may be null);
+// of a second matrix of the same order in the same launch when b is given.
+struct InvTriMat {
+    const double* M;
+    int64_t ld;
+    int lower, unit;
+    double* D;
+    double* Dt;
+};
+void inv_diag64(Exec& ex, int64_t n, const InvTriMat& a, const InvTriMat* b = nullptr);
+// FP32 Cholesky (lower, in place); Dinv (dinv_elems(n) values) receives the
+// inverses of the 64 x 64 diagonal blocks of L in the layout of
+// inv_diag_blocks.
+void cholesky_f32(Exec& ex, int64_t n, float* C, int64_t ldc, int32_t* info, float* Dinv);
 // LU with partial pivoting in place; piv 0-based; info 3000+k.
 void lu_factor(Exec& ex, int64_t n, double* C, int64_t ldc, int32_t* piv, int32_t* info);
 // Householder QR (R only) of the s x n matrix W (in place); R (FP64, n x n,
@@ -152,10 +168,6 @@ void upper_solve_lb(Exec& ex, int64_t n, const double* U, int64_t ld, const doub
                     int32_t* flags, int32_t* info);
 // *info = 1000 + k + 1 for the first zero or non-finite R(k, k) (if still 0)
 void check_r_diag(Exec& ex, int64_t n, const double* R, int64_t ldr, int32_t* info);
-// out (c x r, ldo) = in^T (in r x c, ldi)
-void transpose_f64(Exec& ex, int64_t r, int64_t c, const double* in, int64_t ldi, double* out, int64_t ldo);
-// transposes of the 64 x 64 blocks of a block-inverse array (dinv_elems(n))
-void transpose_dinv(Exec& ex, int64_t n, const double* D, double* Dt);
 bool lu_supported(int64_t n);
 // r = b - A x
 void residual(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, const double* b, const double* x,

@@ -89,8 +89,8 @@ pne_status nne_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const 
     gemm_f64_partials(ex, g);
     gemm_f64_reduce(ex, g);
     lu_factor(ex, n, b.C, n, b.piv, dinfo);
-    inv_diag_blocks<double>(ex, n, b.C, n, 1, 0, 1, b.dinv1);
-    inv_diag_blocks<double>(ex, n, b.C, n, 0, 0, 0, b.dinv2);
+    const InvTriMat lo{b.C, n, 1, 1, b.dinv1, nullptr}, up{b.C, n, 0, 0, b.dinv2, nullptr};
+    inv_diag64(ex, n, lo, &up);
     lu_solve_lb(ex, n, b.C, n, b.piv, b.dinv1, b.dinv2, b.c, dx, b.flags, dinfo);
     for (int32_t k = 0; k < refine_steps; ++k) {
         residual(ex, m, n, dA, lda, db, dx, b.r);

@@ -208,7 +208,7 @@ pne_status qr_ls_solve(int64_t m, int64_t n, const double* dA, int64_t lda, cons
     const double* R = bufs[(p.counts.size() - 1) & 1];
     const int64_t ldr = p.N1;
     check_r_diag(ex, n, R, ldr, dinfo);
-    inv_diag_blocks<double>(ex, n, R, ldr, 0, 0, 0, b.DR);
+    inv_diag64(ex, n, InvTriMat{R, ldr, 0, 0, b.DR, nullptr});
     upper_solve_lb(ex, n, R, ldr, b.DR, R + n * ldr, dx, b.flags, dinfo);
     fill_nan_on_info(ex, n, dx, dinfo);
     return hipGetLastError() == hipSuccess ? PNE_OK : PNE_EHIP;

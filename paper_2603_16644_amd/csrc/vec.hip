@@ -23,50 +23,7 @@ void inv_diag_blocks(Exec& ex, int64_t n, const T* M, int64_t ld, int lower, int
     if (lower) launch<InvDiag<T, false>>(ex, nblocks, 1, a);
     else launch<InvDiag<T, true>>(ex, nblocks, 1, a);
 }
-template void inv_diag_blocks<double>(Exec&, int64_t, const double*, int64_t, int, int, int, double*, int64_t, int64_t);
 template void inv_diag_blocks<float>(Exec&, int64_t, const float*, int64_t, int, int, int, float*, int64_t, int64_t);
-
-// out(j, i) = in(i, j) through a 64 x 64 LDS tile per work-group.
-struct Transpose {
-    struct Args {
-        int64_t r, c;
-        const double* in;
-        int64_t ldi;
-        double* out;
-        int64_t ldo;
-        int64_t in_stride, out_stride;   // per blockIdx.y (batches of small matrices)
-    };
-    static constexpr int NTH = 256, WPE = 0;
-    static __device__ void run(const Args& a, int bx, int by)
-    {
-        __shared__ double t[64 * 65];
-        const int64_t tiles_r = (a.r + 63) / 64;
-        const int64_t i0 = (bx % tiles_r) * 64, j0 = (bx / tiles_r) * 64;
-        const double* __restrict__ in = a.in + by * a.in_stride;
-        double* __restrict__ out = a.out + by * a.out_stride;
-        for (int e = threadIdx.x; e < 64 * 64; e += NTH) {
-            const int ii = e & 63, jj = e >> 6;
-            const int64_t i = i0 + ii, j = j0 + jj;
-            t[jj * 65 + ii] = (i < a.r && j < a.c) ? in[i + j * a.ldi] : 0.0;
-        }
-        __syncthreads();
-        for (int e = threadIdx.x; e < 64 * 64; e += NTH) {
-            const int jj = e & 63, ii = e >> 6;
-            const int64_t i = i0 + ii, j = j0 + jj;
-            if (i < a.r && j < a.c) out[j + i * a.ldo] = t[jj * 65 + ii];
-        }
-    }
-};
-
-void transpose_f64(Exec& ex, int64_t r, int64_t c, const double* in, int64_t ldi, double* out, int64_t ldo)
-{
-    launch<Transpose>(ex, ceil_div(r, 64) * ceil_div(c, 64), 1, Transpose::Args{r, c, in, ldi, out, ldo, 0, 0});
-}
-
-void transpose_dinv(Exec& ex, int64_t n, const double* D, double* Dt)
-{
-    launch<Transpose>(ex, 1, ceil_div(n, TB), Transpose::Args{TB, TB, D, TB, Dt, TB, TB * TB, TB * TB});
-}
 
 // ---------------------------------------------------------------- multi-work-group triangular solve
 // x := U^{-1} x for a triangular n x n matrix U (column-major, lower or

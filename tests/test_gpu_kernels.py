@@ -97,3 +97,23 @@ def test_right_substitution_nonfinite_column(pne, col, val):
     Cg, _, _, _ = pne.pne_gram(dev(A), torch.zeros(m, dtype=torch.float64, device="cuda"), dev(R))
     d = np.diag(Cg.cpu().numpy())
     assert np.all(np.isfinite(d[:col])) and not np.any(np.isfinite(d[col:]))
+
+
+@pytest.mark.parametrize("n", [1, 3, 5, 16, 17, 63, 64, 65, 81, 128, 130, 257, 700])
+def test_cholesky_blocks(pne, n):
+    """The factor of C = A^T A (R = I): groups of four, blocks of 16 and 64 and
+    their remainders.  Cholesky's backward error |L L^T - C| <= (n + 1) u |L|
+    |L|^T, widened by the inverses of four columns (16) and the rounding of
+    the product (2)."""
+    m = n + 300
+    rng = np.random.default_rng(17 + n)
+    A = rng.standard_normal((m, n)) * np.exp(rng.uniform(-3, 3, n))   # columns of unequal size
+    b = np.zeros(m)
+    C0, _, _, _ = pne.pne_gram(dev(A), torch.from_numpy(b).cuda(), dev(np.eye(n)))
+    L, _, _, info = pne.pne_gram(dev(A), torch.from_numpy(b).cuda(), dev(np.eye(n)), factor=True)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    C, L = np.tril(C0.cpu().numpy()), np.tril(L.cpu().numpy())
+    tol = (n + 19) * U * np.abs(L) @ np.abs(L).T
+    assert np.all(np.abs(np.tril(L @ L.T) - C) <= np.tril(2 * tol))
+    assert np.all(np.diag(L) > 0)
