@@ -113,7 +113,11 @@ size_t pne_workspace_size(int64_t m, int64_t n, const pne_opts* opts, int hpne);
  *   1. [AUTO] condition estimate and precision pick (see cond_est);
  *   2. A_s = Omega A, Omega s x m with N(0, 1/s) entries generated on the fly
  *      from (seed, problem_id, row, column) (Algorithm 1 "Sketch");
- *   3. Householder QR of A_s in qr_prec, R_s promoted to FP64;
+ *   3. triangular factor of A_s, R_s promoted to FP64: Householder QR in
+ *      FP64 for qr_prec FP64; otherwise A_s and R_s rounded to qr_prec and
+ *      the factor between them from the Cholesky factor of the FP64 Gram
+ *      matrix A_s^T A_s (the QR factor up to the signs of its rows, which
+ *      cancel; a pivot below FP32 roundoff of its column is raised to it);
  *   4. A_p = A R_s^{-1} (FP64, blocked substitution);
  *   5. C = A_p^T A_p, c = A_p^T b (FP64);
  *   6. Cholesky C = L L^T, L L^T y = c, R_s x = y (FP64);
@@ -136,7 +140,8 @@ pne_status hpne_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const
                       int32_t* dinfo, pne_info* hinfo, pne_stream_t stream);
 
 /* sketch_precond: the preconditioner alone (Algorithm 1 steps "Sketch",
- * "Thin QR", "Promote R_s"; Section 6.2).  Writes the upper triangle of the
+ * "Thin QR", "Promote R_s"; Section 6.2), by Householder QR in every
+ * precision.  Writes the upper triangle of the
  * n x n FP64 matrix R_s into dR (ldr >= n); the strict lower triangle is set
  * to zero.  Workspace: sketch_precond_workspace_size. */
 size_t sketch_precond_workspace_size(int64_t m, int64_t n, const pne_opts* opts);
@@ -165,8 +170,8 @@ pne_status cond_est(int64_t m, int64_t n, const double* dA, int64_t lda, float* 
  * is zero or not finite); *dchoice by the thresholds of cond_est.  kappa(A_s)
  * is within the condition number of the sketched orthonormal basis (< 3.73
  * for s = 3n) of kappa(A).  pne_opts.cond_method = 1 makes AUTO use this
- * estimate; when it picks FP32 for both steps, its R is the preconditioner
- * (the FP32 sketch and QR are not repeated).
+ * estimate; when it picks FP32 for both steps, the preconditioner comes from
+ * its sketch (which is not drawn again).
  * Workspace: cond_est_qr_workspace_size. */
 size_t cond_est_qr_workspace_size(int64_t m, int64_t n, int64_t s);
 pne_status cond_est_qr(int64_t m, int64_t n, const double* dA, int64_t lda, int64_t s, uint64_t seed,

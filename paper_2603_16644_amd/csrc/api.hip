@@ -189,17 +189,33 @@ inline void mark(Exec& ex, int phase)
     if (!ex.recording()) prof_mark(phase, ex.st);
 }
 
+// Slots of the split sketch Gram product: what the scratch holds, and at most
+// m / n, which every FP32 sketch's scratch holds (so that the estimate below
+// and a solve split alike).
+int64_t gram_slots(const Problem& p, size_t bytes)
+{
+    const int64_t have = (int64_t)(bytes / ((size_t)p.n * p.n * 8)), most = p.m / p.n;
+    return have < most ? have : most;
+}
+
 // The condition estimate of one problem into b.k0 / b.choice: the FP32 Gram
 // estimate of Section 6.1, or (cond_method 1, no known kappa) the estimate
-// from the FP32 QR of the FP32 sketch, which leaves that sketch in b.W and
-// its R factor in b.R.
+// from the FP32 QR of the FP32 sketch.  In a solver the latter also leaves
+// the preconditioner of that sketch in b.R, in case the pick is FP32 (the
+// QR's own R goes to b.C); otherwise the QR's R is in b.R.
 int run_condest(Exec& ex, const Problem& p, const double* dA, const pne_opts* o, uint32_t pid, const Buffers& b,
-                size_t scratch_cap)
+                size_t scratch_cap, bool solver)
 {
-    if (p.cond_method == 1 && !(o->known_kappa > 0.0))
-        return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.R,
-                              b.scratch, scratch_cap);
-    return condest_run(ex, p.m, p.n, dA, p.lda, o->known_kappa, b.k0, b.choice, b.scratch, scratch_cap);
+    if (!(p.cond_method == 1 && !(o->known_kappa > 0.0)))
+        return condest_run(ex, p.m, p.n, dA, p.lda, o->known_kappa, b.k0, b.choice, b.scratch, scratch_cap);
+    if (!solver)
+        return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.R, b.scratch,
+                              scratch_cap);
+    // (b.y holds the two words of the factor's own bookkeeping; a zero
+    // diagonal shows in the estimate, which then does not pick FP32)
+    const SketchFactorBuffers sf{b.R, b.C, b.dinv1, b.c, (uint32_t*)b.y, (int32_t*)b.y + 1, p.m / p.n};
+    return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.C, b.scratch,
+                          scratch_cap, &sf);
 }
 
 // With the QR estimate and both precisions AUTO, an FP32 pick means the
@@ -213,13 +229,13 @@ bool precond_from_condest(const Problem& p, const pne_opts* o, int sk, int qr)
 
 // Resolve AUTO through the condition estimate (one host synchronisation).
 pne_status resolve_precision(Exec& ex, const Problem& p, const double* dA, const pne_opts* o, const Buffers& b,
-                             size_t scratch_cap, int* sk, int* qr, float* k0)
+                             size_t scratch_cap, bool solver, int* sk, int* qr, float* k0)
 {
     *sk = p.sketch_prec;
     *qr = p.qr_prec;
     *k0 = NAN;
     if (*sk != PNE_PREC_AUTO && *qr != PNE_PREC_AUTO) return PNE_OK;
-    int rc = run_condest(ex, p, dA, o, o->problem_id, b, scratch_cap);
+    int rc = run_condest(ex, p, dA, o, o->problem_id, b, scratch_cap, solver);
     if (rc) return (pne_status)rc;
     float hk0;
     int32_t hch;
@@ -234,9 +250,11 @@ pne_status resolve_precision(Exec& ex, const Problem& p, const double* dA, const
 
 size_t scratch_cap_of(const Buffers& b) { return (size_t)((char*)b.W - (char*)b.scratch); }
 
-// sketch + QR -> b.R
+// sketch and its triangular factor -> b.R: the Householder QR for FP64 and
+// where R itself is asked for, else (solvers, where the signs of its rows
+// cancel) the factor from the sketch's Gram matrix.
 pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t seed, uint32_t pid, int sk,
-                       int qr, const Buffers& b, int32_t* dinfo)
+                       int qr, const Buffers& b, int32_t* dinfo, bool solver)
 {
     const bool w64 = (qr == PNE_PREC_FP64);
     const size_t cap = scratch_cap_of(b);
@@ -246,7 +264,11 @@ pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t se
                  : sketch_run(ex, p.m, p.n, dA, p.lda, p.s, seed, pid, sk, p.br, w64 ? nullptr : (float*)b.W, p.s,
                               w64 ? (double*)b.W : nullptr, p.s, b.scratch, cap);
     if (rc) return (pne_status)rc;
-    rc = qr_r(ex, p.s, p.n, b.W, p.s, qr, b.R, p.n, dinfo, b.scratch, cap);
+    if (solver && !w64)
+        rc = sketch_factor(ex, p.s, p.n, (float*)b.W, p.s, qr, b.R, p.n, b.C, (double*)b.scratch, gram_slots(p, cap),
+                           b.dinv1, b.c, (uint32_t*)b.y, dinfo);
+    else
+        rc = qr_r(ex, p.s, p.n, b.W, p.s, qr, b.R, p.n, dinfo, b.scratch, cap);
     mark(ex, PH_QR);
     return (pne_status)rc;
 }
@@ -372,11 +394,11 @@ pne_status solve_impl(int hpne, int64_t m, int64_t n, const double* dA, int64_t 
     zero_i32(ex, 1, dinfo);
     int sk, qr;
     float k0;
-    pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), &sk, &qr, &k0);
+    pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), true, &sk, &qr, &k0);
     if (rc) return rc;
     mark(ex, PH_CONDEST);
     if (!precond_from_condest(p, o, sk, qr)) {
-        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo);
+        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, true);
         if (rc) return rc;
     }
     rc = run_solve(ex, p, dA, db, dx, b, dinfo);
@@ -462,7 +484,7 @@ pne_status record_batch(Recorder& rec, int64_t batch, const pne_problem_desc* hd
         pne_status rc = PNE_OK;
         if (!precond_from_condest(p, o, sk[i], qr[i])) {
             rc = run_precond(ex, p, A, o->seed, (uint32_t)hd[i].problem_id, sk[i], qr[i], L.buf[i],
-                             dinfo ? dinfo + i : nullptr);
+                             dinfo ? dinfo + i : nullptr, true);
             if (rc) return rc;
         }
         rc = run_solve(ex, p, A, b, x, L.buf[i], dinfo ? dinfo + i : nullptr);
@@ -482,7 +504,7 @@ pne_status record_condest(Recorder& rec, int64_t batch, const pne_problem_desc* 
         const Problem& p = L.prob[i];
         const Buffers& b = L.buf[i];
         int rc = run_condest(ex, p, dA_base ? dA_base + hd[i].a_offset : nullptr, o, (uint32_t)hd[i].problem_id, b,
-                             scratch_cap_of(b));
+                             scratch_cap_of(b), true);
         if (rc) return (pne_status)rc;
     }
     return PNE_OK;
@@ -781,10 +803,10 @@ pne_status sketch_precond(int64_t m, int64_t n, const double* dA, int64_t lda, c
     zero_i32(ex, 1, dinfo);
     int sk, qr;
     float k0;
-    pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), &sk, &qr, &k0);
+    pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), false, &sk, &qr, &k0);
     if (rc) return rc;
     if (!precond_from_condest(p, o, sk, qr)) {
-        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo);
+        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, false);
         if (rc) return rc;
     }
     copy_f64(ex, n, n, b.R, n, dR, ldr);

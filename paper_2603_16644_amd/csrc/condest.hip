@@ -250,9 +250,9 @@ int condest_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, do
 // orthonormal basis of kappa(A) (< 3.73 asymptotically for s = 3n), and an
 // FP32 QR resolves kappa up to about 1/u_32, so the single-precision band
 // of Algorithm 1 (kappa0 <= 8) is reachable, which the FP32 Gram estimate
-// (breakdown from kappa ~ 4e3) is not.  W (s x n FP32) and R (n x n FP64)
-// receive the sketch and R: they are exactly the preconditioner an FP32
-// sketch and FP32 QR with the same seed compute.
+// (breakdown from kappa ~ 4e3) is not.  The sketch is exactly the one an FP32
+// solve with the same seed draws; with sf its preconditioner is formed from
+// it as that solve would (sketch_factor).
 
 // Rf = fl32(R) on and above the diagonal, 0 below; ||Rf||_1 into *out.
 struct RToF32 {
@@ -318,7 +318,7 @@ size_t condest_qr_workspace_bytes(int64_t m, int64_t n, int64_t s, int64_t kchun
 
 int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int64_t s, uint64_t seed,
                    uint32_t pid, float* dk0, int32_t* dchoice, float* W, double* R, void* work,
-                   size_t work_bytes)
+                   size_t work_bytes, const SketchFactorBuffers* sf)
 {
     if (n > 4096) return PNE_ENOTSUP;
     if (!qr_supported(s, PNE_PREC_FP32)) return PNE_ENOTSUP;
@@ -334,6 +334,12 @@ int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda,
     zero_i32(ex, 1, info);
     int rc = sketch_run(ex, m, n, A, lda, s, seed, pid, PNE_PREC_FP32, 128, W, s, nullptr, 0, rest, rest_bytes);
     if (rc) return rc;
+    if (sf) {
+        const int64_t have = (int64_t)(rest_bytes / ((size_t)n * n * 8));
+        rc = sketch_factor(ex, s, n, W, s, PNE_PREC_FP32, sf->R, n, sf->C, (double*)rest,
+                           have < sf->pslots ? have : sf->pslots, sf->tab, sf->gd, sf->amax, sf->info);
+        if (rc) return rc;
+    }
     rc = qr_r(ex, s, n, W, s, PNE_PREC_FP32, R, n, info, rest, rest_bytes);
     if (rc) return rc;
     // (no new stage: the launches below keep counting within the QR's last

@@ -2,7 +2,8 @@
 // is contiguous in memory (A: K x M, B: K x N, column-major), in 64 x 64
 // output tiles: the Gram products A_p^T A_p and A_p^T A with A_p^T b, B^T A
 // of the not-normal equations and small FP64 sketches (see tn_route for the
-// sizes; larger products run in 128 x 128 tiles in gemm.hip).
+// sizes; larger products run in 128 x 128 tiles in gemm.hip), and the FP64
+// Gram matrix of an FP32 sketch (gram_f32).
 //
 // An FP64 MFMA 16x16x4 keeps a SIMD's matrix core busy for 64 cycles and
 // needs one operand value per lane and side.  A wavefront holds the 64 x 64
@@ -56,18 +57,23 @@ __device__ __forceinline__ void tn_lower_tile(int64_t id, int64_t& ti, int64_t& 
 // and the loads are buffer loads (uniform base, one 32-bit offset register
 // per 16-column block, K advance in a scalar register), which leaves the
 // accumulators and both operand buffers in registers.
-template <bool WIDE>
+template <typename TI, bool WIDE>
 struct GemmTn {
     typedef GemmArgs Args;
     static constexpr int NTH = 256, WPE = WIDE ? 1 : 2;   // (64-bit addresses: 440 registers)
     static __device__ void run(const GemmArgs& g, int bx, int by);
 };
 
-template <bool WIDE>
-__device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int by)
+template <typename TI, bool WIDE>
+__device__ __forceinline__ void GemmTn<TI, WIDE>::run(const GemmArgs& g, int bx, int by)
 {
     constexpr int BM = 64;
-    constexpr int KS = 8, KL = 2 * KS;   // K values per step and per turn of the loop
+    constexpr int E = 16 / sizeof(TI);       // K values of a lane's 16 bytes
+    constexpr int KS = 4 * E, KL = 2 * KS;   // K values per step (64 bytes of a column) and per turn of the loop
+    constexpr int64_t SZ = sizeof(TI);
+    typedef TI vin __attribute__((ext_vector_type(E), aligned(sizeof(TI))));
+    typedef const __attribute__((address_space(1))) TI* gpi;
+    typedef const __attribute__((address_space(1))) vin* gpvi;
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t M = g.M, N = g.N;
@@ -118,7 +124,7 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
     const double* __restrict__ bv = (const double*)g.bvec;
     // op(A) bvec is formed beside the blocks on the diagonal (lower-triangle
     // products) or of the first tile column
-    const bool fold = bv != nullptr && (g.lower ? (i0 == j0) : (j0 == 0));
+    const bool fold = E == 2 && bv != nullptr && (g.lower ? (i0 == j0) : (j0 == 0));
 
     v4d acc[4][4];
 #pragma unroll
@@ -128,45 +134,45 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
     double cs[4] = {0, 0, 0, 0};
 
     if (mask != 0 && kbeg < kend) {
-        const gpc pa = (gpc)((gp64)g.A + i0 * g.lda + kbeg), pb = (gpc)((gp64)g.B + j0 * g.ldb + kbeg);
+        const gpc pa = (gpc)((gpi)g.A + i0 * g.lda + kbeg), pb = (gpc)((gpi)g.B + j0 * g.ldb + kbeg);
         const gpc pv = (gpc)(gp64)(fold ? bv + kbeg : nullptr);
         // last column of each operand's 64 (columns past the matrix read it;
         // results not stored), and the lane's column and K offset in each
         // 16-column block, in bytes
         const int ila = (int)(M - 1 - i0 < 63 ? M - 1 - i0 : 63), ilb = (int)(N - 1 - j0 < 63 ? N - 1 - j0 : 63);
-        const uint32_t lda8 = (uint32_t)(g.lda * 8), ldb8 = (uint32_t)(g.ldb * 8);
+        const uint32_t lda8 = (uint32_t)(g.lda * SZ), ldb8 = (uint32_t)(g.ldb * SZ);
         auto oa = [&](int t) {
             const int c = t * 16 + r16;
-            return ((uint64_t)(c < ila ? c : ila) * g.lda + 2 * g4) * 8;
+            return (uint64_t)(c < ila ? c : ila) * g.lda * SZ + 16 * g4;
         };
         auto ob = [&](int t) {
             const int c = t * 16 + r16;
-            return ((uint64_t)(c < ilb ? c : ilb) * g.ldb + 2 * g4) * 8;
+            return (uint64_t)(c < ilb ? c : ilb) * g.ldb * SZ + 16 * g4;
         };
         const uint32_t ov = 16 * g4;
         const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pa, 0, -1, 0x00027000);
         const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)pb, 0, -1, 0x00027000);
-        v2d8 xa[2][4], xb[2][4];
+        vin xa[2][4], xb[2][4];
         auto load = [&](auto bufc, int64_t k) {
             constexpr int b = decltype(bufc)::value;
             if constexpr (WIDE) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    xa[b][t] = *(gpv2)(pa + 8 * k + oa(t));
-                    xb[b][t] = *(gpv2)(pb + 8 * k + ob(t));
+                    xa[b][t] = *(gpvi)(pa + SZ * k + oa(t));
+                    xb[b][t] = *(gpvi)(pb + SZ * k + ob(t));
                 }
             } else {
                 // (column offsets formed anew from an opaque lane index:
                 // kept in registers they would cost the last eight)
-                const int so = (int)(8 * k);
+                const int so = (int)(SZ * k);
                 int r = r16;
                 asm volatile("" : "+v"(r));
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int c = t * 16 + r, ca = c < ila ? c : ila, cb = c < ilb ? c : ilb;
-                    xa[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(
+                    xa[b][t] = __builtin_bit_cast(vin, __builtin_amdgcn_raw_buffer_load_b128(
                                                             ra, (int)((uint32_t)ca * lda8 + 16 * g4), so, 0));
-                    xb[b][t] = __builtin_bit_cast(v2d8, __builtin_amdgcn_raw_buffer_load_b128(
+                    xb[b][t] = __builtin_bit_cast(vin, __builtin_amdgcn_raw_buffer_load_b128(
                                                             rb, (int)((uint32_t)cb * ldb8 + 16 * g4), so, 0));
                 }
             }
@@ -177,20 +183,23 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
             constexpr unsigned MASK = decltype(maskc)::value;
             const unsigned mk = MASK ? MASK : mask;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < E; ++h)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
                         if ((mk >> (4 * a + c)) & 1u)
-                            acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(xb[b][c][h], xa[b][a][h], acc[a][c], 0, 0, 0);
+                            acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xb[b][c][h], (double)xa[b][a][h],
+                                                                             acc[a][c], 0, 0, 0);
         };
         auto fold_step = [&](auto bufc, int64_t k) {
             constexpr int b = decltype(bufc)::value;
-            if (!fold) return;
-            const v2d8 v = *(gpv2)(pv + 8 * k + ov);
+            if constexpr (E == 2) {   // (only FP64 products fold)
+                if (!fold) return;
+                const v2d8 v = *(gpv2)(pv + 8 * k + ov);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) cs[t] += xa[b][t][0] * v[0] + xa[b][t][1] * v[1];
+                for (int t = 0; t < 4; ++t) cs[t] += xa[b][t][0] * v[0] + xa[b][t][1] * v[1];
+            }
         };
         using B0 = std::integral_constant<int, 0>;
         using B1 = std::integral_constant<int, 1>;
@@ -230,13 +239,13 @@ __device__ __forceinline__ void GemmTn<WIDE>::run(const GemmArgs& g, int bx, int
         // both sides
         for (int64_t k = main; k < len; k += KS) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const bool in = k + 2 * g4 + h < len;
+            for (int h = 0; h < E; ++h) {
+                const bool in = k + E * g4 + h < len;
                 const double v = (fold && in) ? *(gp64)(pv + 8 * (k + h) + ov) : 0.0;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    xa[0][t][h] = in ? *(gp64)(pa + 8 * (k + h) + oa(t)) : 0.0;
-                    xb[0][t][h] = in ? *(gp64)(pb + 8 * (k + h) + ob(t)) : 0.0;
+                    xa[0][t][h] = in ? *(gpi)(pa + SZ * (k + h) + oa(t)) : (TI)0;
+                    xb[0][t][h] = in ? *(gpi)(pb + SZ * (k + h) + ob(t)) : (TI)0;
                     cs[t] += xa[0][t][h] * v;
                 }
             }
@@ -351,8 +360,34 @@ void gemm_tn_partials(Exec& ex, const GemmArgs& g0)
     if (g.kchunk <= 0) g.kchunk = ceil_div(ceil_div(g.K, g.splits), 16) * 16;
     g.xcd_remap = !ex.recording() && g.splits > 1;
     const int64_t tiles = tn_tiles(g.M, g.N, g.lower);
-    if (g.lda >= ((int64_t)1 << 23) || g.ldb >= ((int64_t)1 << 23)) launch<GemmTn<true>>(ex, tiles, g.splits, g);
-    else launch<GemmTn<false>>(ex, tiles, g.splits, g);
+    if (g.lda >= ((int64_t)1 << 23) || g.ldb >= ((int64_t)1 << 23)) launch<GemmTn<double, true>>(ex, tiles, g.splits, g);
+    else launch<GemmTn<double, false>>(ex, tiles, g.splits, g);
+}
+
+// Lower triangle of G = W^T W in FP64 for an FP32 W (rows x n, ld ldw < 2^23;
+// the products are exact in FP64).  P: partials, room for pslots n x n FP64
+// matrices; one K chunk is written straight into G.
+void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots)
+{
+    GemmArgs g{};
+    g.M = n; g.N = n; g.K = rows;
+    g.A = W; g.lda = ldw; g.transA = 1;
+    g.B = W; g.ldb = ldw; g.transB = 0;
+    g.alpha = 1.0;
+    g.C = G; g.ldc = n;
+    g.lower = 1;
+    // two work-groups per CU, chunks of 256 rows at least
+    const int64_t tiles = tn_tiles(n, n, 1);
+    int64_t sp = 512 / tiles;
+    if (sp > rows / 256) sp = rows / 256;
+    if (sp > pslots) sp = pslots;
+    if (sp < 1) sp = 1;
+    g.kchunk = ceil_div(ceil_div(rows, sp), 16) * 16;
+    g.splits = ceil_div(rows, g.kchunk);
+    g.P = g.splits > 1 ? (void*)P : (void*)G;
+    g.xcd_remap = !ex.recording() && g.splits > 1;
+    launch<GemmTn<float, false>>(ex, tiles, g.splits, g);
+    if (g.splits > 1) gemm_f64_reduce(ex, g);
 }
 
 }  // namespace pne

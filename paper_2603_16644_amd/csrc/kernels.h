@@ -141,6 +141,11 @@ size_t qr_workspace_bytes(int64_t s, int64_t n, int prec);
 int qr_r(Exec& ex, int64_t s, int64_t n, void* W, int64_t ldw, int prec, double* R, int64_t ldr,
          int32_t* info, void* work, size_t work_bytes);
 bool qr_supported(int64_t s, int prec);
+// The same factor up to the signs of its rows, for FP32, BF16 and FP16, from
+// the FP64 Gram matrix of the sketch and its Cholesky factor (qr.hip).
+int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
+                  double* P, int64_t pslots, double* tab, double* gd, uint32_t* amax, int32_t* info);
+void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots);
 
 // ---------------------------------------------------------------- vectors
 // inverses of the 64 x 64 diagonal blocks of op(M) (dinv_elems(n) values);
@@ -214,11 +219,19 @@ size_t condest_workspace_bytes(int64_t m, int64_t n, int64_t kchunk_fixed = 0);
 int condest_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, double known_kappa, float* dk0,
                 int32_t* dchoice, void* work, size_t work_bytes);
 // estimate from the FP32 QR of the FP32 sketch (s rows, seed, pid); W (s x n
-// FP32, ld s) and R (n x n FP64) receive the sketch and its R factor
+// FP32, ld s) and R (n x n FP64) are its sketch and its R factor.  With sf the
+// solvers' preconditioner of the same sketch is formed too (sketch_factor,
+// into sf->R, before the QR overwrites W; R may be sf->C).
+struct SketchFactorBuffers {
+    double *R, *C, *tab, *gd;
+    uint32_t* amax;
+    int32_t* info;
+    int64_t pslots;
+};
 size_t condest_qr_workspace_bytes(int64_t m, int64_t n, int64_t s, int64_t kchunk_fixed = 0);
 int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int64_t s, uint64_t seed,
                    uint32_t pid, float* dk0, int32_t* dchoice, float* W, double* R, void* work,
-                   size_t work_bytes);
+                   size_t work_bytes, const SketchFactorBuffers* sf = nullptr);
 
 // ---------------------------------------------------------------- single solves (api.hip)
 // workspace bytes of one PNE (hpne = 0) / HPNE (hpne = 1) solve, after the

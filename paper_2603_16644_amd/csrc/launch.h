@@ -186,7 +186,7 @@ struct Recorder {
 // of the pipeline in every member of a batch.
 enum Stage : uint32_t {
     ST_INIT = 1, ST_CONDEST_GRAM, ST_CONDEST_FACTOR, ST_CONDEST_INV, ST_CONDEST_EST,
-    ST_SKETCH, ST_SKETCH_REDUCE, ST_QR_ROUND, ST_QR, ST_QR_EXTRACT, ST_TRSM, ST_GRAM, ST_GRAM_REDUCE,
+    ST_SKETCH, ST_SKETCH_REDUCE, ST_SKFACTOR, ST_SKFACTOR_CHOL, ST_SKFACTOR_END, ST_QR_ROUND, ST_QR, ST_QR_EXTRACT, ST_TRSM, ST_GRAM, ST_GRAM_REDUCE,
     ST_FACTOR, ST_FACTOR_INV, ST_SOLVE, ST_REFINE, ST_FINISH
 };
 
