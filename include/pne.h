@@ -193,12 +193,11 @@ pne_status nne_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const 
 /* qr_ls_solve: least squares by FP64 Householder QR on the GPU -- the
  * direct QR solver the paper measures PNE/HPNE against (Section 7.4), with
  * Q never formed: the QR of the augmented matrix [A b] = Q [R_A c; 0 rho]
- * gives x = R_A^{-1} c.  The tall QR is a tree of blocked Householder QRs
- * (TSQR): row blocks of at most 6144 rows are factored together, then groups
- * of their stacked R factors, until one R remains.  n <= 3070.  dA: m x n
- * (lda >= m); db: m; dx: n (output); dinfo: one device int32 (1000+k for a
- * zero or non-finite R_A(k,k); x is then NaN).  Uploads one launch table per
- * tree level (one wait each).  Workspace: qr_ls_workspace_size. */
+ * gives x = R_A^{-1} c.  Communication-avoiding QR: 16 columns at a time,
+ * row blocks of at most 1024 rows factored side by side, then their stacked
+ * R factors, until one R remains.  n <= 3071.  dA: m x n (lda >= m); db: m;
+ * dx: n (output); dinfo: one device int32 (1000+k for a zero or non-finite
+ * R_A(k,k); x is then NaN).  Workspace: qr_ls_workspace_size. */
 size_t qr_ls_workspace_size(int64_t m, int64_t n);
 pne_status qr_ls_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const double* db, double* dx,
                        void* dwork, size_t work_bytes, int32_t* dinfo, pne_stream_t stream);

@@ -141,6 +141,11 @@ size_t qr_workspace_bytes(int64_t s, int64_t n, int prec);
 int qr_r(Exec& ex, int64_t s, int64_t n, void* W, int64_t ldw, int prec, double* R, int64_t ldr,
          int32_t* info, void* work, size_t work_bytes);
 bool qr_supported(int64_t s, int prec);
+// FP64, any height (qr_r: up to the heights of qr_supported).
+int qr_f64(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info, void* work,
+           size_t work_bytes);
+size_t caqr_workspace_bytes(int64_t s);
+void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* work);
 // The same factor up to the signs of its rows, for FP32, BF16 and FP16, from
 // the FP64 Gram matrix of the sketch and its Cholesky factor (qr.hip).
 int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,

@@ -2,6 +2,8 @@
 // "Thin QR factorization A_s = Q_s R_s"; Section 6.2), then the promotion of
 // R_s to FP64 (Algorithm 1, "Promote R_s").
 //
+// FP32, BF16 and FP16 here, FP64 in caqr.hip.
+//
 // Blocked compact-WY form (Golub & Van Loan, Section 5.2.3):
 //   panel:  one work-group (512 or 1024 threads) holds the h x NB panel in
 //           registers (thread t owns rows t, t+NT, ...) and applies NB reflectors
@@ -11,10 +13,9 @@
 //           the triangular factor T (H_1..H_NB = I - V T V^T);
 //   update: Y = V^T W_trail, Z = T^T Y, W_trail -= V Z in one kernel (a
 //           wavefront per trailing column).
-// Working precision: FP64 for qr_prec = FP64, FP32 otherwise.  For BF16 and
-// FP16 the input is rounded to the format before the factorization and R_s
+// Working precision FP32.  For BF16 and FP16 the input is rounded to the format before the factorization and R_s
 // after it (FP32 arithmetic in between); FP16 input is first scaled by a
-// power of two that keeps R_s inside the FP16 range (QrScale).
+// power of two that keeps R_s inside the FP16 range (qr_scale).
 #include "common.h"
 #include "convert.h"
 #include "kernels.h"
@@ -66,7 +67,7 @@ struct PanelShared {
 // barriers per column) where it compiles free of register spills, the
 // owner-computed one (three barriers, T built column by column) elsewhere.
 template <typename T, int KS>
-constexpr bool panel_redundant() { return KS >= 0 && sizeof(T) == 4; }
+constexpr bool panel_redundant() { return KS >= 0; }
 
 // One column step of the panel (see QrPanel).  KS >= 0 makes the column
 // index a compile-time constant (KS == k); KS < 0 takes k at run time.  The
@@ -718,44 +719,28 @@ __device__ void RDiagCheck::run(const Args& a, int, int)
     }
 }
 
-// Widest panel of a factorization: 16, except FP64 sketches taller than 2048
-// rows, which use 8 throughout (register budget of the panel kernel).
-template <typename T>
-static int qr_nb(int64_t s)
-{
-    if (s > 6144) return 0;
-    return (sizeof(T) == 8 && s > 2048) ? 8 : 16;
-}
+// Tallest matrix of a factorization.
+constexpr int64_t QR_SMAX = 6144;
+// Widest FP32 panel, and the width at height h: panels taller than 2304 rows
+// use 8 columns (the 16-column panel kernel would spill registers there).
+constexpr int QR_NB = 16;
+static int panel_nb(int64_t h) { return h > 2304 ? 8 : QR_NB; }
 
-// Width of the panel at height h: FP32 panels taller than 2304 rows use 8
-// columns (the 16-column panel kernel would spill registers there).
-template <typename T>
-static int panel_nb(int64_t s, int64_t h)
-{
-    const int nb = qr_nb<T>(s);
-    return (sizeof(T) == 4 && h > 2304) ? 8 : nb;
-}
+bool qr_supported(int64_t s, int) { return s <= QR_SMAX; }
 
-bool qr_supported(int64_t s, int prec)
+static size_t qr_f32_bytes(int64_t s, int64_t n)
 {
-    return prec == PNE_PREC_FP64 ? qr_nb<double>(s) > 0 : qr_nb<float>(s) > 0;
-}
-
-template <typename T>
-static size_t qr_bytes(int64_t s, int64_t n)
-{
-    const int nb = qr_nb<T>(s) ? qr_nb<T>(s) : 8;
     Arena ar(nullptr, 0);
-    ar.take<T>((size_t)s * nb);          // V
-    ar.take<T>((size_t)nb * nb);         // T
-    ar.take<T>((size_t)ceil_div(s, QS_ROWS) * n * nb);   // chunk partials of V^T W
-    ar.take<float>(4);                                    // FP16 input scale
+    ar.take<float>((size_t)s * QR_NB);                              // V
+    ar.take<float>((size_t)QR_NB * QR_NB);                          // T
+    ar.take<float>((size_t)ceil_div(s, QS_ROWS) * n * QR_NB);       // chunk partials of V^T W
+    ar.take<float>(4);                                              // FP16 input scale
     return ar.used;
 }
 
 size_t qr_workspace_bytes(int64_t s, int64_t n, int prec)
 {
-    return prec == PNE_PREC_FP64 ? qr_bytes<double>(s, n) : qr_bytes<float>(s, n);
+    return prec == PNE_PREC_FP64 ? caqr_workspace_bytes(s) : qr_f32_bytes(s, n);
 }
 
 template <typename T, int NB, int RPT, int NT, bool U>
@@ -766,54 +751,41 @@ static void panel_launch(Exec& ex, int64_t h, int w, T* Wp, int64_t ldw, T* V, i
 
 // Panel shapes (rows per thread, threads, unrolled column loop): the
 // smallest instantiation covering the panel height; unrolled only where the
-// compiled kernel is free of register spills (FP32: 16-column panels up to
-// 2304 rows, 8-column panels above).
+// compiled kernel is free of register spills (16-column panels up to 2304
+// rows, 8-column panels up to 4096).
 template <typename T, int NB>
 static void panel_dispatch(Exec& ex, int64_t h, int w, T* Wp, int64_t ldw, T* V, int64_t ldv, T* Tm)
 {
-    if constexpr (sizeof(T) == 4 && NB == 8) {
+    if constexpr (NB == 8) {
         if (h <= 3072) panel_launch<T, NB, 4, 768, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
         else if (h <= 4096) panel_launch<T, NB, 8, 512, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
         else panel_launch<T, NB, 12, 512, false>(ex, h, w, Wp, ldw, V, ldv, Tm);
-    } else if constexpr (sizeof(T) == 4) {
+    } else {
         if (h <= 1024) panel_launch<T, NB, 1, 1024, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
         else if (h <= 2048) panel_launch<T, NB, 2, 1024, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
         else panel_launch<T, NB, 3, 768, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
-    } else if constexpr (NB == 16) {
-        if (h <= 1024) panel_launch<T, NB, 1, 1024, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
-        else panel_launch<T, NB, 4, 512, false>(ex, h, w, Wp, ldw, V, ldv, Tm);
-    } else {
-        if (h <= 2048) panel_launch<T, NB, 4, 512, true>(ex, h, w, Wp, ldw, V, ldv, Tm);
-        else if (h <= 3072) panel_launch<T, NB, 6, 512, false>(ex, h, w, Wp, ldw, V, ldv, Tm);
-        else if (h <= 4096) panel_launch<T, NB, 8, 512, false>(ex, h, w, Wp, ldw, V, ldv, Tm);
-        else panel_launch<T, NB, 12, 512, false>(ex, h, w, Wp, ldw, V, ldv, Tm);
     }
 }
 
-template <typename T>
-static int qr_run(Exec& ex, int64_t s, int64_t n, T* W, int64_t ldw, int prec, double* R, int64_t ldr,
-                  int32_t* info, void* work, size_t work_bytes)
+static int qr_f32(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr,
+                  int32_t* info, void* work)
 {
-    if (work_bytes < qr_bytes<T>(s, n)) return PNE_EWORKSPACE;
-    const int NBv = qr_nb<T>(s);
-    if (!NBv) return PNE_ENOTSUP;   // V holds up to NBv columns
-    Arena ar(work, work_bytes);
-    T* V = ar.take<T>((size_t)s * NBv);
-    T* Tm = ar.take<T>((size_t)NBv * NBv);
-    T* Pq = ar.take<T>((size_t)ceil_div(s, QS_ROWS) * n * NBv);
+    typedef float T;
+    Arena ar(work, qr_f32_bytes(s, n));
+    T* V = ar.take<T>((size_t)s * QR_NB);
+    T* Tm = ar.take<T>((size_t)QR_NB * QR_NB);
+    T* Pq = ar.take<T>((size_t)ceil_div(s, QS_ROWS) * n * QR_NB);
     uint32_t* amax = ar.take<uint32_t>(4);
     ex.stage(ST_QR_ROUND);
-    if constexpr (sizeof(T) == 4) {
-        if (prec == PNE_PREC_FP16) qr_max(ex, s, n, (const float*)W, ldw, amax);
-        if (prec == PNE_PREC_BF16 || prec == PNE_PREC_FP16)
-            launch<RoundMatrix<T>>(ex, ceil_div(s * n, 256), 1, RoundMatrixArgs{s, n, W, ldw, prec, amax});
-    }
+    if (prec == PNE_PREC_FP16) qr_max(ex, s, n, W, ldw, amax);
+    if (prec == PNE_PREC_BF16 || prec == PNE_PREC_FP16)
+        launch<RoundMatrix<T>>(ex, ceil_div(s * n, 256), 1, RoundMatrixArgs{s, n, W, ldw, prec, amax});
     ex.stage(ST_QR);
     int64_t c0 = 0;
     while (c0 < n) {
         ex.iter((uint32_t)c0);
         const int64_t h = s - c0;
-        const int nb = panel_nb<T>(s, h);
+        const int nb = panel_nb(h);
         const int w = (int)((n - c0 < nb) ? n - c0 : nb);
         T* Wp = W + c0 + c0 * ldw;
         if (nb == 16) panel_dispatch<T, 16>(ex, h, w, Wp, ldw, V, s, Tm);
@@ -919,11 +891,26 @@ void check_r_diag(Exec& ex, int64_t n, const double* R, int64_t ldr, int32_t* in
     launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
 }
 
+// FP64 (any height): the Householder QR of caqr.hip.
+int qr_f64(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info, void* work,
+           size_t work_bytes)
+{
+    if (work_bytes < caqr_workspace_bytes(s)) return PNE_EWORKSPACE;
+    ex.stage(ST_QR);
+    caqr_factor(ex, s, n, W, ldw, (double*)work);
+    ex.stage(ST_QR_EXTRACT);
+    launch<ExtractR<double>>(ex, ceil_div(n * n, 256), 1, ExtractRArgs{n, W, ldw, PNE_PREC_FP64, R, ldr, nullptr, s});
+    launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
+    return launch_status(ex);
+}
+
 int qr_r(Exec& ex, int64_t s, int64_t n, void* W, int64_t ldw, int prec, double* R, int64_t ldr,
          int32_t* info, void* work, size_t work_bytes)
 {
-    if (prec == PNE_PREC_FP64) return qr_run<double>(ex, s, n, (double*)W, ldw, prec, R, ldr, info, work, work_bytes);
-    return qr_run<float>(ex, s, n, (float*)W, ldw, prec, R, ldr, info, work, work_bytes);
+    if (work_bytes < qr_workspace_bytes(s, n, prec)) return PNE_EWORKSPACE;
+    if (!qr_supported(s, prec)) return PNE_ENOTSUP;
+    if (prec == PNE_PREC_FP64) return qr_f64(ex, s, n, (double*)W, ldw, R, ldr, info, work, work_bytes);
+    return qr_f32(ex, s, n, (float*)W, ldw, prec, R, ldr, info, work);
 }
 
 }  // namespace pne

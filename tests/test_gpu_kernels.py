@@ -145,3 +145,45 @@ def test_sketch_factor_nearly_dependent_columns(pne, sk, qr, n):
     kappa = np.linalg.cond(A)
     e = (x.cpu().numpy() - xs) * d
     assert np.linalg.norm(e) <= 10 * kappa * U * np.linalg.norm(xs * d)
+
+
+@pytest.mark.parametrize("m,n,lda", [
+    (1, 1, 1), (5, 5, 7), (16, 15, 16), (16, 16, 16), (40, 16, 41), (129, 17, 129),   # few chunks, last panel narrow
+    (1024, 31, 1024), (1025, 33, 1025), (1041, 40, 1050), (2065, 64, 2065),           # one block, two, three
+    (3000, 600, 3000), (6145, 150, 6145),                                             # blocks shrink with the panel
+    (65537, 20, 65537), (1048593, 2, 1048593),                                        # three levels, last chunk of one row
+])
+def test_qr_blocks_and_levels(pne, m, n, lda):
+    """Householder QR of [A b] at the edges of its 16-row chunks, 1024-row
+    blocks and levels.  Backward error of a tree of Householder reflectors:
+    columnwise c sqrt(m n) u with c = 8 (rounding errors of random sign), so
+    |x - x*| <= c sqrt(m n) u kappa (1 + kappa |r| / (|A| |x*|)) |x*|."""
+    rng = np.random.default_rng(m + 3 * n)
+    A = rng.standard_normal((m, n)) + 2 * np.sqrt(m) * np.eye(m, n)
+    xs = rng.standard_normal(n)
+    Q, _ = np.linalg.qr(A)
+    r = rng.standard_normal(m)
+    r -= Q @ (Q.T @ r)
+    r -= Q @ (Q.T @ r)
+    r *= 1e-3
+    b = A @ xs + r
+    x, info = pne.qr_ls_solve(dev(A, lda), torch.from_numpy(b).cuda())
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    sv = np.linalg.svd(A, compute_uv=False)
+    kappa = sv[0] / sv[-1]
+    tol = 8 * np.sqrt(m * n) * U * kappa * (1 + kappa * np.linalg.norm(r) / (sv[0] * np.linalg.norm(xs)))
+    # b itself is rounded: sqrt(n) u |A| |x*| per row, of random sign
+    assert np.linalg.norm(x.cpu().numpy() - xs) <= 2 * tol * np.linalg.norm(xs)
+
+
+def test_qr_zero_and_nonfinite_columns(pne):
+    """A zero column and a NaN are reported (1000 + column) and x is NaN."""
+    rng = np.random.default_rng(8)
+    for bad, col in ((0.0, 18), (np.nan, 3)):
+        A = rng.standard_normal((1100, 40))
+        A[:, col] = bad
+        x, info = pne.qr_ls_solve(dev(A), torch.from_numpy(A[:, 0] * 1.0).cuda())
+        torch.cuda.synchronize()
+        assert 1000 < int(info.item()) <= 1000 + col + 1
+        assert bool(torch.isnan(x).all())
