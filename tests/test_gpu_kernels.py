@@ -187,3 +187,48 @@ def test_qr_zero_and_nonfinite_columns(pne):
         torch.cuda.synchronize()
         assert 1000 < int(info.item()) <= 1000 + col + 1
         assert bool(torch.isnan(x).all())
+
+
+@pytest.mark.parametrize("n", [1, 5, 16, 17, 31, 32, 33, 63, 65, 128, 129, 257, 300, 513, 1000, 1025, 1100, 2060])
+def test_lu_panels(pne, n):
+    """P C = L U at the edges of panels, chunks and panel heights, for
+    C = R^-T A^T A.  Backward error of Gaussian elimination
+    |P C - L U| <= n u |L| |U|, with three roundings to a multiplier instead of
+    one (3) and the rounding of the product (2); |l| <= 1 by pivoting."""
+    m = n + 10
+    rng = np.random.default_rng(31 + n)
+    A = rng.standard_normal((m, n))
+    R = np.triu(rng.standard_normal((n, n))) / np.sqrt(n) + np.diag(np.where(rng.random(n) < 0.5, -1.0, 1.0) * 2)
+    b = torch.zeros(m, dtype=torch.float64, device="cuda")
+    C0, _, _, _ = pne.pne_gram(dev(A), b, dev(R), hpne=True)
+    LU, _, piv, info = pne.pne_gram(dev(A), b, dev(R), hpne=True, factor=True)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    C, LU, piv = C0.cpu().numpy().copy(), LU.cpu().numpy(), piv.cpu().numpy()
+    for k, p in enumerate(piv):
+        assert k <= p < n
+        C[[k, p]] = C[[p, k]]
+    L, Um = np.tril(LU, -1) + np.eye(n), np.triu(LU)
+    assert np.abs(L).max() <= 1 + 4 * U
+    assert np.all(np.abs(L @ Um - C) <= (3 * n + 2) * U * (np.abs(L) @ np.abs(Um)))
+
+
+@pytest.mark.parametrize("n", [40, 200])
+def test_lu_pivot_ties_zeros_and_nonfinite(pne, n):
+    """Equal entries: the first row is the pivot.  A zero pivot and a NaN are
+    reported at the first column that has one."""
+    # C = 64 everywhere, 128 on the diagonal but for its first entry
+    m = 64 + n
+    A = np.zeros((m, n))
+    A[:64, :] = 1.0
+    A[64:, :] = 8.0 * np.eye(n)
+    A[64, 0] = 0.0
+    b = torch.zeros(m, dtype=torch.float64, device="cuda")
+    I = dev(np.eye(n))
+    _, _, piv, info = pne.pne_gram(dev(A), b, I, hpne=True, factor=True)
+    assert int(info.item()) == 0 and piv.cpu().numpy().tolist() == list(range(n))
+    Z = A.copy()
+    Z[:, 20] = 0.0
+    assert int(pne.pne_gram(dev(Z), b, I, hpne=True, factor=True)[3].item()) == 3021
+    Z[70, 33] = np.nan      # row and column 33 of C: the first column has one
+    assert int(pne.pne_gram(dev(Z), b, I, hpne=True, factor=True)[3].item()) == 3001
