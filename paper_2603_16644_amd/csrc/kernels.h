@@ -36,7 +36,7 @@ inline int64_t opk_bytes(int op)
 struct SketchPlan {
     int op;
     int64_t chunk, nchunks, ldk, splits, kchunk;
-    int wide;       // 256 x 256 product tiles (one large unscaled sketch)
+    int wm, wn;     // wide product tiles of 32 wm x 64 wn (one large unscaled sketch; 0: not)
     size_t bytes;
 };
 // kchunk_fixed > 0: split the product over rows of A in chunks of this

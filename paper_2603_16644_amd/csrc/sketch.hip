@@ -364,20 +364,20 @@ __device__ void GemmLp<OP, SCALED>::run(const GemmLpArgs& a, int bx, int by)
     }
 }
 
-// Wide variant for one large unscaled sketch (BF16 or FP32 operands):
-// 256 x 256 output tile per work-group of eight waves (2 x 4 waves of
-// 128 x 64), K tiles of 128 bytes per row, two LDS buffers (one barrier per
+// Wide variant for one large unscaled sketch (BF16 or FP32 operands): tiles of
+// up to 256 x 256 per work-group of eight waves (2 x 4 waves of 16 TI x 16 TJ
+// outputs), K tiles of 128 bytes per row, two LDS buffers (one barrier per
 // K tile) and the next tile held in registers.  Twice the MFMA work of the
-// 128 x 128 tile per byte brought in from L2.
-constexpr int LW_BM = 256, LW_BN = 256;
-template <int OP>
+// 128 x 128 tile per byte brought in from L2.  Tile sizes: wide_tile.
+template <int OP, int TI, int TJ>
 struct GemmLpW {
     typedef GemmLpArgs Args;
     static constexpr int NTH = 512, WPE = 2;
+    static constexpr int LW_BM = 32 * TI, LW_BN = 64 * TJ;
     static __device__ void run(const GemmLpArgs& a, int bx, int by);
 };
-template <int OP>
-__device__ void GemmLpW<OP>::run(const GemmLpArgs& a, int bx, int by)
+template <int OP, int TI, int TJ>
+__device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
 {
     typedef typename Op<OP>::T T;
     const T* __restrict__ Om = (const T*)a.Om;
@@ -390,7 +390,7 @@ __device__ void GemmLpW<OP>::run(const GemmLpArgs& a, int bx, int by)
     constexpr int PADE = 16 / E;
     constexpr int LDR = BK + PADE;
     constexpr int VPR = 8;                       // 16-byte vectors per tile row
-    constexpr int VPT = LW_BM * VPR / 512;       // vectors per thread per operand
+    constexpr int VA = (LW_BM * VPR + 511) / 512, VB = LW_BN * VPR / 512;   // vectors per thread
     __shared__ __attribute__((aligned(16))) T As[2][LW_BM * LDR];
     __shared__ __attribute__((aligned(16))) T Bs[2][LW_BN * LDR];
 
@@ -402,30 +402,40 @@ __device__ void GemmLpW<OP>::run(const GemmLpArgs& a, int bx, int by)
     const int64_t kbeg = (int64_t)by * kchunk;
     const int64_t kend = (kbeg + kchunk < ldk) ? kbeg + kchunk : ldk;
 
-    v4f acc[8][4];
+    v4f acc[TI][TJ];
 #pragma unroll
-    for (int x = 0; x < 8; ++x)
+    for (int x = 0; x < TI; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int y = 0; y < TJ; ++y) acc[x][y] = (v4f){0.f, 0.f, 0.f, 0.f};
 
-    uint4 ra[VPT], rb[VPT];
+    uint4 ra[VA], rb[VB];
     auto gload = [&](int64_t k) {
 #pragma unroll
-        for (int q = 0; q < VPT; ++q) {
+        for (int q = 0; q < VA; ++q) {
             const int v = tid + 512 * q;
             const int row = v / VPR, c = v % VPR;
-            const int64_t gi = i0 + row, gj = j0 + row;
-            const int64_t koff = k + (int64_t)c * (16 / E);
-            ra[q] = (gi < M) ? *(const uint4*)(Om + gi * ldk + koff) : make_uint4(0, 0, 0, 0);
-            rb[q] = (gj < N) ? *(const uint4*)(Aq + gj * ldk + koff) : make_uint4(0, 0, 0, 0);
+            const int64_t gi = i0 + row;
+            ra[q] = (row < LW_BM && gi < M) ? *(const uint4*)(Om + gi * ldk + k + c * (16 / E)) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < VB; ++q) {
+            const int v = tid + 512 * q;
+            const int row = v / VPR, c = v % VPR;
+            const int64_t gj = j0 + row;
+            rb[q] = (gj < N) ? *(const uint4*)(Aq + gj * ldk + k + c * (16 / E)) : make_uint4(0, 0, 0, 0);
         }
     };
     auto sstore = [&](int buf) {
 #pragma unroll
-        for (int q = 0; q < VPT; ++q) {
+        for (int q = 0; q < VA; ++q) {
             const int v = tid + 512 * q;
             const int row = v / VPR, c = v % VPR;
-            *(uint4*)(As[buf] + row * LDR + c * (16 / E)) = ra[q];
+            if (row < LW_BM) *(uint4*)(As[buf] + row * LDR + c * (16 / E)) = ra[q];
+        }
+#pragma unroll
+        for (int q = 0; q < VB; ++q) {
+            const int v = tid + 512 * q;
+            const int row = v / VPR, c = v % VPR;
             *(uint4*)(Bs[buf] + row * LDR + c * (16 / E)) = rb[q];
         }
     };
@@ -444,16 +454,16 @@ __device__ void GemmLpW<OP>::run(const GemmLpArgs& a, int bx, int by)
 #pragma unroll
         for (int kk = 0; kk < BK; kk += Op<OP>::KI) {
             const int ko = kk + g4 * Op<OP>::EPL;
-            const T* pa[4];
-            const T* pb[8];
+            const T* pa[TJ];
+            const T* pb[TI];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) pb[t] = as + (wm * 128 + t * 16 + r16) * LDR + ko;   // Omega rows i
+            for (int t = 0; t < TI; ++t) pb[t] = as + (wm * 16 * TI + t * 16 + r16) * LDR + ko;   // Omega rows i
 #pragma unroll
-            for (int t = 0; t < 4; ++t) pa[t] = bs + (wn * 64 + t * 16 + r16) * LDR + ko;    // A columns j
+            for (int t = 0; t < TJ; ++t) pa[t] = bs + (wn * 16 * TJ + t * 16 + r16) * LDR + ko;   // A columns j
 #pragma unroll
-            for (int ti = 0; ti < 8; ++ti)
+            for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = mfma16<OP>(pa[tj], pb[ti], acc[ti][tj]);
+                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16<OP>(pa[tj], pb[ti], acc[ti][tj]);
         }
         if (k + BK < kend) {
             sstore(buf ^ 1);
@@ -463,14 +473,14 @@ __device__ void GemmLpW<OP>::run(const GemmLpArgs& a, int bx, int by)
     }
     float* Pp = P + (int64_t)by * M * N;
 #pragma unroll
-    for (int ti = 0; ti < 8; ++ti) {
-        const int64_t i = i0 + wm * 128 + ti * 16 + r16;
+    for (int ti = 0; ti < TI; ++ti) {
+        const int64_t i = i0 + wm * 16 * TI + ti * 16 + r16;
         if (i >= M) continue;
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj)
+        for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t j = j0 + wn * 64 + tj * 16 + 4 * g4 + r;
+                const int64_t j = j0 + wn * 16 * TJ + tj * 16 + 4 * g4 + r;
                 if (j < N) {
                     float v = acc[ti][tj][r];
                     if (accumulate) v += Pp[i + j * M];
@@ -521,6 +531,47 @@ size_t sketch_workspace_bytes(int64_t m, int64_t n, int64_t s, int prec, int64_t
     return p.bytes;
 }
 
+// Tile (32 wm x 64 wn) and split count of the wide kernel.  One work-group
+// runs per CU, the largest split count whose work-groups fit the machine at
+// once: the time is that of (rounds of 256 work-groups) x (tile) / (splits).
+// 256 x 256 reads least from LDS and L2 per product, which BF16 is bound by;
+// FP32 is bound by the matrix cores, where a smaller tile that leaves fewer
+// CUs idle or pads less is faster: 6000 x 2000 is 192 tiles of 256 x 256 or
+// 256 of 192 x 256, 771 x 257 is 8 of 256 x 256 (62% padding) or 15 of 160 x
+// 128.  Measured: 6000 x 2000 x 1e6 257 -> 197 ms (122 TFLOP/s), 771 x 257 x
+// 30011 0.28 -> 0.18 ms.  A smaller tile never takes more splits, so the partial sums stay
+// within the space of 256 x 256.
+static void wide_tile(int64_t s, int64_t n, int op, int64_t maxsplit, int* wm, int* wn, int64_t* splits)
+{
+    static const int tiles[][2] = {{8, 4}, {6, 4}, {6, 2}, {5, 3}, {5, 2}};
+    double best = 0.0;
+    for (const auto& t : tiles) {
+        const int64_t nt = ceil_div(s, 32 * t[0]) * ceil_div(n, 64 * t[1]);
+        int64_t sp = 256 / nt;
+        sp = sp < 1 ? 1 : (sp < maxsplit ? sp : maxsplit);
+        const double cost = (double)ceil_div(nt * sp, 256) * t[0] * t[1] / sp;
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            *wm = t[0];
+            *wn = t[1];
+            *splits = sp;
+        }
+        if (op != OPK_F32) return;
+    }
+}
+template <int OP>
+static void wide_launch(Exec& ex, const SketchPlan& p, int64_t s, int64_t n, const GemmLpArgs& a)
+{
+    const int64_t gx = ceil_div(s, 32 * p.wm) * ceil_div(n, 64 * p.wn);
+    if constexpr (OP == OPK_F32) {
+        if (p.wm == 6 && p.wn == 4) return launch<GemmLpW<OP, 6, 4>>(ex, gx, p.splits, a);
+        if (p.wm == 6 && p.wn == 2) return launch<GemmLpW<OP, 6, 2>>(ex, gx, p.splits, a);
+        if (p.wm == 5 && p.wn == 3) return launch<GemmLpW<OP, 5, 3>>(ex, gx, p.splits, a);
+        if (p.wm == 5 && p.wn == 2) return launch<GemmLpW<OP, 5, 2>>(ex, gx, p.splits, a);
+    }
+    launch<GemmLpW<OP, 8, 4>>(ex, gx, p.splits, a);
+}
+
 SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed)
 {
     SketchPlan p{};
@@ -542,14 +593,9 @@ SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, in
         p.kchunk = kc;
         p.splits = ceil_div(p.ldk, kc);
     } else if (op == OPK_BF16 || op == OPK_F32) {
-        // one wide-tile work-group per CU: the largest split count whose
-        // work-groups fit one wave of the machine
-        p.wide = 1;
-        const int64_t tiles = ceil_div(s, LW_BM) * ceil_div(n, LW_BN);
-        int64_t want = 256 / tiles;
         int64_t maxsplit = p.ldk / (4 * align);
         if (maxsplit < 1) maxsplit = 1;
-        p.splits = want < 1 ? 1 : (want < maxsplit ? want : maxsplit);
+        wide_tile(s, n, op, maxsplit, &p.wm, &p.wn, &p.splits);
         p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
         p.splits = ceil_div(p.ldk, p.kchunk);
     } else {
@@ -640,8 +686,8 @@ static void launch_chunk(Exec& ex, const SketchPlan& p, const double* A, int64_t
         }
         const GemmLpArgs ga{Omq, Aq, p.ldk, s, n, sc, br, (float*)P, p.kchunk, accumulate};
         if constexpr (!SC) {
-            if (p.wide) {
-                launch<GemmLpW<OP>>(ex, ceil_div(s, LW_BM) * ceil_div(n, LW_BN), p.splits, ga);
+            if (p.wm) {
+                wide_launch<OP>(ex, p, s, n, ga);
                 if (!ex.recording()) prof_mark(PH_SK_GEMM, ex.st);
                 return;
             }

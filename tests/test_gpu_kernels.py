@@ -232,3 +232,18 @@ def test_lu_pivot_ties_zeros_and_nonfinite(pne, n):
     assert int(pne.pne_gram(dev(Z), b, I, hpne=True, factor=True)[3].item()) == 3021
     Z[70, 33] = np.nan      # row and column 33 of C: the first column has one
     assert int(pne.pne_gram(dev(Z), b, I, hpne=True, factor=True)[3].item()) == 3001
+
+
+@pytest.mark.parametrize("s,n", [
+    (305, 100), (1413, 471), (535, 107), (1140, 380), (405, 135), (1432, 716),   # 160 x 128, 192 x 128, 160 x 192
+    (990, 198), (702, 702), (641, 212), (1334, 667)])                            # 256 x 256, 192 x 256
+def test_sketch_tiles(pne, s, n):
+    """FP32 sketches through every tile of the wide product against the FP64
+    sketch of the same Omega: per entry the tolerance of the FP32 sketch, 1e-4
+    of the size of a sum of m products, sqrt(m / s) for unit entries."""
+    m = 20000
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(n, m, dtype=torch.float64, device="cuda", generator=g).t()
+    got, ref = pne.pne_sketch(A, s, seed=4, prec="fp32"), pne.pne_sketch(A, s, seed=4, prec="fp64")
+    torch.cuda.synchronize()
+    assert float((got - ref).abs().max()) <= 1e-4 * np.sqrt(m / s)
