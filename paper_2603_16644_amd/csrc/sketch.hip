@@ -159,46 +159,73 @@ __device__ void QuantizePlain<OP>::run(const QuantArgs& a, int bx, int by)
     }
 }
 
+// Scaled formats: one scale per block of br rows of a column (br a multiple of
+// 64).  A wavefront takes QS_BLKS blocks of a column with their rows in
+// registers (QS_RPL per lane at most; longer blocks are read twice), so A is
+// read once: bound by memory.  A work-group per block, reading it for the
+// largest entry and again to convert, is bound by the launch of its 1.6e6
+// work-groups at 400,000 x 500 (1.27 ms; 0.45 ms so).
+constexpr int QS_RPL = 4, QS_BLKS = 4;
 template <int OP>
 struct QuantizeScaled {
     typedef QuantArgs Args;
     static constexpr int NTH = 256, WPE = 0;
-    static __device__ void run(const QuantArgs& a, int bx, int by);
+    static constexpr int BLKS = 4 * QS_BLKS;     // blocks of a work-group
+    static __device__ __forceinline__ float scale_of(float amax)
+    {
+        if (amax == 0.0f) return 0.0f;
+        if constexpr (OP == OPK_F16) {
+            int E;
+            frexpf(amax, &E);                   // amax = f 2^E, f in [0.5, 1)
+            return ldexpf(1.0f, (E - 1) - 14);
+        } else {
+            return amax / 448.0f;
+        }
+    }
+    static __device__ void run(const QuantArgs& a, int bx, int by)
+    {
+        const int64_t kc = a.kc, ldk = a.ldk, br = a.br, n = a.n, j = by;
+        const double* __restrict__ Aj = a.A + a.k0 + j * a.lda;
+        typename Op<OP>::T* __restrict__ Qj = (typename Op<OP>::T*)a.Aq + j * ldk;
+        const int lane = threadIdx.x & 63;
+        const int64_t kb0 = (int64_t)bx * BLKS + (threadIdx.x >> 6) * QS_BLKS;
+        if (br > 64 * QS_RPL) {
+            for (int i = 0; i < QS_BLKS; ++i) {
+                const int64_t r0 = (kb0 + i) * br;
+                if (r0 >= ldk) return;
+                float amax = 0.0f;
+                for (int64_t r = r0 + lane; r < r0 + br && r < kc; r += 64) amax = fmaxf(amax, fabsf((float)Aj[r]));
+                const float scale = scale_of(wave_max(amax));
+                if (lane == 0) a.sc[(kb0 + i) * n + j] = scale;
+                for (int64_t r = r0 + lane; r < r0 + br && r < ldk; r += 64)
+                    Qj[r] = to_op<OP>((r < kc && scale != 0.0f) ? (float)Aj[r] / scale : 0.0f);
+            }
+            return;
+        }
+        float v[QS_BLKS][QS_RPL];
+#pragma unroll
+        for (int i = 0; i < QS_BLKS; ++i)
+#pragma unroll
+            for (int q = 0; q < QS_RPL; ++q) {
+                const int64_t r = (kb0 + i) * br + 64 * q + lane;
+                v[i][q] = (64 * q < br && r < kc) ? (float)Aj[r] : 0.0f;
+            }
+#pragma unroll
+        for (int i = 0; i < QS_BLKS; ++i) {
+            float amax = 0.0f;
+#pragma unroll
+            for (int q = 0; q < QS_RPL; ++q) amax = fmaxf(amax, fabsf(v[i][q]));
+            const int64_t r0 = (kb0 + i) * br;
+            const float scale = scale_of(wave_max(amax));
+            if (r0 < ldk && lane == 0) a.sc[(kb0 + i) * n + j] = scale;
+#pragma unroll
+            for (int q = 0; q < QS_RPL; ++q) {
+                const int64_t r = r0 + 64 * q + lane;
+                if (64 * q < br && r < ldk) Qj[r] = to_op<OP>((r < kc && scale != 0.0f) ? v[i][q] / scale : 0.0f);
+            }
+        }
+    }
 };
-template <int OP>
-__device__ void QuantizeScaled<OP>::run(const QuantArgs& a, int bx, int by)
-{
-    const double* __restrict__ A = a.A;
-    const int64_t lda = a.lda, k0 = a.k0, kc = a.kc, ldk = a.ldk, br = a.br, n = a.n;
-    typename Op<OP>::T* __restrict__ Aq = (typename Op<OP>::T*)a.Aq;
-    float* __restrict__ sc = a.sc;
-    __shared__ float red[4];
-    const int64_t kb = bx, j = by;
-    const int64_t r0 = kb * br;
-    float amax = 0.0f;
-    for (int64_t r = r0 + threadIdx.x; r < r0 + br && r < kc; r += 256)
-        amax = fmaxf(amax, fabsf((float)A[(k0 + r) + j * lda]));
-    amax = wave_max(amax);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
-    __syncthreads();
-    amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float scale;
-    if (amax == 0.0f) {
-        scale = 0.0f;
-    } else if constexpr (OP == OPK_F16) {
-        int E;
-        frexpf(amax, &E);                   // amax = f 2^E, f in [0.5, 1)
-        scale = ldexpf(1.0f, (E - 1) - 14);
-    } else {
-        scale = amax / 448.0f;
-    }
-    if (threadIdx.x == 0) sc[kb * n + j] = scale;
-    for (int64_t r = r0 + threadIdx.x; r < r0 + br && r < ldk; r += 256) {
-        float t = 0.0f;
-        if (r < kc && scale != 0.0f) t = (float)A[(k0 + r) + j * lda] / scale;
-        Aq[j * ldk + r] = to_op<OP>(t);
-    }
-}
 
 // ---------------------------------------------------------------- 3. MFMA product
 // P[i + j*M] (+)= sum_{k in split} Om[i*ldk + k] * Aq[j*ldk + k]  (per scale
@@ -364,20 +391,26 @@ __device__ void GemmLp<OP, SCALED>::run(const GemmLpArgs& a, int bx, int by)
     }
 }
 
-// Wide variant for one large unscaled sketch (BF16 or FP32 operands): tiles of
+// Wide variant for one large sketch: tiles of
 // up to 256 x 256 per work-group of eight waves (2 x 4 waves of 16 TI x 16 TJ
 // outputs), K tiles of 128 bytes per row, two LDS buffers (one barrier per
 // K tile) and the next tile held in registers.  Twice the MFMA work of the
 // 128 x 128 tile per byte brought in from L2.  Tile sizes: wide_tile.
-template <int OP, int TI, int TJ>
+//
+// SCALED: a K tile lies in one scale block (br a multiple of the tile), its
+// scales come to LDS with it, and the block's sum in tmp is scaled and added
+// to acc at the block's end.  128 x 256 outputs then, for the two sets of
+// accumulators; FP8 400,000 x 500 to 1500 rows 1.98 -> 0.66 ms against 128 x 128
+// with two barriers per 64 rows and scales from memory.
+template <int OP, int TI, int TJ, bool SCALED = false>
 struct GemmLpW {
     typedef GemmLpArgs Args;
     static constexpr int NTH = 512, WPE = 2;
     static constexpr int LW_BM = 32 * TI, LW_BN = 64 * TJ;
     static __device__ void run(const GemmLpArgs& a, int bx, int by);
 };
-template <int OP, int TI, int TJ>
-__device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
+template <int OP, int TI, int TJ, bool SCALED>
+__device__ void GemmLpW<OP, TI, TJ, SCALED>::run(const GemmLpArgs& a, int bx, int by)
 {
     typedef typename Op<OP>::T T;
     const T* __restrict__ Om = (const T*)a.Om;
@@ -393,6 +426,7 @@ __device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
     constexpr int VA = (LW_BM * VPR + 511) / 512, VB = LW_BN * VPR / 512;   // vectors per thread
     __shared__ __attribute__((aligned(16))) T As[2][LW_BM * LDR];
     __shared__ __attribute__((aligned(16))) T Bs[2][LW_BN * LDR];
+    __shared__ __attribute__((aligned(16))) float Ss[2][SCALED ? LW_BN : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wm = w & 1, wn = w >> 1;
@@ -402,14 +436,19 @@ __device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
     const int64_t kbeg = (int64_t)by * kchunk;
     const int64_t kend = (kbeg + kchunk < ldk) ? kbeg + kchunk : ldk;
 
-    v4f acc[TI][TJ];
+    v4f acc[TI][TJ], tmp[SCALED ? TI : 1][SCALED ? TJ : 1];
 #pragma unroll
     for (int x = 0; x < TI; ++x)
 #pragma unroll
-        for (int y = 0; y < TJ; ++y) acc[x][y] = (v4f){0.f, 0.f, 0.f, 0.f};
+        for (int y = 0; y < TJ; ++y) {
+            acc[x][y] = (v4f){0.f, 0.f, 0.f, 0.f};
+            if constexpr (SCALED) tmp[x][y] = (v4f){0.f, 0.f, 0.f, 0.f};
+        }
 
     uint4 ra[VA], rb[VB];
+    float rs = 0.0f;
     auto gload = [&](int64_t k) {
+        if constexpr (SCALED) rs = (tid < LW_BN && j0 + tid < N) ? a.sc[(int64_t)((uint32_t)k / (uint32_t)a.br) * N + j0 + tid] : 0.0f;
 #pragma unroll
         for (int q = 0; q < VA; ++q) {
             const int v = tid + 512 * q;
@@ -426,6 +465,9 @@ __device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
         }
     };
     auto sstore = [&](int buf) {
+        if constexpr (SCALED) {
+            if (tid < LW_BN) Ss[buf][tid] = rs;
+        }
 #pragma unroll
         for (int q = 0; q < VA; ++q) {
             const int v = tid + 512 * q;
@@ -463,7 +505,24 @@ __device__ void GemmLpW<OP, TI, TJ>::run(const GemmLpArgs& a, int bx, int by)
 #pragma unroll
             for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < TJ; ++tj) acc[ti][tj] = mfma16<OP>(pa[tj], pb[ti], acc[ti][tj]);
+                for (int tj = 0; tj < TJ; ++tj) {
+                    if constexpr (SCALED) tmp[ti][tj] = mfma16<OP>(pa[tj], pb[ti], tmp[ti][tj]);
+                    else acc[ti][tj] = mfma16<OP>(pa[tj], pb[ti], acc[ti][tj]);
+                }
+        }
+        if constexpr (SCALED) {
+            if ((uint32_t)(k + BK) % (uint32_t)a.br == 0 || k + BK >= kend) {
+#pragma unroll
+                for (int tj = 0; tj < TJ; ++tj) {
+                    const v4f sv = *(const v4f*)(Ss[buf] + wn * 16 * TJ + tj * 16 + 4 * g4);
+#pragma unroll
+                    for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[ti][tj][r] += tmp[ti][tj][r] * sv[r];
+                        tmp[ti][tj] = (v4f){0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+            }
         }
         if (k + BK < kend) {
             sstore(buf ^ 1);
@@ -559,6 +618,11 @@ static void wide_tile(int64_t s, int64_t n, int op, int64_t maxsplit, int* wm, i
         if (op != OPK_F32) return;
     }
 }
+// Scale blocks that hold whole K tiles (128 bytes per row) of the wide kernel.
+static bool wide_scaled(int op, int64_t br)
+{
+    return (op == OPK_FP8 || op == OPK_F16) && br % (128 / opk_bytes(op)) == 0;
+}
 template <int OP>
 static void wide_launch(Exec& ex, const SketchPlan& p, int64_t s, int64_t n, const GemmLpArgs& a)
 {
@@ -569,7 +633,8 @@ static void wide_launch(Exec& ex, const SketchPlan& p, int64_t s, int64_t n, con
         if (p.wm == 5 && p.wn == 3) return launch<GemmLpW<OP, 5, 3>>(ex, gx, p.splits, a);
         if (p.wm == 5 && p.wn == 2) return launch<GemmLpW<OP, 5, 2>>(ex, gx, p.splits, a);
     }
-    launch<GemmLpW<OP, 8, 4>>(ex, gx, p.splits, a);
+    if constexpr (OP == OPK_FP8 || OP == OPK_F16) launch<GemmLpW<OP, 4, 4, true>>(ex, gx, p.splits, a);
+    else launch<GemmLpW<OP, 8, 4>>(ex, gx, p.splits, a);
 }
 
 SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed)
@@ -596,6 +661,16 @@ SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, in
         int64_t maxsplit = p.ldk / (4 * align);
         if (maxsplit < 1) maxsplit = 1;
         wide_tile(s, n, op, maxsplit, &p.wm, &p.wn, &p.splits);
+        p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
+        p.splits = ceil_div(p.ldk, p.kchunk);
+    } else if (wide_scaled(op, br)) {
+        // the same with 128 x 256 tiles
+        int64_t maxsplit = p.ldk / (4 * align);
+        if (maxsplit < 1) maxsplit = 1;
+        p.wm = 4;
+        p.wn = 4;
+        const int64_t want = 256 / (ceil_div(s, 128) * ceil_div(n, 256));
+        p.splits = want < 1 ? 1 : (want < maxsplit ? want : maxsplit);
         p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
         p.splits = ceil_div(p.ldk, p.kchunk);
     } else {
@@ -681,16 +756,14 @@ static void launch_chunk(Exec& ex, const SketchPlan& p, const double* A, int64_t
     } else {
         if constexpr (SC) {
             const QuantArgs q{A, lda, k0, kc, p.ldk, br, n, Aq, sc};
-            launch<QuantizeScaled<OP>>(ex, ceil_div(p.ldk, br), n, q);
+            launch<QuantizeScaled<OP>>(ex, ceil_div(ceil_div(p.ldk, br), QuantizeScaled<OP>::BLKS), n, q);
             if (!ex.recording()) prof_mark(PH_SK_QUANT, ex.st);
         }
         const GemmLpArgs ga{Omq, Aq, p.ldk, s, n, sc, br, (float*)P, p.kchunk, accumulate};
-        if constexpr (!SC) {
-            if (p.wm) {
-                wide_launch<OP>(ex, p, s, n, ga);
-                if (!ex.recording()) prof_mark(PH_SK_GEMM, ex.st);
-                return;
-            }
+        if (p.wm) {
+            wide_launch<OP>(ex, p, s, n, ga);
+            if (!ex.recording()) prof_mark(PH_SK_GEMM, ex.st);
+            return;
         }
         launch<GemmLp<OP, SC>>(ex, ceil_div(s, LP_BM) * ceil_div(n, LP_BN), p.splits, ga);
     }

@@ -247,3 +247,29 @@ def test_sketch_tiles(pne, s, n):
     got, ref = pne.pne_sketch(A, s, seed=4, prec="fp32"), pne.pne_sketch(A, s, seed=4, prec="fp64")
     torch.cuda.synchronize()
     assert float((got - ref).abs().max()) <= 1e-4 * np.sqrt(m / s)
+
+
+@pytest.mark.parametrize("prec,u", [("fp8", 2.0 ** -4), ("fp16", 2.0 ** -11)])
+@pytest.mark.parametrize("m,n,s,br", [
+    (1, 1, 1, 128), (700, 3, 9, 64), (1000, 17, 130, 128), (2049, 257, 300, 128),    # blocks and tiles cut short
+    (1500, 40, 120, 192), (3001, 65, 129, 256), (3001, 20, 70, 320), (5000, 30, 90, 1024),
+])
+def test_sketch_scaled_blocks(pne, prec, u, m, n, s, br):
+    """Sketches with a scale per block of br rows (in registers up to 256 rows,
+    read twice above; blocks that are no multiple of the product's K tile go
+    to the narrow product) against the oracle.  Both operands are rounded
+    (where Omega differs in its last bit, to neighbours): per entry at most 2 u
+    of its sum of absolute products, on average the root of the sum of squares
+    of the products, sqrt(pi / 2) |a|_2 / |a|_1 of that sum for a Gaussian
+    Omega, times 2 u (sqrt(2 / 3) u expected)."""
+    import oracle as orc
+    rng = np.random.default_rng(m + n)
+    A = rng.standard_normal((m, n)) * np.exp(rng.uniform(-4, 4, (m, 1)))
+    A[:: 7, n // 2] = 0.0
+    got = pne.pne_sketch(dev(A), s, seed=21, prec=prec, block_rows=br).cpu().numpy()
+    ref, ab = orc.sketch(A, s, seed=21, prec=prec, block_rows=br, want_abs=True)
+    err = np.abs(got - ref)
+    assert np.all(err <= (2 * u + 1e-4) * ab + 1e-300)
+    a1, a2 = np.abs(A).sum(axis=0), np.sqrt((A * A).sum(axis=0))
+    mean = 2 * u * np.sqrt(np.pi / 2) * float((a2 / np.where(a1 > 0, a1, 1)).max())
+    assert float(np.sum(err)) <= mean * float(np.sum(ab))
