@@ -83,44 +83,48 @@ __device__ void InvDiag<T, UPPER>::run(const InvDiagArgs& a, int bx, int)
     for (int c = 0; c < TB; ++c) D[lane + c * TB] = Ys[lane * TBL + c];
 }
 
+// sum_k p[k * step] x[k], k = 0 .. w-1 in this order, for w <= TB.  A full
+// block's TB loads are in flight together (one after another they cost a
+// memory latency each).
+template <typename T>
+__device__ __forceinline__ T block_dot(const T* __restrict__ p, int64_t step, int w, const T* x)
+{
+    T s = 0;
+    if (w == TB) {
+        T v[TB];
+#pragma unroll
+        for (int k = 0; k < TB; ++k) v[k] = p[k * step];
+#pragma unroll
+        for (int k = 0; k < TB; ++k) s += v[k] * x[k];
+    } else {
+        for (int k = 0; k < w; ++k) s += p[k * step] * x[k];
+    }
+    return s;
+}
+
 // x (in LDS) := U^{-1} x using the inverted diagonal blocks Dinv of U
 // (stored as by InvDiag for U, or for U^T when dtrans is set, in which case
 // block (r, c) is read as Dinv[c + r*TB]).  U(i, j) = trans ? M[j + i ld] :
 // M[i + j ld]; `lower` says whether U is lower triangular.  `tmp` is LDS
 // scratch of TB elements.  Whole work-group.
 template <typename T>
-__device__ inline void wg_trsv_inv(int64_t n, const T* __restrict__ M, int64_t ld, bool lower, bool trans,
+__device__ __forceinline__ void wg_trsv_inv(int64_t n, const T* __restrict__ M, int64_t ld, bool lower, bool trans,
                                    const T* __restrict__ Dinv, bool dtrans, T* x, T* tmp)
 {
     const int tid = threadIdx.x;
-    auto U = [&](int64_t i, int64_t j) -> T { return trans ? M[j + i * ld] : M[i + j * ld]; };
+    const int64_t si = trans ? ld : 1, sj = trans ? 1 : ld;   // U(i, j) = M[i si + j sj]
     const int64_t nb = (n + TB - 1) / TB;
     for (int64_t bb = 0; bb < nb; ++bb) {
         const int64_t blk = lower ? bb : nb - 1 - bb;
         const int64_t b0 = blk * TB;
         const int bw = (int)((n - b0 < TB) ? n - b0 : TB);
         const T* D = Dinv + blk * TB * TB;
-        if (tid < bw) {
-            T s = 0;
-            for (int c = 0; c < bw; ++c) s += (dtrans ? D[c + tid * TB] : D[tid + c * TB]) * x[b0 + c];
-            tmp[tid] = s;
-        }
+        if (tid < bw) tmp[tid] = block_dot(D + (dtrans ? (int64_t)tid * TB : tid), dtrans ? 1 : TB, bw, x + b0);
         __syncthreads();
         if (tid < bw) x[b0 + tid] = tmp[tid];
         __syncthreads();
-        if (lower) {
-            for (int64_t i = b0 + bw + tid; i < n; i += blockDim.x) {
-                T s = 0;
-                for (int k = 0; k < bw; ++k) s += U(i, b0 + k) * x[b0 + k];
-                x[i] -= s;
-            }
-        } else {
-            for (int64_t i = tid; i < b0; i += blockDim.x) {
-                T s = 0;
-                for (int k = 0; k < bw; ++k) s += U(i, b0 + k) * x[b0 + k];
-                x[i] -= s;
-            }
-        }
+        const int64_t i0 = lower ? b0 + bw : 0, i1 = lower ? n : b0;
+        for (int64_t i = i0 + tid; i < i1; i += blockDim.x) x[i] -= block_dot(M + i * si + b0 * sj, sj, bw, x + b0);
         __syncthreads();
     }
 }
