@@ -422,7 +422,7 @@ def main():
                                       "phases_ms": {k: round(v, 4) for k, v in mean_phases(phs32).items()}},
             "srft_bf16_pne_refine1": {"solves_per_s": 1.0 / tsbf, "ms": tsbf * 1e3, "rel_err": esbf},
             "qr_solver": {"solves_per_s": 1.0 / tq, "ms": tq * 1e3, "rel_err": eq,
-                          "kind": "FP64 Householder QR of [A b] (TSQR tree), Q never formed"},
+                          "kind": "FP64 Householder QR of [A b] (communication-avoiding), Q never formed"},
             "speedup_vs_qr_solver": tq / t_mix,
             "speedup_vs_fp64": t64 / t_mix,
             "hpne_speedup_vs_fp64": th64 / th,

@@ -498,14 +498,13 @@ struct PotrfInvArgs {
     int64_t c0;       // global index of the block's first column
     void* Dinv;       // 64 x 64 inverse out
 };
-template <typename T>
 struct PotrfInv {
+    typedef float T;
     typedef PotrfInvArgs Args;
     static constexpr int NTH = 256, WPE = 0;
     static __device__ void run(const PotrfInvArgs& p, int, int);
 };
-template <typename T>
-__device__ void PotrfInv<T>::run(const PotrfInvArgs& p, int, int)
+__device__ void PotrfInv::run(const PotrfInvArgs& p, int, int)
 {
     __shared__ T L[CB * PD_LD];   // L[r + c * PD_LD]
     __shared__ T X[CB * PD_LD];   // inverse
@@ -660,7 +659,7 @@ void cholesky_f32(Exec& ex, int64_t n, float* C, int64_t ldc, int32_t* info, flo
         const int w = (int)((n - c0 < CB) ? n - c0 : CB);
         T* D = C + c0 + c0 * ldc;
         T* Db = Dinv + (c0 / CB) * CB * CB;
-        launch<PotrfInv<T>>(ex, 1, 1, PotrfInvArgs{w, D, ldc, info, c0, Db});
+        launch<PotrfInv>(ex, 1, 1, PotrfInvArgs{w, D, ldc, info, c0, Db});
         const int64_t rem = n - c0 - w;
         if (rem <= 0) break;
         // X := X L_JJ^{-T}: in place (each work-group reads all of its rows
