@@ -215,6 +215,43 @@ __device__ __forceinline__ T wave_transpose_total(T (&v)[NB])
     }
 }
 
+// Sum of p[z * stride], z = q, q + G, ... < n in this order, eight loads in
+// flight together.
+template <int G, typename T>
+__device__ __forceinline__ T slot_sum(const T* __restrict__ p, int64_t stride, int64_t n, int q)
+{
+    T s = 0;
+    int64_t z = q;
+    for (; z + 7 * G < n; z += 8 * G) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(z + u * G) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; z < n; z += G) s += p[z * stride];
+    return s;
+}
+// The G partial sums of a work-group of 256 threads, thread (e, q) = (tid %
+// (256 / G), tid / (256 / G)) holding partial q of entry e: the total, in the
+// threads with q = 0 (added in order of q).  Whole work-group.
+template <int G, typename T>
+__device__ __forceinline__ T slot_total(T s, T* lds)
+{
+    if constexpr (G > 1) {
+        constexpr int E = 256 / G;
+        __syncthreads();
+        lds[threadIdx.x] = s;
+        __syncthreads();
+        T t = 0;
+#pragma unroll
+        for (int q = 0; q < G; ++q) t += lds[threadIdx.x % E + q * E];
+        return t;
+    } else {
+        return s;
+    }
+}
+
 // Block-wide sum for blockDim.x a multiple of 64 (<= 1024).  `red` is a
 // __shared__ array of at least blockDim.x/64 elements.  All threads get the
 // result.  Contains two barriers.

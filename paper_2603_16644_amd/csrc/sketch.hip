@@ -560,25 +560,30 @@ struct SketchReduceArgs {
     double* o64;
     int64_t ld64;
 };
-template <typename TP>
+// (G threads per entry: as GemmReduce.)
+template <typename TP, int G>
 struct SketchReduce {
     typedef SketchReduceArgs Args;
     static constexpr int NTH = 256, WPE = 0;
     static __device__ void run(const SketchReduceArgs& a, int bx, int by);
 };
-template <typename TP>
-__device__ void SketchReduce<TP>::run(const SketchReduceArgs& a, int bx, int)
+template <typename TP, int G>
+__device__ void SketchReduce<TP, G>::run(const SketchReduceArgs& a, int bx, int)
 {
+    __shared__ TP lds[G > 1 ? 256 : 1];
+    constexpr int E = 256 / G;
     const TP* __restrict__ P = (const TP*)a.P;
     const int64_t splits = a.splits, M = a.M, N = a.N, ld32 = a.ld32, ld64 = a.ld64;
     const double scale = a.scale;
     float* __restrict__ o32 = a.o32;
     double* __restrict__ o64 = a.o64;
-    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
-    if (idx >= M * N) return;
-    const int64_t i = idx % M, j = idx / M;
+    const int64_t idx = (int64_t)bx * E + threadIdx.x % E;
+    const bool in = idx < M * N;
     TP s = 0;
-    for (int64_t p = 0; p < splits; ++p) s += P[p * M * N + idx];
+    if (in) s = slot_sum<G>(P + idx, M * N, splits, threadIdx.x / E);
+    s = slot_total<G>(s, lds);
+    if (!in || threadIdx.x >= E) return;
+    const int64_t i = idx % M, j = idx / M;
     if (o32) o32[i + j * ld32] = (float)(s * (TP)scale);
     if (o64) o64[i + j * ld64] = (double)s * scale;
 }
@@ -801,8 +806,13 @@ int sketch_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int
     ex.stage(ST_SKETCH_REDUCE);
     const double scale = 1.0 / sqrt((double)s);
     const SketchReduceArgs ra{P, p.splits, s, n, scale, As32, ld32, As64, ld64};
-    if (p.op == OPK_F64) launch<SketchReduce<double>>(ex, ceil_div(s * n, 256), 1, ra);
-    else launch<SketchReduce<float>>(ex, ceil_div(s * n, 256), 1, ra);
+    if (p.splits >= 32) {
+        if (p.op == OPK_F64) launch<SketchReduce<double, 16>>(ex, ceil_div(s * n, 16), 1, ra);
+        else launch<SketchReduce<float, 16>>(ex, ceil_div(s * n, 16), 1, ra);
+    } else {
+        if (p.op == OPK_F64) launch<SketchReduce<double, 1>>(ex, ceil_div(s * n, 256), 1, ra);
+        else launch<SketchReduce<float, 1>>(ex, ceil_div(s * n, 256), 1, ra);
+    }
     if (!ex.recording()) prof_mark(PH_SK_REDUCE, ex.st);
     return launch_status(ex);
 }

@@ -273,3 +273,22 @@ def test_sketch_scaled_blocks(pne, prec, u, m, n, s, br):
     a1, a2 = np.abs(A).sum(axis=0), np.sqrt((A * A).sum(axis=0))
     mean = 2 * u * np.sqrt(np.pi / 2) * float((a2 / np.where(a1 > 0, a1, 1)).max())
     assert float(np.sum(err)) <= mean * float(np.sum(ab))
+
+
+@pytest.mark.parametrize("n", [1, 5, 38, 130])
+@pytest.mark.parametrize("m", [128 * 31, 128 * 32, 128 * 33 + 7, 70001])
+@pytest.mark.parametrize("hpne", [False, True])
+def test_partial_sums(pne, hpne, m, n):
+    """Gram matrix and right-hand side from about 31, 32, 33 and several
+    hundred partial sums: a thread per entry below 32, sixteen above.  Errors
+    of sums of m rounded products in any order: (m + 2) u |A|^T |A|."""
+    rng = np.random.default_rng(m + n)
+    A, b = rng.standard_normal((m, n)), rng.standard_normal(m)
+    C, c, _, info = pne.pne_gram(dev(A), torch.from_numpy(b).cuda(), dev(np.eye(n)), hpne=hpne)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    C, c = C.cpu().numpy(), c.cpu().numpy()
+    tol = (m + 2) * U
+    err = np.abs(C - A.T @ A)
+    assert np.all((err if hpne else np.tril(err)) <= 2 * tol * (np.abs(A).T @ np.abs(A)))
+    assert np.all(np.abs(c - A.T @ b) <= 2 * tol * (np.abs(A).T @ np.abs(b)))
