@@ -214,14 +214,17 @@ __device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int 
     const int64_t ib = k + 1 + ti, jb = k + 1 + tj;
     const gw64 C = (gw64)a.C;
     // 16 rows x 64 columns of C at (block row rb, block column cb); past the
-    // matrix: the identity on the diagonal, else 0
+    // matrix: the identity on the diagonal, else 0.  Above the diagonal
+    // nothing has written C, and what lies there must not be read: chol16
+    // multiplies it by the zeros of an inverse, which a NaN or an infinity
+    // survives.
     auto load = [&](v4d (&x)[4], int64_t rb, int64_t cb) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int64_t i = rb * CB + 16 * w + r16, j = cb * CB + 16 * c + 4 * q + g4;
-                x[c][q] = (i < n && j < n) ? C[i + j * a.ldc] : (i == j ? 1.0 : 0.0);
+                x[c][q] = (i < n && j <= i) ? C[i + j * a.ldc] : (i == j ? 1.0 : 0.0);
             }
     };
     v4d acc[4];
