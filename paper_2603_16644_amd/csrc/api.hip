@@ -198,30 +198,26 @@ int64_t gram_slots(const Problem& p, size_t bytes)
     return have < most ? have : most;
 }
 
+// Whether the QR of the estimate below can work on a copy of the sketch, in
+// A_p's memory, which is free until the solve (s n floats there).
+bool keeps_sketch(const Problem& p) { return p.s <= 2 * ap_ld(p.m); }
+
 // The condition estimate of one problem into b.k0 / b.choice: the FP32 Gram
 // estimate of Section 6.1, or (cond_method 1, no known kappa) the estimate
-// from the FP32 QR of the FP32 sketch.  In a solver the latter also leaves
-// the preconditioner of that sketch in b.R, in case the pick is FP32 (the
-// QR's own R goes to b.C); otherwise the QR's R is in b.R.
+// from the FP32 QR of the FP32 sketch, with the QR's R in b.R.  In a solver
+// the sketch stays in b.W (keeps_sketch), in case the pick is FP32.
 int run_condest(Exec& ex, const Problem& p, const double* dA, const pne_opts* o, uint32_t pid, const Buffers& b,
                 size_t scratch_cap, bool solver)
 {
     if (!(p.cond_method == 1 && !(o->known_kappa > 0.0)))
         return condest_run(ex, p.m, p.n, dA, p.lda, o->known_kappa, b.k0, b.choice, b.scratch, scratch_cap);
-    if (!solver)
-        return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.R, b.scratch,
-                              scratch_cap);
-    // (b.y holds the two words of the factor's own bookkeeping; a zero
-    // diagonal shows in the estimate, which then does not pick FP32)
-    const SketchFactorBuffers sf{b.R, b.C, b.dinv1, b.c, (uint32_t*)b.y, (int32_t*)b.y + 1, p.m / p.n};
-    return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.C, b.scratch,
-                          scratch_cap, &sf);
+    return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.R, b.scratch,
+                          scratch_cap, solver && keeps_sketch(p) ? (float*)b.Ap : nullptr);
 }
 
-// With the QR estimate and both precisions AUTO, an FP32 pick means the
-// estimate already computed the preconditioner (FP32 sketch, FP32 QR, same
-// seed and rows): R_s is in b.R and is reused as it stands.
-bool precond_from_condest(const Problem& p, const pne_opts* o, int sk, int qr)
+// With the QR estimate and both precisions AUTO, an FP32 pick means that the
+// sketch is the estimate's (FP32, same seed and rows).
+bool sketch_from_condest(const Problem& p, const pne_opts* o, int sk, int qr)
 {
     return p.cond_method == 1 && p.sketch_kind == 0 && !(o->known_kappa > 0.0) && p.sketch_prec == PNE_PREC_AUTO &&
            p.qr_prec == PNE_PREC_AUTO && sk == PNE_PREC_FP32 && qr == PNE_PREC_FP32;
@@ -250,15 +246,18 @@ pne_status resolve_precision(Exec& ex, const Problem& p, const double* dA, const
 
 size_t scratch_cap_of(const Buffers& b) { return (size_t)((char*)b.W - (char*)b.scratch); }
 
-// sketch and its triangular factor -> b.R: the Householder QR for FP64 and
-// where R itself is asked for, else (solvers, where the signs of its rows
-// cancel) the factor from the sketch's Gram matrix.
+// sketch (unless it is in b.W already: sketched) and its triangular factor ->
+// b.R: the Householder QR for FP64 and where R itself is asked for, else
+// (solvers, where the signs of its rows cancel) the factor from the sketch's
+// Gram matrix.
 pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t seed, uint32_t pid, int sk,
-                       int qr, const Buffers& b, int32_t* dinfo, bool solver)
+                       int qr, const Buffers& b, int32_t* dinfo, bool solver, bool sketched)
 {
     const bool w64 = (qr == PNE_PREC_FP64);
     const size_t cap = scratch_cap_of(b);
-    int rc = p.sketch_kind == 1
+    int rc = PNE_OK;
+    if (!sketched)
+        rc = p.sketch_kind == 1
                  ? srft_run(ex, p.m, p.n, dA, p.lda, p.s, seed, pid, srft_prec(sk), w64 ? nullptr : (float*)b.W, p.s,
                             w64 ? (double*)b.W : nullptr, p.s, b.scratch, cap)
                  : sketch_run(ex, p.m, p.n, dA, p.lda, p.s, seed, pid, sk, p.br, w64 ? nullptr : (float*)b.W, p.s,
@@ -397,10 +396,9 @@ pne_status solve_impl(int hpne, int64_t m, int64_t n, const double* dA, int64_t 
     pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), true, &sk, &qr, &k0);
     if (rc) return rc;
     mark(ex, PH_CONDEST);
-    if (!precond_from_condest(p, o, sk, qr)) {
-        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, true);
-        if (rc) return rc;
-    }
+    rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, true,
+                     sketch_from_condest(p, o, sk, qr) && keeps_sketch(p));
+    if (rc) return rc;
     rc = run_solve(ex, p, dA, db, dx, b, dinfo);
     if (rc) return rc;
     if (hipGetLastError() != hipSuccess) return PNE_EHIP;
@@ -470,8 +468,7 @@ pne_status record_batch(Recorder& rec, int64_t batch, const pne_problem_desc* hd
                         const double* db_base, double* dx_base, const pne_opts* o, const BatchLayout& L,
                         const int32_t* sk, const int32_t* qr, int32_t* dinfo)
 {
-    // (members whose QR estimate already computed the FP32 preconditioner
-    // skip the sketch and QR)
+    // (members that take their sketch from the QR estimate do not draw it)
     for (int64_t i = 0; i < batch; ++i) {
         Exec ex;
         ex.rec = &rec;
@@ -481,12 +478,10 @@ pne_status record_batch(Recorder& rec, int64_t batch, const pne_problem_desc* hd
         const double* A = dA_base ? dA_base + hd[i].a_offset : nullptr;
         const double* b = db_base ? db_base + hd[i].b_offset : nullptr;
         double* x = dx_base ? dx_base + hd[i].x_offset : nullptr;
-        pne_status rc = PNE_OK;
-        if (!precond_from_condest(p, o, sk[i], qr[i])) {
-            rc = run_precond(ex, p, A, o->seed, (uint32_t)hd[i].problem_id, sk[i], qr[i], L.buf[i],
-                             dinfo ? dinfo + i : nullptr, true);
-            if (rc) return rc;
-        }
+        pne_status rc = run_precond(ex, p, A, o->seed, (uint32_t)hd[i].problem_id, sk[i], qr[i], L.buf[i],
+                                    dinfo ? dinfo + i : nullptr, true,
+                                    sketch_from_condest(p, o, sk[i], qr[i]) && keeps_sketch(p));
+        if (rc) return rc;
         rc = run_solve(ex, p, A, b, x, L.buf[i], dinfo ? dinfo + i : nullptr);
         if (rc) return rc;
     }
@@ -579,7 +574,7 @@ struct pne_batch_plan_s {
     std::vector<pne::LaunchGroup> ce_groups;    // condition estimate (AUTO)
     std::vector<pne::LaunchGroup> main_groups;  // the solves
     pne::TuneParams tune;
-    bool rerun_ce = false;   // some member takes its preconditioner from the estimate
+    bool rerun_ce = false;   // some member takes its sketch from the estimate
     hipGraphExec_t gexec = nullptr;
     ~pne_batch_plan_s()
     {
@@ -646,7 +641,7 @@ pne_status plan_create(int64_t batch, const pne_problem_desc* hd, const double* 
     for (LaunchGroup& g : plan->main_groups) g.off += toff;
     plan->tune = tp;
     for (int64_t i = 0; i < batch; ++i)
-        if (precond_from_condest(L.prob[i], o, sk[i], qr[i])) plan->rerun_ce = true;
+        if (sketch_from_condest(L.prob[i], o, sk[i], qr[i]) && keeps_sketch(L.prob[i])) plan->rerun_ce = true;
     *out = plan;
     return PNE_OK;
 }
@@ -805,8 +800,9 @@ pne_status sketch_precond(int64_t m, int64_t n, const double* dA, int64_t lda, c
     float k0;
     pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), false, &sk, &qr, &k0);
     if (rc) return rc;
-    if (!precond_from_condest(p, o, sk, qr)) {
-        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, false);
+    // (an FP32 pick from the QR estimate: its R is the answer)
+    if (!sketch_from_condest(p, o, sk, qr)) {
+        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, false, false);
         if (rc) return rc;
     }
     copy_f64(ex, n, n, b.R, n, dR, ldr);

@@ -257,8 +257,8 @@ int condest_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, do
 // FP32 QR resolves kappa up to about 1/u_32, so the single-precision band
 // of Algorithm 1 (kappa0 <= 8) is reachable, which the FP32 Gram estimate
 // (breakdown from kappa ~ 4e3) is not.  The sketch is exactly the one an FP32
-// solve with the same seed draws; with sf its preconditioner is formed from
-// it as that solve would (sketch_factor).
+// solve with the same seed draws; with Wqr the QR works on a copy there and
+// the sketch stays in W for that solve.
 
 // Rf = fl32(R) on and above the diagonal, 0 below; ||Rf||_1 into *out.
 struct RToF32 {
@@ -324,7 +324,7 @@ size_t condest_qr_workspace_bytes(int64_t m, int64_t n, int64_t s, int64_t kchun
 
 int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int64_t s, uint64_t seed,
                    uint32_t pid, float* dk0, int32_t* dchoice, float* W, double* R, void* work,
-                   size_t work_bytes, const SketchFactorBuffers* sf)
+                   size_t work_bytes, float* Wqr)
 {
     if (n > 4096) return PNE_ENOTSUP;
     if (!qr_supported(s, PNE_PREC_FP32)) return PNE_ENOTSUP;
@@ -340,13 +340,9 @@ int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda,
     zero_i32(ex, 1, info);
     int rc = sketch_run(ex, m, n, A, lda, s, seed, pid, PNE_PREC_FP32, 128, W, s, nullptr, 0, rest, rest_bytes);
     if (rc) return rc;
-    if (sf) {
-        const int64_t have = (int64_t)(rest_bytes / ((size_t)n * n * 8));
-        rc = sketch_factor(ex, s, n, W, s, PNE_PREC_FP32, sf->R, n, sf->C, (double*)rest,
-                           have < sf->pslots ? have : sf->pslots, sf->tab, sf->gd, sf->amax, sf->info);
-        if (rc) return rc;
-    }
-    rc = qr_r(ex, s, n, W, s, PNE_PREC_FP32, R, n, info, rest, rest_bytes);
+    // (W is followed by padding where s n is odd)
+    if (Wqr) copy_f64(ex, ceil_div(s * n, 2), 1, (const double*)W, ceil_div(s * n, 2), (double*)Wqr, ceil_div(s * n, 2));
+    rc = qr_r(ex, s, n, Wqr ? Wqr : W, s, PNE_PREC_FP32, R, n, info, rest, rest_bytes);
     if (rc) return rc;
     // (no new stage: the launches below keep counting within the QR's last
     // stage, so the launch keys of a batched recording stay increasing)

@@ -224,19 +224,13 @@ size_t condest_workspace_bytes(int64_t m, int64_t n, int64_t kchunk_fixed = 0);
 int condest_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, double known_kappa, float* dk0,
                 int32_t* dchoice, void* work, size_t work_bytes);
 // estimate from the FP32 QR of the FP32 sketch (s rows, seed, pid); W (s x n
-// FP32, ld s) and R (n x n FP64) are its sketch and its R factor.  With sf the
-// solvers' preconditioner of the same sketch is formed too (sketch_factor,
-// into sf->R, before the QR overwrites W; R may be sf->C).
-struct SketchFactorBuffers {
-    double *R, *C, *tab, *gd;
-    uint32_t* amax;
-    int32_t* info;
-    int64_t pslots;
-};
+// FP32, ld s) and R (n x n FP64) are its sketch and its R factor.  The QR
+// overwrites the sketch, or, with Wqr (s n floats, rounded up to even, 8-byte
+// aligned), a copy of it there.
 size_t condest_qr_workspace_bytes(int64_t m, int64_t n, int64_t s, int64_t kchunk_fixed = 0);
 int condest_qr_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int64_t s, uint64_t seed,
                    uint32_t pid, float* dk0, int32_t* dchoice, float* W, double* R, void* work,
-                   size_t work_bytes, const SketchFactorBuffers* sf = nullptr);
+                   size_t work_bytes, float* Wqr = nullptr);
 
 // ---------------------------------------------------------------- single solves (api.hip)
 // workspace bytes of one PNE (hpne = 0) / HPNE (hpne = 1) solve, after the
