@@ -198,25 +198,28 @@ int64_t gram_slots(const Problem& p, size_t bytes)
     return have < most ? have : most;
 }
 
-// Whether the QR of the estimate below can work on a copy of the sketch, in
-// A_p's memory, which is free until the solve (s n floats there).
-bool keeps_sketch(const Problem& p) { return p.s <= 2 * ap_ld(p.m); }
+// Whether the solvers' FP32, BF16 and FP16 factors of the sketch come from its
+// Gram matrix: where A_p's memory, free until the solve, holds what its second
+// pass works on (m of about s + 2.5 n and more); else from Householder QR.
+bool gram_factor(const Problem& p) { return sketch_factor_doubles(p.s, p.n) <= (size_t)(ap_ld(p.m) * p.n); }
 
 // The condition estimate of one problem into b.k0 / b.choice: the FP32 Gram
 // estimate of Section 6.1, or (cond_method 1, no known kappa) the estimate
 // from the FP32 QR of the FP32 sketch, with the QR's R in b.R.  In a solver
-// the sketch stays in b.W (keeps_sketch), in case the pick is FP32.
+// that factors the Gram matrix of a sketch the QR works on a copy in A_p's
+// memory and the sketch stays in b.W, in case the pick is FP32.
 int run_condest(Exec& ex, const Problem& p, const double* dA, const pne_opts* o, uint32_t pid, const Buffers& b,
                 size_t scratch_cap, bool solver)
 {
     if (!(p.cond_method == 1 && !(o->known_kappa > 0.0)))
         return condest_run(ex, p.m, p.n, dA, p.lda, o->known_kappa, b.k0, b.choice, b.scratch, scratch_cap);
     return condest_qr_run(ex, p.m, p.n, dA, p.lda, p.s, o->seed, pid, b.k0, b.choice, (float*)b.W, b.R, b.scratch,
-                          scratch_cap, solver && keeps_sketch(p) ? (float*)b.Ap : nullptr);
+                          scratch_cap, solver && gram_factor(p) ? (float*)b.Ap : nullptr);
 }
 
 // With the QR estimate and both precisions AUTO, an FP32 pick means that the
-// sketch is the estimate's (FP32, same seed and rows).
+// sketch is the estimate's (FP32, same seed and rows), and R too where it comes
+// from Householder QR.
 bool sketch_from_condest(const Problem& p, const pne_opts* o, int sk, int qr)
 {
     return p.cond_method == 1 && p.sketch_kind == 0 && !(o->known_kappa > 0.0) && p.sketch_prec == PNE_PREC_AUTO &&
@@ -246,15 +249,16 @@ pne_status resolve_precision(Exec& ex, const Problem& p, const double* dA, const
 
 size_t scratch_cap_of(const Buffers& b) { return (size_t)((char*)b.W - (char*)b.scratch); }
 
-// sketch (unless it is in b.W already: sketched) and its triangular factor ->
-// b.R: the Householder QR for FP64 and where R itself is asked for, else
-// (solvers, where the signs of its rows cancel) the factor from the sketch's
-// Gram matrix.
+// sketch (unless it is the estimate's: sketched) and its triangular factor ->
+// b.R: the Householder QR for FP64, where R itself is asked for and where the
+// problem is too small for gram_factor; else (solvers, where the signs of its
+// rows cancel) the factor from the sketch's Gram matrix.
 pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t seed, uint32_t pid, int sk,
                        int qr, const Buffers& b, int32_t* dinfo, bool solver, bool sketched)
 {
-    const bool w64 = (qr == PNE_PREC_FP64);
+    const bool w64 = (qr == PNE_PREC_FP64), gram = solver && !w64 && gram_factor(p);
     const size_t cap = scratch_cap_of(b);
+    if (sketched && !gram) return PNE_OK;   // (b.R is the estimate's R)
     int rc = PNE_OK;
     if (!sketched)
         rc = p.sketch_kind == 1
@@ -263,9 +267,9 @@ pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t se
                  : sketch_run(ex, p.m, p.n, dA, p.lda, p.s, seed, pid, sk, p.br, w64 ? nullptr : (float*)b.W, p.s,
                               w64 ? (double*)b.W : nullptr, p.s, b.scratch, cap);
     if (rc) return (pne_status)rc;
-    if (solver && !w64)
+    if (gram)
         rc = sketch_factor(ex, p.s, p.n, (float*)b.W, p.s, qr, b.R, p.n, b.C, (double*)b.scratch, gram_slots(p, cap),
-                           b.dinv1, b.c, (uint32_t*)b.y, dinfo);
+                           b.dinv1, b.c, (uint32_t*)b.y, b.Ap, dinfo);
     else
         rc = qr_r(ex, p.s, p.n, b.W, p.s, qr, b.R, p.n, dinfo, b.scratch, cap);
     mark(ex, PH_QR);
@@ -313,7 +317,7 @@ void run_factor(Exec& ex, const Problem& p, const Buffers& b, int32_t* dinfo)
     const int hpne = p.hpne;
     ex.stage(ST_FACTOR);
     if (hpne) lu_factor(ex, n, b.C, n, b.piv, dinfo);
-    else cholesky64(ex, n, b.C, n, (double*)b.scratch, n, b.Lt, n, b.dinv1, nullptr, 0.0, dinfo);
+    else cholesky64(ex, n, b.C, n, (double*)b.scratch, n, b.Lt, n, b.dinv1, dinfo);
     ex.stage(ST_FACTOR_INV);
     const double* L = hpne ? b.C : (const double*)b.scratch;
     const InvTriMat lo{L, n, 1, hpne ? 1 : 0, b.dinv1, hpne ? nullptr : b.dinv1t};
@@ -397,7 +401,7 @@ pne_status solve_impl(int hpne, int64_t m, int64_t n, const double* dA, int64_t 
     if (rc) return rc;
     mark(ex, PH_CONDEST);
     rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, true,
-                     sketch_from_condest(p, o, sk, qr) && keeps_sketch(p));
+                     sketch_from_condest(p, o, sk, qr));
     if (rc) return rc;
     rc = run_solve(ex, p, dA, db, dx, b, dinfo);
     if (rc) return rc;
@@ -480,7 +484,7 @@ pne_status record_batch(Recorder& rec, int64_t batch, const pne_problem_desc* hd
         double* x = dx_base ? dx_base + hd[i].x_offset : nullptr;
         pne_status rc = run_precond(ex, p, A, o->seed, (uint32_t)hd[i].problem_id, sk[i], qr[i], L.buf[i],
                                     dinfo ? dinfo + i : nullptr, true,
-                                    sketch_from_condest(p, o, sk[i], qr[i]) && keeps_sketch(p));
+                                    sketch_from_condest(p, o, sk[i], qr[i]));
         if (rc) return rc;
         rc = run_solve(ex, p, A, b, x, L.buf[i], dinfo ? dinfo + i : nullptr);
         if (rc) return rc;
@@ -641,7 +645,7 @@ pne_status plan_create(int64_t batch, const pne_problem_desc* hd, const double* 
     for (LaunchGroup& g : plan->main_groups) g.off += toff;
     plan->tune = tp;
     for (int64_t i = 0; i < batch; ++i)
-        if (sketch_from_condest(L.prob[i], o, sk[i], qr[i]) && keeps_sketch(L.prob[i])) plan->rerun_ce = true;
+        if (sketch_from_condest(L.prob[i], o, sk[i], qr[i])) plan->rerun_ce = true;
     *out = plan;
     return PNE_OK;
 }
@@ -800,11 +804,8 @@ pne_status sketch_precond(int64_t m, int64_t n, const double* dA, int64_t lda, c
     float k0;
     pne_status rc = resolve_precision(ex, p, dA, o, b, scratch_cap_of(b), false, &sk, &qr, &k0);
     if (rc) return rc;
-    // (an FP32 pick from the QR estimate: its R is the answer)
-    if (!sketch_from_condest(p, o, sk, qr)) {
-        rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, false, false);
-        if (rc) return rc;
-    }
+    rc = run_precond(ex, p, dA, o->seed, o->problem_id, sk, qr, b, dinfo, false, sketch_from_condest(p, o, sk, qr));
+    if (rc) return rc;
     copy_f64(ex, n, n, b.R, n, dR, ldr);
     if (hipGetLastError() != hipSuccess) return PNE_EHIP;
     if (hinfo) {

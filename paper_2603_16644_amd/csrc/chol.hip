@@ -33,9 +33,12 @@
 //
 // A non-positive or non-finite pivot at global column k sets *info to
 // 2000 + k + 1 (first failure only) and the factor continues as NaN.  With
-// tau > 0 (Gram matrix of a sketch) nothing is reported: a pivot below
-// tau C_kk is raised to it, a zero column gives a zero pivot, and the caller
-// looks at the diagonal.
+// tau > 0 (Gram matrix of a sketch) C + tau diag(C) is factored, and *info
+// stays: *state gets 1 where a pivot is small (below CHOL_LOW tau C_kk, so
+// that the shift counts), 2 or 3 where one is zero or not finite, else 0.  A
+// shift of every pivot and not a floor under the small ones: raising single
+// pivots that are rounding noise leaves the noise beside them to grow column
+// by column, until the factor overflows.
 #include "common.h"
 #include "kernels.h"
 #include "launch.h"
@@ -118,9 +121,10 @@ struct CholStepArgs {
     double* tab;       // table of block column b at tab + b * CB * CB
     double* gd;        // tau > 0: copy of the diagonal of C
     double tau;
-    int32_t* info;
+    int32_t* state;    // tau > 0 (null: not wanted)
+    int32_t* info;     // tau = 0
 };
-template <bool FLOOR>
+template <bool SHIFT>
 struct CholStep {
     typedef CholStepArgs Args;
     static constexpr int NTH = 256, WPE = 1;
@@ -130,9 +134,11 @@ struct CholStep {
 // Factor of a 16 x 16 diagonal block (one wavefront, accumulator layout), four
 // columns a step; gt: the groups of its table (also put at lt in LDS).  Every
 // lane factors the 4 x 4 pivot block, read by readlane; lane (r, g) then
-// forms column g of its inverse.  fl: (FLOOR) lowest pivot of column r16.
-// Returns the columns whose pivot was bad, a bit each.
-template <bool FLOOR>
+// forms column g of its inverse.  Returns the columns whose pivot was bad, a
+// bit each; or (SHIFT, with fl the shift of column r16) 1 for a small pivot, 2
+// for a zero or non-finite one.
+constexpr double CHOL_LOW = 256.0;
+template <bool SHIFT>
 __device__ __forceinline__ unsigned chol16(v4d& t, v2d* lt, gwv2 gt, double fl)
 {
     const int lane = threadIdx.x & 63, r16 = lane & 15, g4 = lane >> 4;
@@ -152,14 +158,18 @@ __device__ __forceinline__ unsigned chol16(v4d& t, v2d* lt, gwv2 gt, double fl)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             double d = l[j][j];
-            if (FLOOR) {
+            if (SHIFT) {
                 const double f = lane_value(fl, 4 * q + j);
-                d = d < f ? f : d;   // (a NaN stays)
+                d += f;
+                badm |= d < CHOL_LOW * f ? 1u : 0u;
+                d = d < 0.5 * f ? 0.5 * f : d;   // (a NaN stays)
             }
             // d <= 0, NaN and infinity all give NaN
             r[j] = rsqrt_full(d);
-            if (FLOOR) r[j] = d == 0.0 ? 0.0 : r[j];
-            else if (__builtin_amdgcn_ballot_w64(r[j] != r[j]) != 0) badm |= 1u << (4 * q + j);
+            if (SHIFT) {
+                badm |= d == 0.0 || r[j] != r[j] ? 2u : 0u;
+                r[j] = d == 0.0 ? 0.0 : r[j];
+            } else if (__builtin_amdgcn_ballot_w64(r[j] != r[j]) != 0) badm |= 1u << (4 * q + j);
             ld = g4 == j ? d * r[j] : ld;
 #pragma unroll
             for (int i = j + 1; i < 4; ++i) l[i][j] *= r[j];
@@ -195,11 +205,12 @@ __device__ __forceinline__ unsigned chol16(v4d& t, v2d* lt, gwv2 gt, double fl)
     return badm;
 }
 
-template <bool FLOOR>
-__device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int bx, int)
+template <bool SHIFT>
+__device__ __forceinline__ void CholStep<SHIFT>::run(const CholStepArgs& a, int bx, int)
 {
     __shared__ __attribute__((aligned(16))) v2d tab[TRI_TAB];
     __shared__ __attribute__((aligned(16))) v2d xj[4 * 4 * 2 * 64];   // [row block][c][p][lane]
+    __shared__ unsigned small[4];                                     // (SHIFT) of each wavefront's 16 columns
     const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t n = a.n, k = a.k;
@@ -272,7 +283,7 @@ __device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int 
                     }
                 }
         }
-    } else if (FLOOR) {
+    } else if (SHIFT) {
         for (int64_t i = tid; i < n; i += NTH) ((gw64)a.gd)[i] = C[i + i * a.ldc];
     }
     if (bx != 0) {
@@ -292,15 +303,17 @@ __device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int 
     const int64_t c0 = ib * CB;
     const gwv2 gt = (gwv2)((gw64)a.tab + ib * CB * CB);
     double fl = 0.0;
-    if (FLOOR) {
+    if (SHIFT) {
         const int64_t col = c0 + 16 * w + r16;
         fl = col < n ? a.tau * ((gp64)a.gd)[col] : 0.0;
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         if (w == c) {
-            const unsigned badm = chol16<FLOOR>(acc[c], tab + c * 256, gt + c * 256, fl);
-            if (badm != 0 && lane == 0 && *a.info == 0)
+            const unsigned badm = chol16<SHIFT>(acc[c], tab + c * 256, gt + c * 256, fl);
+            if (SHIFT) {
+                if (lane == 0) small[c] = badm;
+            } else if (badm != 0 && lane == 0 && *a.info == 0)
                 *a.info = 2000 + (int32_t)(c0 + 16 * c + __builtin_ctz(badm)) + 1;
         }
         __syncthreads();
@@ -339,6 +352,7 @@ __device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int 
                     }
         }
     }
+    if (SHIFT && tid == 0 && a.state) *a.state = (k < 0 ? 0 : *a.state) | (int32_t)(small[0] | small[1] | small[2] | small[3]);
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         if (c <= w)
@@ -352,19 +366,30 @@ __device__ __forceinline__ void CholStep<FLOOR>::run(const CholStepArgs& a, int 
             }
 }
 
-// L (optional) and L^T of C; C is destroyed.  tab: dinv_elems(n) values, tau
-// and gd (n values): see above.
+// L (optional) and L^T of C; C is destroyed.  tab: dinv_elems(n) values; info.
 void cholesky64(Exec& ex, int64_t n, double* C, int64_t ldc, double* L, int64_t ldl, double* Lt, int64_t ldt,
-                double* tab, double* gd, double tau, int32_t* info)
+                double* tab, int32_t* info)
 {
     const int64_t nb = ceil_div(n, CB);
     for (int64_t k = -1; k + 1 < nb; ++k) {
         ex.iter((uint32_t)(k + 1));
         const int64_t r = nb - k - 1;
-        const CholStepArgs a{n, k, C, ldc, L, ldl, Lt, ldt, tab, gd, tau, info};
-        const int64_t wgs = k < 0 ? 1 : r * (r + 1) / 2;
-        if (tau > 0.0) launch<CholStep<true>>(ex, wgs, 1, a);
-        else launch<CholStep<false>>(ex, wgs, 1, a);
+        const CholStepArgs a{n, k, C, ldc, L, ldl, Lt, ldt, tab, nullptr, 0.0, nullptr, info};
+        launch<CholStep<false>>(ex, k < 0 ? 1 : r * (r + 1) / 2, 1, a);
+    }
+}
+// L^T of C + tau diag(C); gd: n values (the diagonal of C, left there).  state:
+// see above; only: where *only is 1 (null: always).
+void cholesky64_shifted(Exec& ex, int64_t n, double* C, int64_t ldc, double* Lt, int64_t ldt, double* tab, double* gd,
+                        double tau, int32_t* state, const int32_t* only)
+{
+    const int64_t nb = ceil_div(n, CB);
+    for (int64_t k = -1; k + 1 < nb; ++k) {
+        ex.iter((uint32_t)(k + 1));
+        const int64_t r = nb - k - 1, wgs = k < 0 ? 1 : r * (r + 1) / 2;
+        const CholStepArgs a{n, k, C, ldc, nullptr, 0, Lt, ldt, tab, gd, tau, state, nullptr};
+        if (only) launch<When<CholStep<true>>>(ex, wgs, 1, When<CholStep<true>>::Args{a, only});
+        else launch<CholStep<true>>(ex, wgs, 1, a);
     }
 }
 

@@ -364,10 +364,13 @@ void gemm_tn_partials(Exec& ex, const GemmArgs& g0)
     else launch<GemmTn<double, false>>(ex, tiles, g.splits, g);
 }
 
-// Lower triangle of G = W^T W in FP64 for an FP32 W (rows x n, ld ldw < 2^23;
-// the products are exact in FP64).  P: partials, room for pslots n x n FP64
-// matrices; one K chunk is written straight into G.
-void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots)
+// Lower triangle of G = W^T W in FP64 for W (rows x n, ld ldw < 2^23) in FP32
+// (the products are exact in FP64) or FP64.  P: partials, room for pslots n x
+// n FP64 matrices; one K chunk is written straight into G.  FP64: where *only
+// is 1.
+template <typename T>
+static void gram_of(Exec& ex, int64_t rows, int64_t n, const T* W, int64_t ldw, double* G, double* P, int64_t pslots,
+                    const int32_t* only)
 {
     GemmArgs g{};
     g.M = n; g.N = n; g.K = rows;
@@ -386,8 +389,18 @@ void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, do
     g.splits = ceil_div(rows, g.kchunk);
     g.P = g.splits > 1 ? (void*)P : (void*)G;
     g.xcd_remap = !ex.recording() && g.splits > 1;
-    launch<GemmTn<float, false>>(ex, tiles, g.splits, g);
-    if (g.splits > 1) gemm_f64_reduce(ex, g);
+    if constexpr (sizeof(T) == 8) launch<When<GemmTn<T, false>>>(ex, tiles, g.splits, {g, only});
+    else launch<GemmTn<T, false>>(ex, tiles, g.splits, g);
+    if (g.splits > 1) gemm_f64_reduce(ex, g, only);
+}
+void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots)
+{
+    gram_of(ex, rows, n, W, ldw, G, P, pslots, nullptr);
+}
+void gram_f64_when(Exec& ex, int64_t rows, int64_t n, const double* W, int64_t ldw, double* G, double* P, int64_t pslots,
+                   const int32_t* only)
+{
+    gram_of(ex, rows, n, W, ldw, G, P, pslots, only);
 }
 
 }  // namespace pne

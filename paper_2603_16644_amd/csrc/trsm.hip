@@ -354,4 +354,51 @@ void trsm_right_upper(Exec& ex, int64_t m, int64_t n, const double* A, int64_t l
     else launch<TrsmRows<false>>(ex, ceil_div(m, 64), 1, t);
 }
 
+// First launch of trsm_sketch: the packed R and the matrix X = [W; sqrt(t)
+// diag(gd)^1/2] in FP64 that the substitution then works on in place.
+struct SketchRows {
+    struct Args {
+        TrsmPack::Args p;
+        int64_t s;           // rows of W (n columns)
+        const float* W;
+        int64_t ldw;
+        const double* gd;    // squared norms of the columns of W
+        double t;
+        double* X;
+        int64_t ldx;
+    };
+    static constexpr int NTH = 256, WPE = 0;
+    static constexpr int COLS = 8;   // blocks of R or columns of X per work-group
+    static __host__ __device__ int64_t pack_wgs(int64_t nblk) { return nblk * ((nblk + COLS - 1) / COLS); }
+    static __device__ void run(const Args& a, int bx, int)
+    {
+        const int64_t n = a.p.n, nblk = (n + TB16 - 1) / TB16, np = pack_wgs(nblk);
+        if (bx < np) {
+            const int kb = (int)(bx % nblk), c0 = (int)(bx / nblk) * COLS;
+            for (int c = c0; c < c0 + COLS; ++c) TrsmPack::run(a.p, c, kb);
+            return;
+        }
+        const int64_t rows = a.s + n, rt = (rows + NTH - 1) / NTH, e = bx - np;
+        const int64_t i = (e % rt) * NTH + threadIdx.x, j0 = (e / rt) * COLS;
+        if (i >= rows) return;
+        for (int64_t j = j0; j < j0 + COLS && j < n; ++j)
+            a.X[i + j * a.ldx] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(a.t * a.gd[j]) : 0.0);
+    }
+};
+
+int64_t trsm_sketch_ld(int64_t s, int64_t n) { return (s + n + 1) & ~(int64_t)1; }
+
+// X = [W; (t diag(gd))^1/2] R^{-1} where *only is 1: (s + n) x n, FP64, leading
+// dimension trsm_sketch_ld(s, n) (< 2^26).
+void trsm_sketch(Exec& ex, int64_t s, int64_t n, const float* W, int64_t ldw, const double* gd, double t, const double* R,
+                 int64_t ldr, double* X, double* pack, const int32_t* only)
+{
+    const int64_t ldx = trsm_sketch_ld(s, n), rows = s + n;
+    const int64_t wgs = SketchRows::pack_wgs(ceil_div(n, TB16)) + ceil_div(rows, 256) * ceil_div(n, SketchRows::COLS);
+    launch<When<SketchRows>>(ex, wgs, 1, {SketchRows::Args{TrsmPack::Args{n, R, ldr, pack}, s, W, ldw, gd, t, X, ldx}, only});
+    // (in place: a lane loads its entries of a panel's columns before it
+    // stores there, and no lane keeps what it loads of another's row)
+    launch<When<TrsmRows<false>>>(ex, ceil_div(rows, 64), 1, {TrsmArgs{rows, n, X, ldx, pack, X, ldx}, only});
+}
+
 }  // namespace pne

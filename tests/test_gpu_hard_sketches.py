@@ -1,0 +1,91 @@
+"""Solves whose sketch is rank deficient, or nearly so, in FP32: the factor of
+the sketch must stay a preconditioner."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import make_problem
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -53
+
+
+@pytest.fixture(scope="module")
+def pne():
+    import paper_2603_16644_amd as p
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    p.lib()
+    return p
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a.T)).cuda().t()
+
+
+def relerr(x, y):
+    return float(np.linalg.norm(x - y) / np.linalg.norm(y))
+
+
+def solve(pne, hpne, A, b, **opts):
+    fn = pne.hpne_solve if hpne else pne.pne_solve
+    x, info, _ = fn(dev(A), torch.from_numpy(b).cuda(), opts=pne.make_opts(**opts))
+    assert int(info.item()) == 0
+    x = x.cpu().numpy()
+    assert np.all(np.isfinite(x))
+    return x
+
+
+@pytest.mark.parametrize("hpne", [False, True])
+@pytest.mark.parametrize("m,n", [(3000, 100), (4000, 600), (900, 200)])
+@pytest.mark.parametrize("sk", ["fp64", "fp32"])
+@pytest.mark.parametrize("kappa", [1e6, 1e7, 1e8, 1e10])
+def test_large_condition_numbers(pne, orc, hpne, m, n, sk, kappa):
+    """An FP32 factor of an FP64 or FP32 sketch, from condition numbers that
+    FP32 resolves to ones whose smallest singular values it loses: the accuracy
+    of the QR solve after one refinement step."""
+    p = make_problem(m, n, kappa, 1e-10, seed=300 + n)
+    A, b, xs = p.numpy_A(), p.numpy_b(), p.numpy_x_star()
+    x = solve(pne, hpne, A, b, seed=7, sketch_prec=sk, qr_prec="fp32", refine_steps=1)
+    assert relerr(x, xs) <= 10 * relerr(orc.qr_ls(A, b), xs)
+
+
+@pytest.mark.parametrize("hpne", [False, True])
+@pytest.mark.parametrize("kappa", [1e12, 1e14])
+def test_beyond_fp32(pne, hpne, kappa):
+    """No breakdown, whatever x is worth there (a BF16 sketch, wrong in its third
+    digit, leaves A_p too ill-conditioned for PNE, whatever the factor)."""
+    p = make_problem(3000, 100, kappa, 1e-10, seed=310)
+    for sk in ("fp64", "fp32"):
+        solve(pne, hpne, p.numpy_A(), p.numpy_b(), seed=7, sketch_prec=sk, qr_prec="fp32", refine_steps=1)
+
+
+@pytest.mark.parametrize("hpne", [False, True])
+@pytest.mark.parametrize("m,n", [(100, 100), (300, 257), (1000, 999), (700, 100)])
+@pytest.mark.parametrize("sk,qr", [("fp32", "fp32"), ("bf16", "fp32"), ("fp32", "fp16")])
+def test_sampled_rows(pne, hpne, m, n, sk, qr):
+    """3 n rows drawn from m with replacement: of a square matrix one in twenty
+    is missed, and the sketch loses as many directions.  Consistent right-hand
+    side: |x - x*| <= 10 kappa u |x*| after three refinement steps."""
+    kappa = 1e3
+    p = make_problem(m, n, kappa, 1e-6, seed=320 + n)
+    A, xs = p.numpy_A(), p.numpy_x_star()
+    for seed in range(4):
+        x = solve(pne, hpne, A, A @ xs, seed=seed, sketch_prec=sk, qr_prec=qr, refine_steps=3, sketch_kind="srft")
+        assert relerr(x, xs) <= 10 * kappa * U
+
+
+@pytest.mark.parametrize("n", [20, 64, 130, 300, 1000])
+def test_many_repeated_columns(pne, n):
+    """Half of the columns repeat the others to 1e-9 (below FP32 roundoff) and
+    all differ in size by 1e6: |x - x*| <= 10 kappa u |x*| in the scaling of
+    the columns, kappa that of the columns scaled to norm 1."""
+    m = 6 * n + 300
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((m, n))
+    A[:, n // 2:] = A[:, :n - n // 2] + 1e-9 * rng.standard_normal((m, n - n // 2))
+    A /= np.linalg.norm(A, axis=0)
+    d = 10.0 ** rng.uniform(-3, 3, n)
+    xs = rng.standard_normal(n) / d
+    x = solve(pne, False, A * d, (A * d) @ xs, seed=3, sketch_prec="fp32", qr_prec="fp32", refine_steps=3)
+    assert np.linalg.norm((x - xs) * d) <= 10 * np.linalg.cond(A) * U * np.linalg.norm(xs * d)
