@@ -269,7 +269,7 @@ pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t se
     if (rc) return (pne_status)rc;
     if (gram)
         rc = sketch_factor(ex, p.s, p.n, (float*)b.W, p.s, qr, b.R, p.n, b.C, (double*)b.scratch, gram_slots(p, cap),
-                           b.dinv1, b.c, (uint32_t*)b.y, b.Ap, dinfo);
+                           b.dinv1, b.c, (uint32_t*)b.y, (int32_t*)b.d, b.Ap, dinfo);
     else
         rc = qr_r(ex, p.s, p.n, b.W, p.s, qr, b.R, p.n, dinfo, b.scratch, cap);
     mark(ex, PH_QR);

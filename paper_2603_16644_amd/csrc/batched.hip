@@ -34,7 +34,7 @@ int stage_phase(uint32_t st)
     case ST_CONDEST_GRAM: case ST_CONDEST_FACTOR: case ST_CONDEST_INV: case ST_CONDEST_EST: return PH_CONDEST;
     case ST_SKETCH: return PH_SK_GEMM;
     case ST_SKETCH_REDUCE: return PH_SK_REDUCE;
-    case ST_SKFACTOR: case ST_SKFACTOR_CHOL: case ST_SKFACTOR_AGAIN: case ST_SKFACTOR_AGAIN_CHOL: case ST_SKFACTOR_END:
+    case ST_SKFACTOR: case ST_SKFACTOR_CHOL: case ST_SKFACTOR_END:
     case ST_QR_ROUND: case ST_QR: case ST_QR_EXTRACT: return PH_QR;
     case ST_TRSM: return PH_TRSM;
     case ST_GRAM: return PH_GRAM_GEMM;

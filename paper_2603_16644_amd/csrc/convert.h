@@ -45,4 +45,16 @@ __device__ __forceinline__ uint8_t f32_to_e4m3_bits(float x)
     return (uint8_t)(sign | code);
 }
 
+// Power of two by which the input of an FP16 QR of `rows` rows is scaled (see
+// QrMax in qr.hip).
+__device__ __forceinline__ float qr_scale(const uint32_t* amax, int64_t rows)
+{
+    const float m = __uint_as_float(*amax);
+    if (!(m <= 3.4e38f) || !(m > 0.0f)) return 1.0f;
+    int t = 0, E;
+    while (t < 31 && ((int64_t)1 << (2 * t)) < rows) ++t;
+    frexpf(m, &E);
+    return ldexpf(1.0f, (14 - t) - E);
+}
+
 }  // namespace pne

@@ -691,7 +691,7 @@ void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int
 }
 
 template <typename TC>
-static void gemm_reduce_launch(Exec& ex, const GemmArgs& g, const int32_t* only = nullptr)
+static void gemm_reduce_launch(Exec& ex, const GemmArgs& g)
 {
     const TileShape ts = tile_shape(g.M, g.N, g.K, g.lower);
     int64_t cnt = g.M * g.N;
@@ -699,10 +699,6 @@ static void gemm_reduce_launch(Exec& ex, const GemmArgs& g, const int32_t* only 
     // (FP32, the condition estimate's Gram matrix: the order of one thread)
     const int64_t most = g.splits_diag > g.splits ? g.splits_diag : g.splits;
     if constexpr (sizeof(TC) == 8) {
-        if (only) {
-            launch<When<GemmReduce<TC, 1>>>(ex, ceil_div(cnt, 256), 1, {GemmReduceArgs{g, ts.bm, ts.bn}, only});
-            return;
-        }
         if (most >= 32) return launch<GemmReduce<TC, 16>>(ex, ceil_div(cnt, 16), 1, GemmReduceArgs{g, ts.bm, ts.bn});
     }
     launch<GemmReduce<TC, 1>>(ex, ceil_div(cnt, 256), 1, GemmReduceArgs{g, ts.bm, ts.bn});
@@ -750,7 +746,7 @@ static void gemm_launch(Exec& ex, const GemmArgs& g0, bool reduce)
 }
 
 void gemm_f64(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, double>(ex, g, true); }
-void gemm_f64_reduce(Exec& ex, const GemmArgs& g, const int32_t* only) { gemm_reduce_launch<double>(ex, g, only); }
+void gemm_f64_reduce(Exec& ex, const GemmArgs& g) { gemm_reduce_launch<double>(ex, g); }
 void gemm_f64_partials(Exec& ex, const GemmArgs& g)
 {
     if (g.transA && !g.transB && tn_route(g.M, g.N, g.K, g.lower)) gemm_tn_partials(ex, g);

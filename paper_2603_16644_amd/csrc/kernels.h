@@ -83,7 +83,7 @@ struct GemmArgs {
 // element types: d = double, f = float; "ddf" = A, B stored double, computed in float
 void gemm_f64(Exec& ex, const GemmArgs& g);           // full path incl. reduce
 void gemm_f64_partials(Exec& ex, const GemmArgs& g);  // partials only (no reduce)
-void gemm_f64_reduce(Exec& ex, const GemmArgs& g, const int32_t* only = nullptr);   // reduce of the partials
+void gemm_f64_reduce(Exec& ex, const GemmArgs& g);    // reduce of the partials
 // A^T B in 64 x 64 tiles with the operands loaded straight into registers
 // (gemm_tn.hip): whether gemm_f64_partials takes that route, and its tiles
 bool tn_route(int64_t M, int64_t N, int64_t K, int lower);
@@ -117,16 +117,11 @@ void trsm_right_upper(Exec& ex, int64_t m, int64_t n, const double* A, int64_t l
 // scratch of dinv_elems(n) values.
 void cholesky64(Exec& ex, int64_t n, double* C, int64_t ldc, double* L, int64_t ldl, double* Lt, int64_t ldt,
                 double* tab, int32_t* info);
-// L^T of C + tau diag(C); gd (n values) is left with the diagonal of C.  *state
-// (if wanted): 1 where a pivot is small, 2 or 3 where one is zero or not
-// finite, else 0.  only: where *only is 1 (null: always).
+// L^T of C + tau diag(C); gd (n values) is left with the diagonal of C.  *state:
+// 1 where a pivot is small, 2 or 3 where one is zero or not finite, else 0.
+// zero2: two words set to zero.
 void cholesky64_shifted(Exec& ex, int64_t n, double* C, int64_t ldc, double* Lt, int64_t ldt, double* tab, double* gd,
-                        double tau, int32_t* state, const int32_t* only);
-// X = [W; (t diag(gd))^1/2] R^{-1} where *only is 1 (X in FP64, (s + n) x n with
-// leading dimension trsm_sketch_ld(s, n), 16-byte aligned; pack as above).
-int64_t trsm_sketch_ld(int64_t s, int64_t n);
-void trsm_sketch(Exec& ex, int64_t s, int64_t n, const float* W, int64_t ldw, const double* gd, double t, const double* R,
-                 int64_t ldr, double* X, double* pack, const int32_t* only);
+                        double tau, int32_t* state, int32_t* zero2);
 // Inverses of the 64 x 64 diagonal blocks of a triangular matrix into D and
 // their transposes into Dt (dinv_elems(n) values each; either may be null);
 // of a second matrix of the same order in the same launch when b is given.
@@ -155,14 +150,15 @@ int qr_f64(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* R, in
            size_t work_bytes);
 size_t caqr_workspace_bytes(int64_t s);
 void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* work);
-// The same factor up to the signs of its rows, for FP32, BF16 and FP16, from
-// the FP64 Gram matrix of the sketch and its Cholesky factor (qr.hip).
+// W rounded to BF16 or (scaled; amax one word) FP16; FP32: as it is.
+void qr_round(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, uint32_t* amax);
+// The factor of qr_r up to the signs of its rows, for FP32, BF16 and FP16, from
+// the FP64 Gram matrix of the sketch and its Cholesky factor (sketch_factor.hip).
 size_t sketch_factor_doubles(int64_t s, int64_t n);   // of X
 int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
-                  double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, double* X, int32_t* info);
+                  double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, int32_t* work, double* X,
+                  int32_t* info);
 void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots);
-void gram_f64_when(Exec& ex, int64_t rows, int64_t n, const double* W, int64_t ldw, double* G, double* P, int64_t pslots,
-                   const int32_t* only);
 
 // ---------------------------------------------------------------- vectors
 // inverses of the 64 x 64 diagonal blocks of op(M) (dinv_elems(n) values);

@@ -186,8 +186,7 @@ struct Recorder {
 // of the pipeline in every member of a batch.
 enum Stage : uint32_t {
     ST_INIT = 1, ST_CONDEST_GRAM, ST_CONDEST_FACTOR, ST_CONDEST_INV, ST_CONDEST_EST,
-    ST_SKETCH, ST_SKETCH_REDUCE, ST_SKFACTOR, ST_SKFACTOR_CHOL,
-    ST_SKFACTOR_AGAIN, ST_SKFACTOR_AGAIN_CHOL, ST_SKFACTOR_END, ST_QR_ROUND, ST_QR, ST_QR_EXTRACT, ST_TRSM, ST_GRAM, ST_GRAM_REDUCE,
+    ST_SKETCH, ST_SKETCH_REDUCE, ST_SKFACTOR, ST_SKFACTOR_CHOL, ST_SKFACTOR_END, ST_QR_ROUND, ST_QR, ST_QR_EXTRACT, ST_TRSM, ST_GRAM, ST_GRAM_REDUCE,
     ST_FACTOR, ST_FACTOR_INV, ST_SOLVE, ST_REFINE, ST_FINISH
 };
 
@@ -215,21 +214,6 @@ struct Exec {
     }
     uint64_t next_key() { return ((uint64_t)stage_ << 56) | ((uint64_t)(iter_ & 0xffffff) << 32) | (sub++ & 0xffffffffu); }
     bool recording() const { return rec != nullptr; }
-};
-
-// A kernel that runs only where the word *state is 1 when it starts, and ends
-// at once elsewhere.
-template <class K>
-struct When {
-    struct Args {
-        typename K::Args a;
-        const int32_t* state;
-    };
-    static constexpr int NTH = K::NTH, WPE = K::WPE;
-    static __device__ __forceinline__ void run(const Args& p, int bx, int by)
-    {
-        if (*p.state == 1) K::run(p.a, bx, by);
-    }
 };
 
 // Status of the launches issued so far: a recording touches no device.

@@ -575,7 +575,7 @@ struct QrApply {
 // and so has every entry of its triangular factor: the FP16 range (largest
 // finite 65504) holds R_s whatever the scale of A.  The factor is exact (a
 // power of two) and is divided out of R_s again in FP64.  amax = 0 or
-// non-finite gives c = 1.  QrMax leaves the bit pattern of amax (the order of
+// non-finite gives c = 1 (qr_scale).  QrMax leaves the bit pattern of amax (the order of
 // non-negative floats is that of their bits; NaN is above infinity) in a word
 // that starts at 0; the kernels that scale form c from it.
 struct QrMaxArgs {
@@ -602,15 +602,6 @@ struct QrMax {
         if ((threadIdx.x & 63) == 0 && mx != 0) atomicMax(a.amax, mx);
     }
 };
-__device__ __forceinline__ float qr_scale(const uint32_t* amax, int64_t rows)
-{
-    const float m = __uint_as_float(*amax);
-    if (!(m <= 3.4e38f) || !(m > 0.0f)) return 1.0f;
-    int t = 0, E;
-    while (t < 31 && ((int64_t)1 << (2 * t)) < rows) ++t;
-    frexpf(m, &E);
-    return ldexpf(1.0f, (14 - t) - E);
-}
 static void qr_max(Exec& ex, int64_t s, int64_t n, const float* W, int64_t ldw, uint32_t* amax)
 {
     zero_i32(ex, 1, (int32_t*)amax);
@@ -643,6 +634,14 @@ __device__ void RoundMatrix<T>::run(const RoundMatrixArgs& a, int bx, int)
     if (prec == PNE_PREC_BF16) v = __uint_as_float((uint32_t)f32_to_bf16_bits(v) << 16);
     else if (prec == PNE_PREC_FP16) v = (float)__builtin_bit_cast(_Float16, f32_to_f16_bits(v * qr_scale(a.amax, rows)));
     M[i + j * ld] = (T)v;
+}
+
+// W rounded to BF16 or (scaled, amax one word) FP16; FP32: as it is.
+void qr_round(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, uint32_t* amax)
+{
+    if (prec == PNE_PREC_FP16) qr_max(ex, s, n, W, ldw, amax);
+    if (prec == PNE_PREC_BF16 || prec == PNE_PREC_FP16)
+        launch<RoundMatrix<float>>(ex, ceil_div(s * n, 256), 1, RoundMatrixArgs{s, n, W, ldw, prec, amax});
 }
 
 // R = upper triangle of W(0:n, 0:n) promoted to FP64 (rounded to BF16/FP16
@@ -777,9 +776,7 @@ static int qr_f32(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     T* Pq = ar.take<T>((size_t)ceil_div(s, QS_ROWS) * n * QR_NB);
     uint32_t* amax = ar.take<uint32_t>(4);
     ex.stage(ST_QR_ROUND);
-    if (prec == PNE_PREC_FP16) qr_max(ex, s, n, W, ldw, amax);
-    if (prec == PNE_PREC_BF16 || prec == PNE_PREC_FP16)
-        launch<RoundMatrix<T>>(ex, ceil_div(s * n, 256), 1, RoundMatrixArgs{s, n, W, ldw, prec, amax});
+    qr_round(ex, s, n, W, ldw, prec, amax);
     ex.stage(ST_QR);
     int64_t c0 = 0;
     while (c0 < n) {
@@ -814,129 +811,6 @@ static int qr_f32(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     }
     ex.stage(ST_QR_EXTRACT);
     launch<ExtractR<T>>(ex, ceil_div(n * n, 256), 1, ExtractRArgs{n, W, ldw, prec, R, ldr, amax, s});
-    launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
-    return launch_status(ex);
-}
-
-// R = R1, or R2 R1 where *state is 1 (upper triangles), rounded to the
-// precision of the factor (FP32, BF16, or FP16 with the input scale divided
-// out), zero below.  32 x 32 entries per work-group, four per thread.
-struct SketchR {
-    struct Args {
-        int64_t n;
-        const double* R1;    // ld n
-        const double* R2;    // ld n
-        const int32_t* state;
-        double* R;
-        int64_t ldr;
-        int prec;
-        const uint32_t* amax;
-        int64_t rows;
-    };
-    static constexpr int NTH = 256, WPE = 0;
-    static constexpr int T = 32;
-    static __device__ void run(const Args& a, int bx, int)
-    {
-        __shared__ double l[T][T + 1], u[T][T + 1];   // l[k][i] of R2, u[j][k] of R1
-        const int64_t n = a.n, nt = (n + T - 1) / T, ti = bx % nt, tj = bx / nt;
-        const int i = threadIdx.x % T, q = threadIdx.x / T;
-        double v[4] = {0, 0, 0, 0};
-        auto entry = [&](const double* M, int64_t r, int64_t c) { return r <= c && c < n ? M[r + c * n] : 0.0; };
-        if (*a.state == 1) {
-            for (int64_t k0 = T * ti; k0 <= T * tj; k0 += T) {
-                __syncthreads();
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    l[q + 8 * e][i] = entry(a.R2, T * ti + i, k0 + q + 8 * e);
-                    u[q + 8 * e][i] = entry(a.R1, k0 + i, T * tj + q + 8 * e);
-                }
-                __syncthreads();
-#pragma unroll 8
-                for (int k = 0; k < T; ++k)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] += l[k][i] * u[q + 8 * e][k];
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = entry(a.R1, T * ti + i, T * tj + q + 8 * e);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int64_t r = T * ti + i, c = T * tj + q + 8 * e;
-            if (r >= n || c >= n) continue;
-            const float f = r <= c ? (float)v[e] : 0.0f;
-            double w = (double)f;
-            if (a.prec == PNE_PREC_BF16) w = (double)__uint_as_float((uint32_t)f32_to_bf16_bits(f) << 16);
-            if (a.prec == PNE_PREC_FP16)
-                w = (double)(float)__builtin_bit_cast(_Float16, f32_to_f16_bits(f)) / (double)qr_scale(a.amax, a.rows);
-            a.R[r + c * a.ldr] = w;
-        }
-    }
-};
-
-// Triangular factor of the FP32 sketch W (s x n) without the factorization of
-// W: R^T R = W^T W with the Gram matrix and its Cholesky factor in FP64.
-//
-// The Householder QR of an s x n sketch is one panel of 8 or 16 columns after
-// another, each with two barriers per column, and an update of the rest that
-// reads W twice: 3.4 ms at 3000 x 1000 whatever the arithmetic.  The Gram
-// matrix is one product.  R agrees with the Householder factor up to the signs
-// of its rows, which cancel in A_p^T A_p, R_s x = y; where R itself is the
-// result, the Householder QR runs.
-//
-// The products of FP32 entries are exact in FP64; what the Gram matrix and its
-// factor lose is a perturbation of C = W^T W by E with |E| up to about n 2^-53
-// |D|^2 (D the columns' norms; the bound is some n^2 2^-53).  So the factor is
-// taken of C + t D^2 with t = 8 n 2^-53, which no rounding makes indefinite,
-// and R1 is the factor of W with each singular value (columns scaled to
-// norm 1) raised by at most sqrt(t): nothing while they are well above it (1e-6
-// at n = 1000).  A pivot below 256 t D^2 says that they may not be (the smallest
-// pivot is 25 to 60 times the square of the smallest singular value for sketches of
-// geometric spectra, n = 100 to 700).  Then W is factored once more where R1
-// has made it nearly orthogonal (Cholesky QR in two passes, Yamamoto et al.
-// 2015, with the shift of Fukaya et al. 2020): X = [W; 2^-24.5 D] R1^{-1}, in
-// FP64, has singular values between 1 and 1 / sqrt(2^49 t) (0.02 at n = 1000), R2
-// is the factor of X^T X, and R = R2 R1 the factor of [W; 2^-24.5 D] to 1e-10
-// in every direction.  The rows 2^-24.5 D keep the directions that W does not
-// have at the size that the rounding errors of an FP32 Householder
-// factorization leave there: condition numbers of A R^-1 equal or below that
-// factorization's for kappa 1e4 to 1e14, for repeated columns and for sampled rows
-// of a square matrix (numpy, n = 2 to 700).  The second pass is launched always
-// and its kernels end at once where the state says so: nothing is read back.
-//
-// Measured, 3000 x 1000: QR 3.4 ms, this 0.44 ms (Gram and reduction 0.1,
-// Cholesky 0.34); 300 x 100 199 -> 57 us, 6000 x 2000 13.3 -> 1.3 ms.
-//
-// C: n x n scratch; P: scratch of pslots n x n FP64 matrices (at least one);
-// tab: dinv_elems(n), gd: n, words: two (FP16: scale; state); X: scratch of
-// sketch_factor_doubles(s, n), 16-byte aligned.
-size_t sketch_factor_doubles(int64_t s, int64_t n)
-{
-    return (size_t)(trsm_sketch_ld(s, n) * n) + trsm_pack_bytes(n) / sizeof(double) + (size_t)(n * n);
-}
-int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
-                  double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, double* X, int32_t* info)
-{
-    uint32_t* amax = words;
-    int32_t* state = (int32_t*)words + 1;
-    double* pack = X + trsm_sketch_ld(s, n) * n;
-    double* R1 = pack + trsm_pack_bytes(n) / sizeof(double);
-    const double t = 8.0 * (double)n * 0x1p-53;
-    ex.stage(ST_SKFACTOR);
-    if (prec == PNE_PREC_FP16) qr_max(ex, s, n, W, ldw, amax);
-    if (prec == PNE_PREC_BF16 || prec == PNE_PREC_FP16)
-        launch<RoundMatrix<float>>(ex, ceil_div(s * n, 256), 1, RoundMatrixArgs{s, n, W, ldw, prec, amax});
-    gram_f32(ex, s, n, W, ldw, C, P, pslots);
-    ex.stage(ST_SKFACTOR_CHOL);
-    cholesky64_shifted(ex, n, C, n, R1, n, tab, gd, t, state, nullptr);
-    ex.stage(ST_SKFACTOR_AGAIN);
-    trsm_sketch(ex, s, n, W, ldw, gd, 0x1p-49, R1, n, X, pack, state);
-    gram_f64_when(ex, s + n, n, X, trsm_sketch_ld(s, n), C, P, pslots, state);
-    ex.stage(ST_SKFACTOR_AGAIN_CHOL);
-    cholesky64_shifted(ex, n, C, n, P, n, tab, gd, t, nullptr, state);
-    ex.stage(ST_SKFACTOR_END);
-    const int64_t nt = ceil_div(n, SketchR::T);
-    launch<SketchR>(ex, nt * nt, 1, SketchR::Args{n, R1, P, state, R, ldr, prec, amax, s});
     launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
     return launch_status(ex);
 }

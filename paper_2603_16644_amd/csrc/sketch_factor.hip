@@ -1,0 +1,271 @@
+// Triangular factor of an FP32 sketch W (s x n) without the factorization of
+// W: R^T R = W^T W with the Gram matrix and its Cholesky factor in FP64.
+//
+// The Householder QR of an s x n sketch is one panel of 8 or 16 columns after
+// another, each with two barriers per column, and an update of the rest that
+// reads W twice: 3.4 ms at 3000 x 1000 whatever the arithmetic.  The Gram
+// matrix is one product.  R agrees with the Householder factor up to the signs
+// of its rows, which cancel in A_p^T A_p, R_s x = y; where R itself is the
+// result, the Householder QR runs.
+//
+// The products of FP32 entries are exact in FP64; what the Gram matrix and its
+// factor lose is a perturbation of C = W^T W of norm up to about n 2^-53 |D|^2
+// (D the columns' norms; the bound is some n^2 2^-53).  So the factor is
+// taken of C + t D^2 with t = 8 n 2^-53, which no rounding makes indefinite,
+// and R1 is the factor of W with each singular value (columns scaled to
+// norm 1) raised by at most sqrt(t): nothing while they are well above it (1e-6
+// at n = 1000).  A pivot below 256 t D^2 says that they may not be (the
+// smallest pivot is 25 to 60 times the square of the smallest singular value
+// for sketches of geometric spectra, n = 100 to 700).  Then W is factored once more
+// where R1 has made it nearly orthogonal (Cholesky QR in two passes, Yamamoto
+// et al. 2015, with the shift of Fukaya et al. 2020): X = [W; 2^-24.5 D] R1^{-1},
+// in FP64, has singular values between 1 and 1 / sqrt(2^49 t) (0.03 at n =
+// 1000), R2 is the factor of X^T X, and R = R2 R1 the factor of [W; 2^-24.5 D]
+// to 1e-10 in every direction.  The rows 2^-24.5 D keep the directions that
+// W does not have at the size that the rounding errors of an FP32 Householder
+// factorization leave there: condition numbers of A R^-1 equal to or below that
+// factorization's for kappa 1e4 to 1e14, for repeated columns and for sampled
+// rows of a square matrix (emulated, n = 2 to 700).
+//
+// The second pass is part of the launch that writes R (SketchEnd), so that
+// nothing is read back and solves that do not need it pay for no launch of it
+// (as 3 + n / 64 launches that end at once it cost 5 us each: 2000 x 100 solves
+// 212 -> 237 us, 100000 x 1000 6.11 -> 6.25 ms).
+//
+// Measured, 3000 x 1000: Householder QR 3.4 ms, this 0.45 ms (Gram and reduction
+// 0.1, Cholesky 0.34, SketchEnd 0.014); 300 x 100 199 -> 57 us, 6000 x 2000 13.3 ->
+// 1.3 ms.  The second pass adds 1.8 ms, 0.12 ms and 6.5 ms to these where it runs.
+#include "chol_dev.h"
+#include "common.h"
+#include "convert.h"
+#include "gemm_tn_dev.h"
+#include "kernels.h"
+#include "launch.h"
+#include "trsm_dev.h"
+
+namespace pne {
+
+struct SketchEndArgs {
+    int64_t s, n;
+    const float* W;
+    int64_t ldw;
+    double* X;           // second pass: (s + n) x n, ld ldx
+    int64_t ldx;
+    double* pack;        // packed R1
+    const double* R1;    // ld n, like R2 and C
+    double* R2;
+    double* C;           // Gram matrix of X
+    double* tab;
+    double* gd;          // squared norms of the columns of W
+    double t;            // shift of the Cholesky factors
+    const int32_t* state;
+    int32_t* work;       // next work item, items done (zero)
+    double* R;
+    int64_t ldr;
+    int prec;
+    const uint32_t* amax;
+    int32_t wgs;
+    int32_t* info;       // 4001 where a wait gives up
+};
+
+// R = R1, or R2 R1 after a second pass (upper triangles), rounded to the
+// precision of the factor (FP32, BF16, or FP16 with the input scale divided
+// out), zero below; 32 x 32 entries per tile, four per thread.
+//
+// The second pass runs where *state is 1.  Its work items are numbered in the
+// order of its phases: pack R1 and form [W; 2^-24.5 D]; substitution, 64 rows an item;
+// Gram matrix, a tile of 64 x 64 an item; the steps of the Cholesky
+// factorization; tiles of R.  A work-group takes the next number from a
+// counter and waits until all items of the earlier phases are done.  Those
+// have lower numbers, so other work-groups took them and are working on them
+// or waiting for lower ones yet: whatever number of work-groups is on the
+// machine, the lowest item not done is never waiting, and every wait ends.
+struct SketchEnd {
+    typedef SketchEndArgs Args;
+    static constexpr int NTH = 256, WPE = 1;
+    static constexpr int T = 32;
+    static constexpr int FILL = 8;   // blocks of R1 or columns of X per item of the first phase
+
+    static __host__ __device__ int64_t tiles(int64_t n) { return (n + T - 1) / T; }
+    static __device__ __forceinline__ int64_t pack_items(int64_t n)
+    {
+        const int64_t nblk = (n + TB16 - 1) / TB16;
+        return nblk * ((nblk + FILL - 1) / FILL);
+    }
+    static __device__ __forceinline__ void fill(const Args& a, int64_t e)
+    {
+        const int64_t n = a.n, nblk = (n + TB16 - 1) / TB16, np = pack_items(n);
+        if (e < np) {
+            const TrsmPack::Args p{n, a.R1, n, a.pack};
+            for (int c = 0; c < FILL; ++c) TrsmPack::run(p, (int)(e / nblk) * FILL + c, (int)(e % nblk));
+            return;
+        }
+        const int64_t rows = a.s + n, rt = (rows + NTH - 1) / NTH;
+        const int64_t i = (e - np) % rt * NTH + threadIdx.x, j0 = (e - np) / rt * FILL;
+        if (i >= rows) return;
+        for (int64_t j = j0; j < j0 + FILL && j < n; ++j)
+            a.X[i + j * a.ldx] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(0x1p-49 * a.gd[j]) : 0.0);
+    }
+    static __device__ __forceinline__ void tile(const Args& a, int64_t e, bool again)
+    {
+        __shared__ double l[T][T + 1], u[T][T + 1];   // l[k][i] of R2, u[j][k] of R1
+        const int64_t n = a.n, nt = tiles(n), ti = e % nt, tj = e / nt;
+        const int i = threadIdx.x % T, q = threadIdx.x / T;
+        double v[4] = {0, 0, 0, 0};
+        auto entry = [&](const double* M, int64_t r, int64_t c) { return r <= c && c < n ? M[r + c * n] : 0.0; };
+        if (again) {
+            for (int64_t k0 = T * ti; k0 <= T * tj; k0 += T) {
+                __syncthreads();
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    l[q + 8 * x][i] = entry(a.R2, T * ti + i, k0 + q + 8 * x);
+                    u[q + 8 * x][i] = entry(a.R1, k0 + i, T * tj + q + 8 * x);
+                }
+                __syncthreads();
+#pragma unroll 8
+                for (int k = 0; k < T; ++k)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) v[x] += l[k][i] * u[q + 8 * x][k];
+            }
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[x] = entry(a.R1, T * ti + i, T * tj + q + 8 * x);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int64_t r = T * ti + i, c = T * tj + q + 8 * x;
+            if (r >= n || c >= n) continue;
+            const float f = r <= c ? (float)v[x] : 0.0f;
+            double w = (double)f;
+            if (a.prec == PNE_PREC_BF16) w = (double)__uint_as_float((uint32_t)f32_to_bf16_bits(f) << 16);
+            if (a.prec == PNE_PREC_FP16)
+                w = (double)(float)__builtin_bit_cast(_Float16, f32_to_f16_bits(f)) / (double)qr_scale(a.amax, a.s);
+            a.R[r + c * a.ldr] = w;
+        }
+    }
+    static __device__ __forceinline__ void wait(const Args& a, int64_t items)
+    {
+        for (uint32_t it = 0; it < (1u << 24); ++it) {
+            if (__hip_atomic_load(a.work + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= items) return;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        int32_t expected = 0;
+        __hip_atomic_compare_exchange_strong(a.info, &expected, 4001, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    }
+    static __device__ __forceinline__ void second_pass(const Args& a)
+    {
+        __shared__ int32_t next;
+        const int64_t n = a.n, rows = a.s + n, nb = (n + CB - 1) / CB, nt = tiles(n);
+        const int64_t fills = pack_items(n) + (rows + NTH - 1) / NTH * ((n + FILL - 1) / FILL);
+        const int64_t subst = (rows + 63) / 64, gram = nb * (nb + 1) / 2;
+        // (Cholesky step k = 0 .. nb - 2 has r (r + 1) / 2 tiles, r = nb - 1 - k)
+        const int64_t chol = 1 + (nb - 1) * nb * (nb + 1) / 6;
+        const int64_t total = fills + subst + gram + chol + nt * nt;
+        // (Thread 0 has one block of its own per turn, between two barriers.  With
+        // one at each end of the turn the compiler joins the two into a path
+        // for thread 0 alone, and the other lanes of its wavefront pass the
+        // barriers without it.)
+        if (threadIdx.x == 0) next = __hip_atomic_fetch_add(a.work, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (;;) {
+            __syncthreads();
+            const int32_t it = __builtin_amdgcn_readfirstlane(next);
+            if (it >= total) break;
+            // the item's phase: its first item, and (Cholesky) its step
+            int64_t first = 0, k = -1;
+            int phase = 0;
+            if (it >= fills) { phase = 1; first = fills; }
+            if (it >= fills + subst) { phase = 2; first = fills + subst; }
+            if (it >= fills + subst + gram) {
+                phase = 3;
+                first = fills + subst + gram;
+                for (int64_t c = 1; k + 1 < nb; ++k) {
+                    if (it < first + c) break;
+                    first += c;
+                    const int64_t r = nb - 2 - k;   // of step k + 1
+                    c = r * (r + 1) / 2;
+                }
+                if (k + 1 >= nb) phase = 4;
+            }
+            if (threadIdx.x == 0 && first > 0) wait(a, first);
+            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            const int e = (int)(it - first);
+            if (phase == 0) {
+                fill(a, e);
+            } else if (phase == 1) {
+                // (in place: a lane loads its entries of a panel's columns
+                // before it stores there, and keeps nothing it loads of
+                // another's row)
+                const TrsmArgs p{rows, n, a.X, a.ldx, a.pack, a.X, a.ldx};
+                TrsmRows<false>::run(p, e, 0);
+            } else if (phase == 2) {
+                GemmArgs g{};
+                g.M = n; g.N = n; g.K = rows;
+                g.A = a.X; g.lda = a.ldx;
+                g.B = a.X; g.ldb = a.ldx;
+                g.lower = 1;
+                g.splits = 1;
+                g.kchunk = (rows + 15) / 16 * 16;
+                g.P = a.C;
+                GemmTn<double, false>::run(g, e, 0);
+            } else if (phase == 3) {
+                const CholStepArgs p{n, k, a.C, n, nullptr, 0, a.R2, n, a.tab, a.gd, a.t, nullptr, nullptr, nullptr};
+                CholStep<true>::run(p, e, 0);
+            } else {
+                tile(a, e, true);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __hip_atomic_fetch_add(a.work + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                next = __hip_atomic_fetch_add(a.work, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    static __device__ __forceinline__ void run(const Args& a, int bx, int)
+    {
+        if (*a.state == 1) {
+            second_pass(a);
+            return;
+        }
+        const int64_t nt = tiles(a.n);
+        for (int64_t e = bx; e < nt * nt; e += a.wgs) tile(a, e, false);
+    }
+};
+
+static int64_t sketch_ld(int64_t s, int64_t n) { return (s + n + 1) & ~(int64_t)1; }
+
+size_t sketch_factor_doubles(int64_t s, int64_t n)
+{
+    return (size_t)(sketch_ld(s, n) * n) + trsm_pack_bytes(n) / sizeof(double) + (size_t)(n * n);
+}
+
+// C: n x n scratch; P: scratch of pslots n x n FP64 matrices (at least one);
+// tab: dinv_elems(n), gd: n, words: two (FP16: scale; state), work: two; X:
+// scratch of sketch_factor_doubles(s, n), 16-byte aligned.
+int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
+                  double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, int32_t* work, double* X,
+                  int32_t* info)
+{
+    uint32_t* amax = words;
+    int32_t* state = (int32_t*)words + 1;
+    double* pack = X + sketch_ld(s, n) * n;
+    double* R1 = pack + trsm_pack_bytes(n) / sizeof(double);
+    const double t = 8.0 * (double)n * 0x1p-53;
+    ex.stage(ST_SKFACTOR);
+    qr_round(ex, s, n, W, ldw, prec, amax);
+    gram_f32(ex, s, n, W, ldw, C, P, pslots);
+    ex.stage(ST_SKFACTOR_CHOL);
+    cholesky64_shifted(ex, n, C, n, R1, n, tab, gd, t, state, work);
+    ex.stage(ST_SKFACTOR_END);
+    // one work-group per CU at most (LDS)
+    const int64_t nt = SketchEnd::tiles(n), most = nt * nt > ceil_div(s, 64) ? nt * nt : ceil_div(s, 64);
+    const int32_t wgs = (int32_t)(most < 256 ? most : 256);
+    launch<SketchEnd>(ex, wgs, 1, SketchEndArgs{s, n, W, ldw, X, sketch_ld(s, n), pack, R1, P, C, tab, gd, t, state, work,
+                                                R, ldr, prec, amax, wgs, info});
+    check_r_diag(ex, n, R, ldr, info);
+    return launch_status(ex);
+}
+
+}  // namespace pne

@@ -89,3 +89,54 @@ def test_many_repeated_columns(pne, n):
     xs = rng.standard_normal(n) / d
     x = solve(pne, False, A * d, (A * d) @ xs, seed=3, sketch_prec="fp32", qr_prec="fp32", refine_steps=3)
     assert np.linalg.norm((x - xs) * d) <= 10 * np.linalg.cond(A) * U * np.linalg.norm(xs * d)
+
+
+@pytest.mark.parametrize("n", [2, 3, 16, 17, 33, 63, 65, 128, 129, 513, 700])
+@pytest.mark.parametrize("qr", ["fp32", "fp16"])
+def test_second_factor_sizes(pne, n, qr):
+    """The last two columns (all but the first of three) repeat the first to
+    1e-9, at the edges of the blocks of the second factor's steps; tolerance as
+    above."""
+    m = 6 * n + 900
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((m, n))
+    k = min(2, n - 1)
+    A[:, n - k:] = A[:, :1] + 1e-9 * rng.standard_normal((m, k))
+    A /= np.linalg.norm(A, axis=0)
+    xs = rng.standard_normal(n)
+    x = solve(pne, False, A, A @ xs, seed=3, sketch_prec="fp32", qr_prec=qr, refine_steps=3)
+    assert np.linalg.norm(x - xs) <= 10 * np.linalg.cond(A) * U * np.linalg.norm(xs)
+
+
+def test_second_factor_in_batches_and_replays(pne):
+    """Members that need the second factor beside members that do not: each
+    solves as it does alone, bit for bit, and a plan replayed from a graph, with
+    other work between the replays, gives the same every time."""
+    from workloads.problems import pack_batch
+    shapes = [(3000, 100, 1e10), (2000, 64, 1e2), (4000, 300, 1e9), (900, 33, 1e8), (700, 100, 1e4)]
+    probs = [make_problem(m, n, k, 1e-10, seed=330 + i) for i, (m, n, k) in enumerate(shapes)]
+    A, b, x, descs = pack_batch(probs, "cuda")
+    o = pne.make_opts(seed=5, sketch_prec="fp64", qr_prec="fp32", refine_steps=1)
+    info = pne.pne_solve_batched(A, b, x, descs, opts=o)
+    torch.cuda.synchronize()
+    assert not bool(info.any())
+    ref = x.clone()
+    for i, (p, d) in enumerate(zip(probs, descs)):
+        Ai = A[d["a_offset"]:d["a_offset"] + p.m * p.n].reshape(p.n, p.m).contiguous().t()
+        bi = b[d["b_offset"]:d["b_offset"] + p.m].contiguous()
+        one = torch.zeros_like(x[d["x_offset"]:d["x_offset"] + p.n])
+        inf1 = pne.pne_solve_batched(Ai.t().reshape(-1), bi, one,
+                                     [dict(m=p.m, n=p.n, lda=p.m, a_offset=0, b_offset=0, x_offset=0, problem_id=i)], opts=o)
+        assert int(inf1.item()) == 0
+        assert torch.equal(one, ref[d["x_offset"]:d["x_offset"] + p.n])
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        plan = pne.BatchPlan(A, b, x, descs, opts=o, stream=st)
+        for _ in range(4):
+            x.fill_(float("nan"))
+            junk = torch.randn(1 << 20, device="cuda").sum()
+            info = plan.execute_graph(st)
+            st.synchronize()
+            assert float(junk) == float(junk) and not bool(info.any())
+            assert torch.equal(x, ref)
+    plan.close()
