@@ -913,7 +913,7 @@ static Problem gram_problem(int64_t m, int64_t n, int64_t lda, int hpne)
     pne_default_opts(&o);
     o.s = n;
     o.sketch_prec = PNE_PREC_FP64;
-    o.qr_prec = PNE_PREC_FP64;
+    o.qr_prec = PNE_PREC_FP32;   // (no QR runs; sizes the workspace)
     o.refine_steps = 0;
     return make_problem(m, n, lda, &o, hpne);
 }

@@ -615,7 +615,8 @@ int64_t gemm_tiles(int64_t M, int64_t N, int64_t K, int lower)
 // resident work-groups), preferring more work-groups when the fill is equal.
 // In a batch (kchunk_fixed > 0) every product is cut into chunks of a fixed
 // length instead, so that work-groups carry similar work across members.
-void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed)
+// most > 0: at most so many splits (not for fixed lengths).
+void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed, int64_t most)
 {
     if (kchunk_fixed > 0) {
         const int64_t kc = ceil_div(kchunk_fixed < K ? kchunk_fixed : K, G_BK) * G_BK;
@@ -628,6 +629,7 @@ void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int
     int64_t maxs = K / 128;
     if (maxs < 1) maxs = 1;
     if (maxs > 4 * slots) maxs = 4 * slots;
+    if (most > 0 && maxs > most) maxs = most;
     int64_t best = 1;
     double best_eff = -1.0;
     for (int64_t sp = 1; sp <= maxs; ++sp) {
@@ -642,6 +644,17 @@ void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int
     *splits = ceil_div(K, kc);
 }
 
+// The plan of A^T B with an n x n result, whichever kernel runs it.  A plan in
+// 64 x 64 tiles never has more partial sums than one in the tiles of GemmCm:
+// four times the tiles would fill the machine best with up to 1.8 times the
+// workspace (A^T B of 50,000 x 185: 227 splits, 62 MB, for 128 and 35 MB), and
+// callers have a fixed one.
+void plan_splitk_product(int64_t K, int64_t n, int lower, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed)
+{
+    plan_splitk(K, gemm_tiles(n, n, K, lower), splits, kchunk, kchunk_fixed);
+    if (tn_route(n, n, K, lower)) plan_splitk(K, tn_tiles(n, n, lower), splits, kchunk, kchunk_fixed, *splits);
+}
+
 // Lower triangles in 128 x 128 tiles: the off-diagonal tiles keep their
 // split count sf, and the diagonal tiles, whose busiest wavefront carries 10
 // of the 16 MFMA blocks (see GemmCm::run), get a split count sd of their
@@ -651,8 +664,7 @@ void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int
 void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int64_t* splits, int64_t* kchunk,
                       int64_t* splits_diag, int64_t* kchunk_diag)
 {
-    plan_splitk(K, tn_route(n, n, K, lower) ? tn_tiles(n, n, lower) : gemm_tiles(n, n, K, lower), splits, kchunk,
-                kchunk_fixed);
+    plan_splitk_product(K, n, lower, splits, kchunk, kchunk_fixed);
     *splits_diag = 0;
     *kchunk_diag = 0;
     if (!lower || kchunk_fixed > 0 || K < 2 * G_BK || tile_shape(n, n, K, lower).bm != 128) return;

@@ -95,7 +95,8 @@ void gemm_f32_partials(Exec& ex, const GemmArgs& g);
 void gemm_ddf(Exec& ex, const GemmArgs& g);           // fl32(A)^T fl32(B) etc.
 // split-K plan: splits and kchunk for a long-K product with `tiles` output
 // tiles (kchunk_fixed > 0: fixed chunk length, for batches)
-void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed = 0);
+void plan_splitk(int64_t K, int64_t tiles, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed = 0, int64_t most = 0);
+void plan_splitk_product(int64_t K, int64_t n, int lower, int64_t* splits, int64_t* kchunk, int64_t kchunk_fixed);
 int64_t gemm_tiles(int64_t M, int64_t N, int64_t K, int lower);
 // split-K plan of the FP64 Gram product (n x n, K = m; lower-triangle tiles
 // when `lower`): plan_splitk, or for lower triangles in 128 x 128 tiles a

@@ -26,7 +26,7 @@ struct NneBuffers {
 size_t nne_layout(int64_t m, int64_t n, void* base, NneBuffers* out)
 {
     NneBuffers b{};
-    plan_splitk(m, tn_route(n, n, m, 0) ? tn_tiles(n, n, 0) : gemm_tiles(n, n, m, 0), &b.splits, &b.kchunk);
+    plan_splitk_product(m, n, 0, &b.splits, &b.kchunk, 0);
     Arena ar(base, 0);
     b.P = ar.take<double>((size_t)b.splits * n * n);
     b.Pc = ar.take<double>((size_t)b.splits * n);

@@ -1,0 +1,48 @@
+"""Workspace sizes and what fits the fixed ones (host code: no GPU).  A caller
+whose memory was enough for a call must not be refused by a later library:
+the sizes below are those of the first versions of the entry points."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def pne():
+    import paper_2603_16644_amd as p
+    if not os.path.exists(p._lib.LIB_PATH):
+        from paper_2603_16644_amd.build import build
+        build()
+    return p
+
+
+@pytest.mark.parametrize("m,n,size", [(49976, 185, 35292416), (8000, 185, 15957504), (100000, 64, 16911616)])
+def test_nne(pne, m, n, size):
+    assert 0 < pne.lib().nne_workspace_size(m, n) <= size
+
+
+@pytest.mark.parametrize("m,n,hpne,size", [(8604, 285, 1, 59221248), (22, 1, 0, 104960), (8604, 285, 0, 60035072)])
+def test_gram(pne, m, n, hpne, size):
+    assert 0 < pne.lib().pne_gram_workspace_size(m, n, hpne) <= size
+
+
+@pytest.mark.parametrize("m,n,opts,size", [
+    (23159, 184, dict(sketch_prec="fp8", qr_prec="fp32"), 68383488),
+    (26958, 169, dict(sketch_prec="fp8", qr_prec="fp32", block_rows=256), 65481472),
+    (23159, 184, dict(sketch_prec="bf16", qr_prec="fp32", sketch_kind="srft"), 69774080),
+    (9474, 317, dict(sketch_prec="fp16", qr_prec="bf16"), 70807808),
+])
+def test_hpne(pne, m, n, opts, size):
+    o = pne.make_opts(**opts)
+    assert 0 < pne.lib().pne_workspace_size(m, n, ctypes.byref(o), 1) <= size
+
+
+@pytest.mark.parametrize("m,n,opts", [
+    (22874, 177, dict(sketch_prec="fp8", qr_prec="fp32")),
+    (14278, 267, dict(sketch_prec="fp32", qr_prec="fp32", sketch_kind="srft")),
+])
+def test_static_array_holds(pne, m, n, opts):
+    """HPNE in the static array of pne_solve_noalloc: past the size check, at
+    the check of the pointers (-1), not refused for its size (-4)."""
+    o, one = pne.make_opts(**opts), ctypes.c_void_p(256)
+    assert pne.lib().pne_solve_noalloc(m, n, None, m, one, one, ctypes.byref(o), 1, one, None, None) == -1
