@@ -205,7 +205,8 @@ pne_status qr_ls_solve(int64_t m, int64_t n, const double* dA, int64_t lda, cons
 /* pne_sketch: the sketch step alone, A_s = Omega A (s x n, FP64 output,
  * ldas >= s) in precision `prec` (FP64, FP32, FP16, BF16, FP8E4M3), with the
  * operand rounding the solvers use.  Omega as in pne_solve.
- * Workspace: pne_sketch_workspace_size. */
+ * Workspace: pne_sketch_workspace_size for block_rows 128; FP8 and FP16 with
+ * other block lengths may need more. */
 size_t pne_sketch_workspace_size(int64_t m, int64_t n, int64_t s, int32_t prec);
 pne_status pne_sketch(int64_t m, int64_t n, const double* dA, int64_t lda, int64_t s, uint64_t seed,
                       uint32_t problem_id, int32_t prec, int32_t block_rows, double* dAs,

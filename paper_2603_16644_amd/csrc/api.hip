@@ -867,7 +867,7 @@ pne_status cond_est_qr(int64_t m, int64_t n, const double* dA, int64_t lda, int6
 size_t pne_sketch_workspace_size(int64_t m, int64_t n, int64_t s, int32_t prec)
 {
     if (n < 1 || m < 1 || s < 1 || !valid_prec(prec, false, true)) return 0;
-    return sketch_workspace_bytes(m, n, s, prec, 128) + 1024;
+    return sketch_workspace_bytes_any(m, n, s, prec) + 1024;
 }
 
 pne_status pne_sketch(int64_t m, int64_t n, const double* dA, int64_t lda, int64_t s, uint64_t seed,

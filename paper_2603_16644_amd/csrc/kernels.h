@@ -41,7 +41,10 @@ struct SketchPlan {
 };
 // kchunk_fixed > 0: split the product over rows of A in chunks of this
 // length (batches) instead of filling the machine with one sketch
-SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed = 0);
+// narrow: a scaled sketch's plan for the narrow product whatever br.
+SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed = 0,
+                       bool narrow = false);
+size_t sketch_workspace_bytes_any(int64_t m, int64_t n, int64_t s, int prec);
 size_t sketch_workspace_bytes(int64_t m, int64_t n, int64_t s, int prec, int64_t br,
                               int64_t kchunk_fixed = 0);
 int sketch_run(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, int64_t s, uint64_t seed,

@@ -595,6 +595,14 @@ size_t sketch_workspace_bytes(int64_t m, int64_t n, int64_t s, int prec, int64_t
     return p.bytes;
 }
 
+// For a caller who has not given the block length yet: FP8 and FP16 sketches
+// take the narrow product, with four times the partial sums, for some.
+size_t sketch_workspace_bytes_any(int64_t m, int64_t n, int64_t s, int prec)
+{
+    const size_t wide = plan_sketch(m, n, s, prec, 128).bytes, narrow = plan_sketch(m, n, s, prec, 128, 0, true).bytes;
+    return wide > narrow ? wide : narrow;
+}
+
 // Tile (32 wm x 64 wn) and split count of the wide kernel.  One work-group
 // runs per CU, the largest split count whose work-groups fit the machine at
 // once: the time is that of (rounds of 256 work-groups) x (tile) / (splits).
@@ -642,7 +650,7 @@ static void wide_launch(Exec& ex, const SketchPlan& p, int64_t s, int64_t n, con
     else launch<GemmLpW<OP, 8, 4>>(ex, gx, p.splits, a);
 }
 
-SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed)
+SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, int64_t kchunk_fixed, bool narrow)
 {
     SketchPlan p{};
     const int op = prec_to_opk(prec);
@@ -668,7 +676,7 @@ SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, in
         wide_tile(s, n, op, maxsplit, &p.wm, &p.wn, &p.splits);
         p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
         p.splits = ceil_div(p.ldk, p.kchunk);
-    } else if (wide_scaled(op, br)) {
+    } else if (wide_scaled(op, br) && !narrow) {
         // the same with 128 x 256 tiles
         int64_t maxsplit = p.ldk / (4 * align);
         if (maxsplit < 1) maxsplit = 1;

@@ -46,3 +46,24 @@ def test_static_array_holds(pne, m, n, opts):
     the check of the pointers (-1), not refused for its size (-4)."""
     o, one = pne.make_opts(**opts), ctypes.c_void_p(256)
     assert pne.lib().pne_solve_noalloc(m, n, None, m, one, one, ctypes.byref(o), 1, one, None, None) == -1
+
+
+@pytest.mark.parametrize("prec,br,m,n,s", [
+    (5, 64, 1846, 1331, 3993), (5, 192, 9561, 1408, 1408), (5, 256, 9561, 1408, 1408), (5, 320, 9561, 1408, 1408),
+    (5, 512, 9561, 1408, 1408), (5, 1024, 1846, 1331, 3993), (3, 192, 25814, 148, 1037), (3, 256, 9561, 1408, 1408),
+    (3, 320, 1363, 1012, 7085),
+])
+def test_sketch_takes_the_size_it_names(pne, prec, br, m, n, s):
+    """pne_sketch with pne_sketch_workspace_size bytes is not refused as too
+    small (-4) where it was not, for other block lengths than the 128 rows that
+    are the default.
+    (Without a GPU the call then ends in the HIP error of its first launch;
+    with one the placeholder pointers must not be used, so it is skipped.)"""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("placeholder device pointers")
+    L = pne.lib()
+    size = L.pne_sketch_workspace_size(m, n, s, prec)
+    p = ctypes.c_void_p(0x100000)
+    assert size > 0
+    assert L.pne_sketch(m, n, p, m, s, 1, 0, prec, br, p, s, p, size, None) == -3
