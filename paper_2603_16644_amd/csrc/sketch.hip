@@ -160,53 +160,46 @@ __device__ void QuantizePlain<OP>::run(const QuantArgs& a, int bx, int by)
 }
 
 // Scaled formats: one scale per block of br rows of a column (br a multiple of
-// 64).  A wavefront takes QS_BLKS blocks of a column with their rows in
-// registers (QS_RPL per lane at most; longer blocks are read twice), so A is
-// read once: bound by memory.  A work-group per block, reading it for the
-// largest entry and again to convert, is bound by the launch of its 1.6e6
-// work-groups at 400,000 x 500 (1.27 ms; 0.45 ms so).
-constexpr int QS_RPL = 4, QS_BLKS = 4;
+// 64).
 template <int OP>
+__device__ __forceinline__ float block_scale(float amax)
+{
+    if (amax == 0.0f) return 0.0f;
+    if constexpr (OP == OPK_F16) {
+        int E;
+        frexpf(amax, &E);                   // amax = f 2^E, f in [0.5, 1)
+        return ldexpf(1.0f, (E - 1) - 14);
+    } else {
+        return amax / 448.0f;
+    }
+}
+template <int OP>
+__device__ __forceinline__ typename Op<OP>::T scaled_op(float v, float scale)
+{
+    return to_op<OP>(scale != 0.0f ? v / scale : 0.0f);
+}
+
+// Blocks of up to 64 RPL rows: a wavefront takes QS_BLKS blocks of a column with
+// their rows in registers, so A is read once and the work-groups are few: bound
+// by memory (400,000 x 500 in blocks of 128 to FP8 0.45 ms; a work-group per block,
+// 1.6e6 of them, 1.27 ms).
+constexpr int QS_BLKS = 4;
+template <int OP, int RPL>
 struct QuantizeScaled {
     typedef QuantArgs Args;
     static constexpr int NTH = 256, WPE = 0;
-    static constexpr int BLKS = 4 * QS_BLKS;     // blocks of a work-group
-    static __device__ __forceinline__ float scale_of(float amax)
-    {
-        if (amax == 0.0f) return 0.0f;
-        if constexpr (OP == OPK_F16) {
-            int E;
-            frexpf(amax, &E);                   // amax = f 2^E, f in [0.5, 1)
-            return ldexpf(1.0f, (E - 1) - 14);
-        } else {
-            return amax / 448.0f;
-        }
-    }
-    static __device__ void run(const QuantArgs& a, int bx, int by)
+    static __device__ void run(const Args& a, int bx, int by)
     {
         const int64_t kc = a.kc, ldk = a.ldk, br = a.br, n = a.n, j = by;
         const double* __restrict__ Aj = a.A + a.k0 + j * a.lda;
         typename Op<OP>::T* __restrict__ Qj = (typename Op<OP>::T*)a.Aq + j * ldk;
         const int lane = threadIdx.x & 63;
-        const int64_t kb0 = (int64_t)bx * BLKS + (threadIdx.x >> 6) * QS_BLKS;
-        if (br > 64 * QS_RPL) {
-            for (int i = 0; i < QS_BLKS; ++i) {
-                const int64_t r0 = (kb0 + i) * br;
-                if (r0 >= ldk) return;
-                float amax = 0.0f;
-                for (int64_t r = r0 + lane; r < r0 + br && r < kc; r += 64) amax = fmaxf(amax, fabsf((float)Aj[r]));
-                const float scale = scale_of(wave_max(amax));
-                if (lane == 0) a.sc[(kb0 + i) * n + j] = scale;
-                for (int64_t r = r0 + lane; r < r0 + br && r < ldk; r += 64)
-                    Qj[r] = to_op<OP>((r < kc && scale != 0.0f) ? (float)Aj[r] / scale : 0.0f);
-            }
-            return;
-        }
-        float v[QS_BLKS][QS_RPL];
+        const int64_t kb0 = ((int64_t)bx * 4 + (threadIdx.x >> 6)) * QS_BLKS;
+        float v[QS_BLKS][RPL];
 #pragma unroll
         for (int i = 0; i < QS_BLKS; ++i)
 #pragma unroll
-            for (int q = 0; q < QS_RPL; ++q) {
+            for (int q = 0; q < RPL; ++q) {
                 const int64_t r = (kb0 + i) * br + 64 * q + lane;
                 v[i][q] = (64 * q < br && r < kc) ? (float)Aj[r] : 0.0f;
             }
@@ -214,16 +207,56 @@ struct QuantizeScaled {
         for (int i = 0; i < QS_BLKS; ++i) {
             float amax = 0.0f;
 #pragma unroll
-            for (int q = 0; q < QS_RPL; ++q) amax = fmaxf(amax, fabsf(v[i][q]));
+            for (int q = 0; q < RPL; ++q) amax = fmaxf(amax, fabsf(v[i][q]));
             const int64_t r0 = (kb0 + i) * br;
-            const float scale = scale_of(wave_max(amax));
+            const float scale = block_scale<OP>(wave_max(amax));
             if (r0 < ldk && lane == 0) a.sc[(kb0 + i) * n + j] = scale;
 #pragma unroll
-            for (int q = 0; q < QS_RPL; ++q) {
+            for (int q = 0; q < RPL; ++q) {
                 const int64_t r = r0 + 64 * q + lane;
-                if (64 * q < br && r < ldk) Qj[r] = to_op<OP>((r < kc && scale != 0.0f) ? v[i][q] / scale : 0.0f);
+                if (64 * q < br && r < ldk) Qj[r] = scaled_op<OP>(v[i][q], scale);
             }
         }
+    }
+};
+
+// Longer blocks, and sketches with too few blocks to fill the machine: a
+// work-group per block, its rows in registers up to 1024, else read twice.
+template <int OP>
+struct QuantizeBlock {
+    typedef QuantArgs Args;
+    static constexpr int NTH = 256, WPE = 0;
+    static __device__ void run(const Args& a, int bx, int by)
+    {
+        __shared__ float red[4];
+        const int64_t kc = a.kc, ldk = a.ldk, br = a.br, j = by, r0 = bx * br;
+        const double* __restrict__ Aj = a.A + a.k0 + j * a.lda;
+        typename Op<OP>::T* __restrict__ Qj = (typename Op<OP>::T*)a.Aq + j * ldk;
+        const int tid = threadIdx.x;
+        const bool held = br <= 1024;
+        float v[4], amax = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t k = tid + 256 * q, r = r0 + k;
+            v[q] = (k < br && r < kc) ? (float)Aj[r] : 0.0f;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) amax = fmaxf(amax, fabsf(v[q]));
+        if (!held)
+            for (int64_t r = r0 + 1024 + tid; r < r0 + br && r < kc; r += NTH) amax = fmaxf(amax, fabsf((float)Aj[r]));
+        amax = wave_max(amax);
+        if ((tid & 63) == 0) red[tid >> 6] = amax;
+        __syncthreads();
+        const float scale = block_scale<OP>(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+        if (tid == 0) a.sc[bx * a.n + j] = scale;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t k = tid + 256 * q, r = r0 + k;
+            if (k < br && r < ldk) Qj[r] = scaled_op<OP>(v[q], scale);
+        }
+        if (!held)
+            for (int64_t r = r0 + 1024 + tid; r < r0 + br && r < ldk; r += NTH)
+                Qj[r] = scaled_op<OP>(r < kc ? (float)Aj[r] : 0.0f, scale);
     }
 };
 
@@ -631,10 +664,22 @@ static void wide_tile(int64_t s, int64_t n, int op, int64_t maxsplit, int* wm, i
         if (op != OPK_F32) return;
     }
 }
-// Scale blocks that hold whole K tiles (128 bytes per row) of the wide kernel.
-static bool wide_scaled(int op, int64_t br)
+// Split count of the narrow product: tiles x splits fill the machine.
+static int64_t narrow_splits(int64_t s, int64_t n, int64_t maxsplit)
 {
-    return (op == OPK_FP8 || op == OPK_F16) && br % (128 / opk_bytes(op)) == 0;
+    const int64_t want = ceil_div(1024, ceil_div(s, LP_BM) * ceil_div(n, LP_BN));   // (FP64 tiles are as large)
+    return want < maxsplit ? want : maxsplit;
+}
+// Scaled sketches for the wide kernel: blocks that hold whole K tiles (128 bytes
+// per row).  Not FP16 where the splits are longer than 1024 rows (a split holds four
+// blocks) and do not fill the machine even in the narrow product's tiles,
+// whose K steps then take less time: 20,000 x 200 in blocks of 1024 to FP16 78
+// us, wide 86; of 256 34 and 34; 20,000 x 1000 in blocks of 1024 315 and 212.
+static bool wide_scaled(int64_t s, int64_t n, int op, int64_t br, int64_t maxsplit)
+{
+    if ((op != OPK_FP8 && op != OPK_F16) || br % (128 / opk_bytes(op)) != 0) return false;
+    return op == OPK_FP8 || br <= 256 ||
+           ceil_div(s, LP_BM) * ceil_div(n, LP_BN) * narrow_splits(s, n, maxsplit) >= 256;
 }
 template <int OP>
 static void wide_launch(Exec& ex, const SketchPlan& p, int64_t s, int64_t n, const GemmLpArgs& a)
@@ -670,31 +715,20 @@ SketchPlan plan_sketch(int64_t m, int64_t n, int64_t s, int prec, int64_t br, in
         if (kc > p.ldk) kc = p.ldk;
         p.kchunk = kc;
         p.splits = ceil_div(p.ldk, kc);
-    } else if (op == OPK_BF16 || op == OPK_F32) {
-        int64_t maxsplit = p.ldk / (4 * align);
-        if (maxsplit < 1) maxsplit = 1;
-        wide_tile(s, n, op, maxsplit, &p.wm, &p.wn, &p.splits);
-        p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
-        p.splits = ceil_div(p.ldk, p.kchunk);
-    } else if (wide_scaled(op, br) && !narrow) {
-        // the same with 128 x 256 tiles
-        int64_t maxsplit = p.ldk / (4 * align);
-        if (maxsplit < 1) maxsplit = 1;
-        p.wm = 4;
-        p.wn = 4;
-        const int64_t want = 256 / (ceil_div(s, 128) * ceil_div(n, 256));
-        p.splits = want < 1 ? 1 : (want < maxsplit ? want : maxsplit);
-        p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
-        p.splits = ceil_div(p.ldk, p.kchunk);
     } else {
-        // split-K so that tiles x splits fills the machine
-        int64_t tiles = ceil_div(s, LP_BM) * ceil_div(n, LP_BN);
-        if (op == OPK_F64) tiles = ceil_div(s, 128) * ceil_div(n, 128);
-        int64_t want = ceil_div(1024, tiles);
         int64_t maxsplit = p.ldk / (4 * align);
         if (maxsplit < 1) maxsplit = 1;
-        p.splits = want < maxsplit ? want : maxsplit;
-        if (p.splits < 1) p.splits = 1;
+        if (op == OPK_BF16 || op == OPK_F32) {
+            wide_tile(s, n, op, maxsplit, &p.wm, &p.wn, &p.splits);
+        } else if (wide_scaled(s, n, op, br, maxsplit) && !narrow) {
+            // the same with 128 x 256 tiles
+            p.wm = 4;
+            p.wn = 4;
+            const int64_t want = 256 / (ceil_div(s, 128) * ceil_div(n, 256));
+            p.splits = want < 1 ? 1 : (want < maxsplit ? want : maxsplit);
+        } else {
+            p.splits = narrow_splits(s, n, maxsplit);
+        }
         p.kchunk = ceil_div(ceil_div(p.ldk, p.splits), align) * align;
         p.splits = ceil_div(p.ldk, p.kchunk);
     }
@@ -769,7 +803,16 @@ static void launch_chunk(Exec& ex, const SketchPlan& p, const double* A, int64_t
     } else {
         if constexpr (SC) {
             const QuantArgs q{A, lda, k0, kc, p.ldk, br, n, Aq, sc};
-            launch<QuantizeScaled<OP>>(ex, ceil_div(ceil_div(p.ldk, br), QuantizeScaled<OP>::BLKS), n, q);
+            // QuantizeScaled's work-groups: four to a CU and more, or those of a
+            // whole batch (2000 x 30 in blocks of 128 rows 5.3 and 2.3 us with a
+            // work-group per block, 20,000 x 200 13.6 and 23.6 us), and blocks of
+            // up to 384 rows (400,000 x 500 in blocks of 320 0.62 ms, 0.69 with a
+            // work-group per block, of 512 0.57 and 0.48)
+            const int64_t blocks = ceil_div(p.ldk, br), wgs = ceil_div(blocks, 4 * QS_BLKS);
+            const bool many = wgs * n >= 1024 || ex.recording();
+            if (many && br <= 256) launch<QuantizeScaled<OP, 4>>(ex, wgs, n, q);
+            else if (many && br <= 384) launch<QuantizeScaled<OP, 8>>(ex, wgs, n, q);
+            else launch<QuantizeBlock<OP>>(ex, blocks, n, q);
             if (!ex.recording()) prof_mark(PH_SK_QUANT, ex.st);
         }
         const GemmLpArgs ga{Omq, Aq, p.ldk, s, n, sc, br, (float*)P, p.kchunk, accumulate};
