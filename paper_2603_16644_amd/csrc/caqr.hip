@@ -263,13 +263,13 @@ struct CaqrPanel {
 // stands for the row of register i / 4 of lane group i % 4, so the update adds
 // to W where it was loaded.  Bound by
 // memory: the trailing columns once in and once out, V from L2.
-// The first work-groups factor the next level's panel, which needs the R
-// factors of this one only (NEXT: there is one).
+// The first npan work-groups factor the next level's panel, which needs the R
+// factors of this one only.
 struct CaqrApplyArgs {
     CaqrArgs a, next;
-    int32_t npan;        // blocks of the next level's panel
+    int32_t npan;        // blocks of the next level's panel (0: this is the last)
 };
-template <int Q, bool NEXT>
+template <int Q>
 struct CaqrApply {
     typedef CaqrApplyArgs Args;
     static constexpr int NTH = 512, WPE = 4;
@@ -335,6 +335,7 @@ struct CaqrApply {
             y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(v[1], x[q][1], y1, 0, 0, 0);
             y0 = __builtin_amdgcn_mfma_f64_16x16x4f64(v[2], x[q][2], y0, 0, 0, 0);
             y1 = __builtin_amdgcn_mfma_f64_16x16x4f64(v[3], x[q][3], y1, 0, 0, 0);
+            if (q & 1) __builtin_amdgcn_sched_barrier(0);   // (V of two sets at a time: 128 registers)
         }
         const double* __restrict__ Tm = a.Tm + (int64_t)b * (CW * CW);
         double tk[4];
@@ -356,9 +357,15 @@ struct CaqrApply {
             double v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = p[4 * k * ldv];
+            // (V Z summed by itself: added to W product by product it would be
+            // rounded to W's last place sixteen times instead of once)
+            v4d vz = (v4d){0, 0, 0, 0};
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                x[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[k], z[k], x[q], 0, 0, 0);
+            for (int k = 0; k < 4; ++k) vz = __builtin_amdgcn_mfma_f64_16x16x4f64(v[k], z[k], vz, 0, 0, 0);
+            x[q] += vz;
+            // (added here: moved down to the stores, as the compiler has it,
+            // the sums keep both their terms in registers)
+            asm volatile("" : "+v"(x[q]));
         }
         if (j0 + c >= a.rem) return;
 #pragma unroll
@@ -377,13 +384,11 @@ struct CaqrApply {
     }
     static __device__ __forceinline__ void run(const Args& p, int bx, int)
     {
-        if constexpr (NEXT) {
-            if (bx < p.npan) {
-                caqr_panel<1>(p.next, bx);
-                return;
-            }
-            bx -= p.npan;
+        if (bx < p.npan) {
+            caqr_panel<1>(p.next, bx);
+            return;
         }
+        bx -= p.npan;
         const CaqrArgs& a = p.a;
         // the tiles of a block on one XCD (work-groups go to the eight in
         // turn), whose L2 then holds the block's V (128 KB)
@@ -439,14 +444,6 @@ int64_t caqr_mats(int64_t s)
 
 }  // namespace
 
-// gx work-groups of the level's apply and npan of the next level's panel.
-template <int Q>
-static void caqr_apply_launch(Exec& ex, int64_t gx, const CaqrApplyArgs& p)
-{
-    if (p.npan > 0) launch<CaqrApply<Q, true>>(ex, gx + p.npan, 1, p);
-    else launch<CaqrApply<Q, false>>(ex, gx, 1, p);
-}
-
 size_t caqr_workspace_bytes(int64_t s) { return (size_t)caqr_mats(s) * CW * CW * sizeof(double); }
 
 // R of the s x n matrix W (s >= n), in place: its upper triangle is R, the
@@ -475,8 +472,8 @@ void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double*
             const CaqrApplyArgs p{a[l], a[last ? l : l + 1], last ? 0 : (int32_t)lv[l + 1].nblk};
             const int64_t nb = lv[l].nblk < 8 ? lv[l].nblk : ceil_div(lv[l].nblk, 8) * 8;
             const int64_t gx = nb * ceil_div(a[l].rem, CW);   // (none for the last columns)
-            if (a[l].cb <= 8) caqr_apply_launch<1>(ex, gx, p);
-            else caqr_apply_launch<8>(ex, gx, p);
+            if (a[l].cb <= 8) launch<CaqrApply<1>>(ex, gx + p.npan, 1, p);
+            else launch<CaqrApply<8>>(ex, gx + p.npan, 1, p);
         }
     }
 }

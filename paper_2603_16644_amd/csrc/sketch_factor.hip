@@ -92,6 +92,14 @@ struct SketchEnd {
         const int64_t nblk = (n + TB16 - 1) / TB16;
         return nblk * ((nblk + FILL - 1) / FILL);
     }
+    // the thread's index, formed anew at every use: what is made of it is not
+    // kept in registers across the phases
+    static __device__ __forceinline__ int thread()
+    {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    }
     static __device__ __forceinline__ void fill(const Args& a, int64_t e)
     {
         const int64_t n = a.n, nblk = (n + TB16 - 1) / TB16, np = pack_items(n);
@@ -101,7 +109,7 @@ struct SketchEnd {
             return;
         }
         const int64_t rows = a.s + n, rt = (rows + NTH - 1) / NTH;
-        const int64_t i = (e - np) % rt * NTH + threadIdx.x, j0 = (e - np) / rt * FILL;
+        const int64_t i = (e - np) % rt * NTH + thread(), j0 = (e - np) / rt * FILL;
         if (i >= rows) return;
         for (int64_t j = j0; j < j0 + FILL && j < n; ++j)
             a.X[i + j * a.ldx] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(0x1p-49 * a.gd[j]) : 0.0);
@@ -110,7 +118,7 @@ struct SketchEnd {
     {
         __shared__ double l[T][T + 1], u[T][T + 1];   // l[k][i] of R2, u[j][k] of R1
         const int64_t n = a.n, nt = tiles(n), ti = e % nt, tj = e / nt;
-        const int i = threadIdx.x % T, q = threadIdx.x / T;
+        const int i = thread() % T, q = thread() / T;
         double v[4] = {0, 0, 0, 0};
         auto entry = [&](const double* M, int64_t r, int64_t c) { return r <= c && c < n ? M[r + c * n] : 0.0; };
         if (again) {
@@ -211,7 +219,7 @@ struct SketchEnd {
                 GemmTn<double, false>::run(g, e, 0);
             } else if (phase == 3) {
                 const CholStepArgs p{n, k, a.C, n, nullptr, 0, a.R2, n, a.tab, a.gd, a.t, nullptr, nullptr, nullptr};
-                CholStep<true>::run(p, e, 0);
+                CholStep<true, true>::run(p, e, 0);
             } else {
                 tile(a, e, true);
             }
