@@ -2,13 +2,18 @@
 
 Usage: python -m paper_2603_16644_amd.build  (or call build()).
 Every HIP source is compiled with -O3 for gfx950 only; packed-FP32 VALU
-instructions are disabled.
+instructions are disabled.  The build fails where a kernel spills vector
+registers: a reload from scratch memory waits for every load in flight, which
+the kernels' pipelines are built around, and a version of the Cholesky step
+whose MFMA operands were spilled once returned wrong values (the cause was
+not found).
 """
 from __future__ import annotations
 
 import concurrent.futures as cf
 import glob
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -20,16 +25,34 @@ BUILD_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Wno-unused-function", "-Wno-unused-variable",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-Rpass-analysis=kernel-resource-usage"]
+
+
+def spills(report: str) -> list[tuple[str, int]]:
+    """(kernel, spilled vector registers) of every kernel that has some, from
+    the compiler's kernel-resource-usage remarks."""
+    found, name = [], ""
+    for key, value in re.findall(r"remark: .*?(Function Name|VGPRs Spill): (\S+)", report):
+        if key == "Function Name":
+            name = value
+        elif int(value):
+            found.append((name, int(value)))
+    return found
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
     cmd = [HIPCC, *FLAGS, "-I", os.path.join(HERE, "..", "include"), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
-    err = "\n".join(l for l in (r.stderr or "").splitlines() if "packed-fp32-ops" not in l)
+    report = r.stderr or ""
     if r.returncode != 0:
+        err = "\n".join(l for l in report.splitlines() if "packed-fp32-ops" not in l and "remark:" not in l)
         raise RuntimeError(f"hipcc failed for {src}:\n{err}")
+    bad = spills(report)
+    if bad:
+        os.remove(obj)
+        raise RuntimeError(f"{src}: spilled vector registers: " + ", ".join(f"{k} ({n})" for k, n in bad))
     return obj
 
 

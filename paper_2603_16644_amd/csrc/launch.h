@@ -123,8 +123,10 @@ void grouped_kernel_wpe(const char* __restrict__ table, int count)
     grouped_body<K>(table, count);
 }
 
+// (A wavefront per SIMD fewer than the kernel's other forms: what the loop
+// keeps across the work items does not fit beside their registers.)
 template <class K>
-__global__ __launch_bounds__(K::NTH) __attribute__((amdgpu_waves_per_eu(K::WPE, K::WPE)))
+__global__ __launch_bounds__(K::NTH) __attribute__((amdgpu_waves_per_eu(K::WPE - 1, K::WPE - 1)))
 void persistent_kernel_wpe(const char* __restrict__ table, int count, int32_t total)
 {
     persistent_body<K>(table, count, total);
@@ -155,7 +157,7 @@ typedef void (*GroupLaunchFn)(const char* dtable, int count, int64_t total_wgs, 
 template <class K>
 void group_launch(const char* dtable, int count, int64_t total_wgs, hipStream_t st, int persistent)
 {
-    if constexpr (K::WPE > 0 && can_persist<K>::value) {
+    if constexpr (K::WPE > 1 && can_persist<K>::value) {
         const int64_t g = persistent ? persistent_grid<K>() : 0;
         if (g > 0 && g < total_wgs) {
             persistent_kernel_wpe<K><<<dim3((uint32_t)g), K::NTH, 0, st>>>(dtable, count, (int32_t)total_wgs);
