@@ -277,7 +277,9 @@ void pne_batch_plan_destroy(pne_batch_plan plan);
  * executions, HIP events on `stream`): the row chunk of the split-K products
  * of a batch (4096, 8192, 16384), the output tile of the short-K products
  * (64 or 128) and the largest order of the Gram products that use 64 x 64
- * tiles (512 or 1024).  The fastest is written to *result and, when the
+ * tiles (512 or 1024), and persistent launches or not.  A candidate that
+ * launches what an earlier one did is not timed again.  The fastest is
+ * written to *result and, when the
  * environment variable PNE_TUNE_CACHE names a file, stored there (JSON)
  * under a key of (solver, sketch and QR precision options, power-of-two
  * buckets of the member count, mean n and mean m); pne_batched_workspace_size,
@@ -292,8 +294,9 @@ typedef struct {
     int32_t lower_small_n;
     double ms;        /* median time of one execution with these parameters */
     int32_t stored;   /* 1 if written to the cache file */
-    int32_t persistent; /* 1: the grouped MFMA products run as persistent
-                           launches (work-groups taking tiles from a counter) */
+    int32_t persistent; /* 1: the grouped LU updates, Gram products in 128 x 128
+                           tiles and FP64 sketches run as persistent launches
+                           (work-groups taking tiles from a counter) */
 } pne_tune_result;
 size_t pne_autotune_batched_workspace_size(int64_t batch, const pne_problem_desc* hdesc, const pne_opts* opts,
                                            int hpne);

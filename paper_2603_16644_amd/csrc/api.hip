@@ -4,6 +4,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "common.h"
@@ -578,6 +579,7 @@ struct pne_batch_plan_s {
     std::vector<pne::LaunchGroup> ce_groups;    // condition estimate (AUTO)
     std::vector<pne::LaunchGroup> main_groups;  // the solves
     pne::TuneParams tune;
+    uint64_t launches = 0;   // hash of the launch sequence, its arguments and which of it is persistent
     bool rerun_ce = false;   // some member takes its sketch from the estimate
     hipGraphExec_t gexec = nullptr;
     ~pne_batch_plan_s()
@@ -587,6 +589,23 @@ struct pne_batch_plan_s {
 };
 
 namespace {
+
+// FNV-1a hash of a launch sequence under the tuned parameters in force.
+uint64_t launch_hash(const GroupSeq& s, uint64_t h)
+{
+    auto add = [&](const void* p, size_t n) {
+        for (size_t i = 0; i < n; ++i) h = (h ^ ((const unsigned char*)p)[i]) * 1099511628211ull;
+    };
+    add(s.blob.data(), s.blob.size());
+    for (const LaunchGroup& g : s.groups) {
+        const bool persistent = g.fn(nullptr, g.count, g.total, nullptr, tune_params().persistent);
+        add(&g.fn, sizeof g.fn);
+        add(&g.off, sizeof g.off);
+        add(&g.total, sizeof g.total);
+        add(&persistent, sizeof persistent);
+    }
+    return h;
+}
 
 // Builds a plan: records, groups and uploads the launch sequence (one wait
 // for the upload; with AUTO the estimate runs once and its picks are read
@@ -644,6 +663,7 @@ pne_status plan_create(int64_t batch, const pne_problem_desc* hd, const double* 
     plan->main_groups = mainseq.groups;
     for (LaunchGroup& g : plan->main_groups) g.off += toff;
     plan->tune = tp;
+    plan->launches = launch_hash(ce, launch_hash(mainseq, 1469598103934665603ull));
     for (int64_t i = 0; i < batch; ++i)
         if (sketch_from_condest(L.prob[i], o, sk[i], qr[i])) plan->rerun_ce = true;
     *out = plan;
@@ -1000,8 +1020,9 @@ pne_status pne_batch_plan_execute_graph(pne_batch_plan plan, pne_stream_t stream
 void pne_batch_plan_destroy(pne_batch_plan plan) { delete plan; }
 
 // Candidate settings of the autotuner: the batch row chunk, the tile of the
-// short-K products (A R^-1, factor updates) and the order up to which
-// lower-triangle long-K products (the Gram matrices) use 64 x 64 tiles.
+// short-K products (LU updates, Gram products of less than 4096 rows), the order
+// up to which lower-triangle long-K products (the Gram matrices) use 64 x 64 tiles,
+// and persistent launches of the products that have them (gemm.hip).
 static std::vector<TuneParams> tune_candidates()
 {
     std::vector<TuneParams> c;
@@ -1050,11 +1071,19 @@ pne_status pne_autotune_batched(int64_t batch, const pne_problem_desc* hdesc, co
     TuneParams best;
     double best_ms = -1.0;
     pne_status rc = PNE_OK;
+    std::vector<uint64_t> timed;
     for (const TuneParams& p : tune_candidates()) {
         pne_batch_plan_s* plan = nullptr;
         rc = plan_create(batch, hdesc, dA_base, db_base, dx_base, o, hpne, dwork, work_bytes, dinfo, st, p, &plan);
         if (rc == PNE_EWORKSPACE) { rc = PNE_OK; continue; }   // needs more than the caller gave
         if (rc) break;
+        // a candidate that launches what an earlier one did is that one (timed
+        // again, it would be picked by noise)
+        if (std::find(timed.begin(), timed.end(), plan->launches) != timed.end()) {
+            delete plan;
+            continue;
+        }
+        timed.push_back(plan->launches);
         // one warm-up execution, then the median of three timed ones
         rc = plan_execute(plan, st, plan->rerun_ce);
         double t[3] = {0, 0, 0};

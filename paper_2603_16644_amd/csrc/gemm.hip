@@ -705,7 +705,8 @@ void plan_splitk_gram(int64_t K, int64_t n, int lower, int64_t kchunk_fixed, int
 template <typename TC>
 static void gemm_reduce_launch(Exec& ex, const GemmArgs& g)
 {
-    const TileShape ts = tile_shape(g.M, g.N, g.K, g.lower);
+    // (the tile tells diagonal from other tiles where the two are split apart)
+    const TileShape ts = g.splits_diag > 0 ? tile_shape(g.M, g.N, g.K, g.lower) : TileShape{1, 1};
     int64_t cnt = g.M * g.N;
     if (g.bvec && g.M > cnt) cnt = g.M;
     // (FP32, the condition estimate's Gram matrix: the order of one thread)

@@ -152,20 +152,24 @@ int64_t persistent_grid()
     return g;
 }
 
-typedef void (*GroupLaunchFn)(const char* dtable, int count, int64_t total_wgs, hipStream_t st, int persistent);
+// Enqueues a grouped launch; returns whether as a persistent one.  Without a
+// table it launches nothing and only answers.
+typedef bool (*GroupLaunchFn)(const char* dtable, int count, int64_t total_wgs, hipStream_t st, int persistent);
 
 template <class K>
-void group_launch(const char* dtable, int count, int64_t total_wgs, hipStream_t st, int persistent)
+bool group_launch(const char* dtable, int count, int64_t total_wgs, hipStream_t st, int persistent)
 {
     if constexpr (K::WPE > 1 && can_persist<K>::value) {
         const int64_t g = persistent ? persistent_grid<K>() : 0;
         if (g > 0 && g < total_wgs) {
-            persistent_kernel_wpe<K><<<dim3((uint32_t)g), K::NTH, 0, st>>>(dtable, count, (int32_t)total_wgs);
-            return;
+            if (dtable) persistent_kernel_wpe<K><<<dim3((uint32_t)g), K::NTH, 0, st>>>(dtable, count, (int32_t)total_wgs);
+            return true;
         }
     }
+    if (!dtable) return false;
     if constexpr (K::WPE > 0) grouped_kernel_wpe<K><<<dim3((uint32_t)total_wgs), K::NTH, 0, st>>>(dtable, count);
     else grouped_kernel<K><<<dim3((uint32_t)total_wgs), K::NTH, 0, st>>>(dtable, count);
+    return false;
 }
 
 struct LaunchRec {

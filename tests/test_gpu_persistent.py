@@ -61,3 +61,17 @@ def test_persistent_products(pne, tmp_path, monkeypatch, hpne, sk, qr, codes):
                 assert torch.equal(x, out[pe])
         plan.close()
     assert torch.equal(out[0], out[1])
+
+
+def test_autotuner_times_equal_launches_once(pne, tmp_path, monkeypatch):
+    """Orders up to 512 and 4096 rows and more, PNE: the tile and persistent
+    settings reach none of the launches, so the tuner leaves them at their
+    defaults instead of picking among equals."""
+    shapes = [(4200 + 301 * i, 40 + 23 * i) for i in range(8)]
+    probs = [make_problem(m, n, 1e3, 1e-6, seed=1300 + i) for i, (m, n) in enumerate(shapes)]
+    A, b, x, descs = pack_batch(probs, "cuda")
+    monkeypatch.setenv("PNE_TUNE_CACHE", str(tmp_path / "tune.json"))
+    o = pne.make_opts(seed=3, sketch_prec="bf16", qr_prec="fp32", refine_steps=1)
+    for _ in range(3):
+        res = pne.autotune_batched(A, b, x, descs, opts=o)
+        assert (res["shortk_tile"], res["lower_small_n"], res["persistent"]) == (64, 512, False)
