@@ -102,18 +102,4 @@ void enqueue_groups(const std::vector<LaunchGroup>& groups, const char* dtables,
     }
 }
 
-int run_recorded(const Recorder& rec, char* dtables, size_t cap, hipStream_t st)
-{
-    GroupSeq seq;
-    int rc = build_groups(rec, &seq);
-    if (rc) return rc;
-    if (seq.blob.empty()) return PNE_OK;
-    if (seq.blob.size() > cap || !dtables) return PNE_EWORKSPACE;
-    // the host blob is released on return: wait for the copy
-    HIP_OK(hipMemcpyAsync(dtables, seq.blob.data(), seq.blob.size(), hipMemcpyHostToDevice, st));
-    HIP_OK(hipStreamSynchronize(st));
-    enqueue_groups(seq.groups, dtables, st, true);
-    return hipGetLastError() == hipSuccess ? PNE_OK : PNE_EHIP;
-}
-
 }  // namespace pne

@@ -14,20 +14,25 @@
 // Everything runs on the FP64 MFMA 16x16x4 in its accumulator layout: lane
 // (r, g) (r = lane % 16, g = lane / 16) holds row r, register q of a
 // 16-column block holds column g + 4 q, and that register is at once the
-// MFMA's operand for the K values 4 q + g (on either side).  The diagonal
-// block is factored by one wavefront, four columns a step, with no LDS and no
-// barrier: the 4 x 4 pivot block goes to every lane by readlane, each lane
-// factors and inverts it, one MFMA per 16 rows applies the inverse, one MFMA
-// per 16 x 16 block updates the rest.  The operands it used are exactly the
-// table a panel substitution needs (tab: per block column 16 groups of the
-// 4 x 4 inverse and its update, then the 6 blocks below the diagonal, negated).
+// MFMA's operand for the K values 4 q + g (on either side).  In the diagonal
+// block wavefront w holds rows 16 w ..: for each block c of 16 columns
+// wavefront c factors its 16 x 16 diagonal block, four columns a step (the 4 x
+// 4 pivot block goes to every lane by readlane, each lane factors and inverts
+// it, one MFMA applies the inverse and one updates the rest), and leaves the
+// operands that it used in LDS (tab); after a barrier the wavefronts below
+// substitute their block with them and leave it in LDS (xj), and after another
+// they update what is right of it.  (One wavefront for all 64 rows, without
+// LDS or barriers, took 30 us per block for 19.)  The operands are exactly the
+// table that a panel substitution needs (tab in memory: per block column 16
+// groups of the 4 x 4 inverse and its update, then the 6 blocks below the
+// diagonal, negated).
 //
 // Bound: latency, 19 us per block column (launch 4, loads 2, panels and update
 // 5, factor 8).  Measured with the block inverses, against the factor and
 // inverse by one work-group, panel product and trailing product in launches
 // of their own: n = 64 94 -> 41 us, 100 171 -> 60 us, 257 395 -> 129 us, 1000 1.25
 // -> 0.37 ms, 2000 2.36 -> 0.80 ms.  (WPE 1: with 256 registers the kernel
-// spills, and a spilled MFMA operand tuple came back wrong.)
+// spills.)
 //
 // A non-positive or non-finite pivot at global column k sets *info to
 // 2000 + k + 1 (first failure only) and the factor continues as NaN.  With

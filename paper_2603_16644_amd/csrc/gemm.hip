@@ -264,106 +264,76 @@ __device__ void GemmCm<TA, TB, TC, BM, BN, PARTIAL>::run(const GemmArgs& g, int 
         role = __builtin_amdgcn_readfirstlane(role);   // (uniform per wavefront)
     }
 
-    // Fast path (FP64 operands, full tile off the diagonal of a lower-
-    // triangle product, 16-byte aligned vector loads, a K range of at least
-    // two whole tiles): no bounds checks, and every step of the steady state
-    // is one basic block holding the LDS stores of the next K tile, the
-    // global loads of the one after it and the MFMAs of the current one, so
-    // that the scheduler can interleave them and the MFMA pipe keeps running
-    // while they issue.  64 x 64 tiles only: on products of 100,000 rows it
-    // raised the MFMA busy share from 57 % to 64 %, while the 128 x 128
-    // tiles of the Gram product ran slower with it (61 % against 64 %).
+    // Fast path (FP64 64 x 64 tiles of a product A B that is not split: the LU
+    // updates), for full tiles off the diagonal of a lower-triangle product,
+    // 16-byte aligned vector loads and a K range of at least two whole tiles:
+    // no bounds checks, and every step of the steady state is one basic block
+    // holding the LDS stores of the next K tile, the global loads of the one
+    // after it and the MFMAs of the current one, so that the scheduler can
+    // interleave them and the MFMA pipe keeps running while they issue.  (On
+    // products of 100,000 rows it raised the MFMA busy share from 57 % to 64 %,
+    // while the 128 x 128 tiles of the Gram product ran slower with it, 61 %
+    // against 64 %.)
+    constexpr bool FAST = sizeof(TA) == 8 && sizeof(TB) == 8 && sizeof(TC) == 8 && BM == 64 && !PARTIAL;
     bool fast = false;
-    if constexpr (sizeof(TA) == 8 && sizeof(TB) == 8 && sizeof(TC) == 8 && BM == 64)
-        fast = vecA && vecB && i0 + BM <= g.M && j0 + BN <= g.N && ((kend - kbeg) % G_BK) == 0 &&
-               kend - kbeg >= 2 * G_BK && !(g.lower && ti == tj);
-    if constexpr (sizeof(TA) == 8 && sizeof(TB) == 8 && sizeof(TC) == 8 && BM == 64) {
+    if constexpr (FAST)
+        fast = !g.transA && !g.transB && !fold && vecA && vecB && i0 + BM <= g.M && j0 + BN <= g.N &&
+               ((kend - kbeg) % G_BK) == 0 && kend - kbeg >= 2 * G_BK && !(g.lower && ti == tj);
+    if constexpr (FAST) {
       if (fast) {
-        // the transposition flags as compile-time constants (one copy of the
-        // loop per combination), so that no branch splits a step
-        auto run_fast = [&](auto tra, auto trb) {
-            constexpr bool TRA = decltype(tra)::value, TRB = decltype(trb)::value;
-            double2 va[APT / 2], vb[BPT / 2];
-            auto gload_fast = [&](int64_t k0) {
-                const TA* pa;
-                if constexpr (!TRA) pa = A + (i0 + (tid & 15) * APT) + (k0 + (tid >> 4)) * g.lda;
-                else pa = A + (k0 + (tid % TPR) * APT) + (i0 + tid / TPR) * g.lda;
+        double2 va[APT / 2], vb[BPT / 2];
+        auto gload_fast = [&](int64_t k0) {
+            const TA* pa = A + (i0 + (tid & 15) * APT) + (k0 + (tid >> 4)) * g.lda;
 #pragma unroll
-                for (int q = 0; q < APT / 2; ++q) va[q] = *(const double2*)(pa + 2 * q);
-                const TB* pb;
-                if constexpr (!TRB) pb = B + (k0 + (tid % (256 / BN)) * BPT) + (j0 + tid / (256 / BN)) * g.ldb;
-                else pb = B + (j0 + (tid & 15) * BPT) + (k0 + (tid >> 4)) * g.ldb;
+            for (int q = 0; q < APT / 2; ++q) va[q] = *(const double2*)(pa + 2 * q);
+            const TB* pb = B + (k0 + (tid % (256 / BN)) * BPT) + (j0 + tid / (256 / BN)) * g.ldb;
 #pragma unroll
-                for (int q = 0; q < BPT / 2; ++q) vb[q] = *(const double2*)(pb + 2 * q);
-            };
-            auto sstore_fast = [&](int b) {
-                TC* as = As[b];
-                TC* bs = Bs[b];
-#pragma unroll
-                for (int q = 0; q < APT; ++q) {
-                    const TC v = (q & 1) ? va[q / 2].y : va[q / 2].x;
-                    if constexpr (!TRA) as[(tid >> 4) * LDA_S + (tid & 15) * APT + q] = v;
-                    else as[((tid % TPR) * APT + q) * LDA_S + tid / TPR] = v;
-                }
-#pragma unroll
-                for (int q = 0; q < BPT; ++q) {
-                    const TC v = (q & 1) ? vb[q / 2].y : vb[q / 2].x;
-                    if constexpr (!TRB) bs[((tid % (256 / BN)) * BPT + q) * LDB_S + tid / (256 / BN)] = v;
-                    else bs[(tid >> 4) * LDB_S + (tid & 15) * BPT + q] = v;
-                }
-            };
-            auto compute = [&](int b) {
-                const TC* as = As[b];
-                const TC* bs = Bs[b];
-#pragma unroll
-                for (int kk = 0; kk < G_BK; kk += 4) {
-                    TC fa[TM], fb[TN];
-#pragma unroll
-                    for (int t = 0; t < TM; ++t) fa[t] = as[(kk + g4) * LDA_S + wm * (BM / 2) + t * 16 + r16];
-#pragma unroll
-                    for (int t = 0; t < TN; ++t) fb[t] = bs[(kk + g4) * LDB_S + wn * (BN / 2) + t * 16 + r16];
-#pragma unroll
-                    for (int a = 0; a < TM; ++a)
-#pragma unroll
-                        for (int b2 = 0; b2 < TN; ++b2) acc[a][b2] = mfma_cm<TC>(fb[b2], fa[a], acc[a][b2]);
-                }
-            };
-            // op(A) b for the folding work-groups, b read directly (uniform
-            // addresses: scalar loads)
-            auto fold_step = [&](int b, int64_t k0) {
-                if (fold && tid < BM) {
-#pragma unroll
-                    for (int kk = 0; kk < G_BK; ++kk) cpart += As[b][kk * LDA_S + tid] * (TC)bv[k0 + kk];
-                }
-            };
-            const int64_t nk = (kend - kbeg) / G_BK;
-            gload_fast(kbeg);
-            sstore_fast(0);
-            gload_fast(kbeg + G_BK);
-            int b = 0;
-            for (int64_t t = 0; t + 2 < nk; ++t) {
-                __syncthreads();
-                fold_step(b, kbeg + t * G_BK);
-                sstore_fast(b ^ 1);                     // tile t + 1
-                gload_fast(kbeg + (t + 2) * G_BK);      // tile t + 2
-                compute(b);                             // tile t
-                b ^= 1;
-            }
-            __syncthreads();
-            fold_step(b, kend - 2 * G_BK);
-            sstore_fast(b ^ 1);
-            compute(b);
-            b ^= 1;
-            __syncthreads();
-            fold_step(b, kend - G_BK);
-            compute(b);
+            for (int q = 0; q < BPT / 2; ++q) vb[q] = *(const double2*)(pb + 2 * q);
         };
-        using F = std::false_type;
-        using T_ = std::true_type;
-        if (!g.transA && !g.transB) run_fast(F{}, F{});
-        else if (!g.transA) run_fast(F{}, T_{});
-        else if (!g.transB) run_fast(T_{}, F{});
-        else run_fast(T_{}, T_{});
+        auto sstore_fast = [&](int b) {
+            TC* as = As[b];
+            TC* bs = Bs[b];
+#pragma unroll
+            for (int q = 0; q < APT; ++q)
+                as[(tid >> 4) * LDA_S + (tid & 15) * APT + q] = (q & 1) ? va[q / 2].y : va[q / 2].x;
+#pragma unroll
+            for (int q = 0; q < BPT; ++q)
+                bs[((tid % (256 / BN)) * BPT + q) * LDB_S + tid / (256 / BN)] = (q & 1) ? vb[q / 2].y : vb[q / 2].x;
+        };
+        auto compute = [&](int b) {
+            const TC* as = As[b];
+            const TC* bs = Bs[b];
+#pragma unroll
+            for (int kk = 0; kk < G_BK; kk += 4) {
+                TC fa[TM], fb[TN];
+#pragma unroll
+                for (int t = 0; t < TM; ++t) fa[t] = as[(kk + g4) * LDA_S + wm * (BM / 2) + t * 16 + r16];
+#pragma unroll
+                for (int t = 0; t < TN; ++t) fb[t] = bs[(kk + g4) * LDB_S + wn * (BN / 2) + t * 16 + r16];
+#pragma unroll
+                for (int a = 0; a < TM; ++a)
+#pragma unroll
+                    for (int b2 = 0; b2 < TN; ++b2) acc[a][b2] = mfma_cm<TC>(fb[b2], fa[a], acc[a][b2]);
+            }
+        };
+        const int64_t nk = (kend - kbeg) / G_BK;
+        gload_fast(kbeg);
+        sstore_fast(0);
+        gload_fast(kbeg + G_BK);
+        int b = 0;
+        for (int64_t t = 0; t + 2 < nk; ++t) {
+            __syncthreads();
+            sstore_fast(b ^ 1);                     // tile t + 1
+            gload_fast(kbeg + (t + 2) * G_BK);      // tile t + 2
+            compute(b);                             // tile t
+            b ^= 1;
+        }
+        __syncthreads();
+        sstore_fast(b ^ 1);
+        compute(b);
+        b ^= 1;
+        __syncthreads();
+        compute(b);
       }
     }
 
@@ -720,25 +690,33 @@ static void gemm_reduce_launch(Exec& ex, const GemmArgs& g)
 template <typename TA, typename TB, typename TC, bool PARTIAL>
 static void gemm_tiles_launch(Exec& ex, const TileShape& ts, int64_t gx, int64_t gy, const GemmArgs& g)
 {
-    if (ts.bm == 64) launch<GemmCm<TA, TB, TC, 64, 64, PARTIAL>>(ex, gx, gy, g);
-    else if (ts.bn == 64) launch<GemmCm<TA, TB, TC, 128, 64, PARTIAL>>(ex, gx, gy, g);
+    // (FP64 split products in 64 x 64 tiles: gemm_tn.hip)
+    constexpr bool SMALL = !(PARTIAL && sizeof(TC) == 8);
+    if constexpr (SMALL) {
+        if (ts.bm == 64) return launch<GemmCm<TA, TB, TC, 64, 64, PARTIAL>>(ex, gx, gy, g);
+    }
+    if (ts.bn == 64) launch<GemmCm<TA, TB, TC, 128, 64, PARTIAL>>(ex, gx, gy, g);
     else launch<GemmCm<TA, TB, TC, 128, 128, PARTIAL>>(ex, gx, gy, g);
 }
 
 template <typename TA, typename TB, typename TC>
-static void gemm_launch(Exec& ex, const GemmArgs& g0, bool reduce)
+static void gemm_whole(Exec& ex, const GemmArgs& g0)
 {
     GemmArgs g = g0;
+    g.splits = 1;
+    g.xcd_remap = 0;
     const TileShape ts = tile_shape(g.M, g.N, g.K, g.lower);
-    const int64_t tiles = gemm_tiles(g.M, g.N, g.K, g.lower);
-    if (tiles == 0) return;
-    const bool partial = g.splits > 1 || !reduce;
-    if (!partial) {
-        g.splits = 1;
-        g.xcd_remap = 0;
-        gemm_tiles_launch<TA, TB, TC, false>(ex, ts, tiles, 1, g);
-        return;
-    }
+    gemm_tiles_launch<TA, TB, TC, false>(ex, ts, gemm_tiles(g.M, g.N, g.K, g.lower), 1, g);
+}
+
+template <typename TA, typename TB, typename TC>
+static void gemm_partials(Exec& ex, const GemmArgs& g0)
+{
+    GemmArgs g = g0;
+    TileShape ts = tile_shape(g.M, g.N, g.K, g.lower);
+    if (sizeof(TC) == 8 && ts.bm == 64) ts = TileShape{128, 128};   // (nothing comes here; see gemm_tiles_launch)
+    const int64_t tm = ceil_div(g.M, (int64_t)ts.bm), tn = ceil_div(g.N, (int64_t)ts.bn);
+    const int64_t tiles = g.lower ? tm * (tm + 1) / 2 : tm * tn;
     if (g.splits < 1) g.splits = 1;
     if (g.kchunk <= 0) g.kchunk = ceil_div(ceil_div(g.K, g.splits), G_BK) * G_BK;
     // (lower-triangle products only: on the FP64 sketch product, whose
@@ -749,24 +727,29 @@ static void gemm_launch(Exec& ex, const GemmArgs& g0, bool reduce)
     if (g.lower && g.splits_diag > 0) {
         // one-dimensional grid: diagonal tiles x splits_diag, then the tiles
         // below the diagonal x splits
-        const int64_t tm = ceil_div(g.M, (int64_t)ts.bm);
         g.xcd_remap = !ex.recording();
         gemm_tiles_launch<TA, TB, TC, true>(ex, ts, tm * g.splits_diag + (tiles - tm) * g.splits, 1, g);
     } else {
         gemm_tiles_launch<TA, TB, TC, true>(ex, ts, tiles, g.splits, g);
     }
-    if (reduce) gemm_reduce_launch<TC>(ex, g);
 }
 
-void gemm_f64(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, double>(ex, g, true); }
+void gemm_f64(Exec& ex, const GemmArgs& g) { gemm_whole<double, double, double>(ex, g); }
 void gemm_f64_reduce(Exec& ex, const GemmArgs& g) { gemm_reduce_launch<double>(ex, g); }
 void gemm_f64_partials(Exec& ex, const GemmArgs& g)
 {
     if (g.transA && !g.transB && tn_route(g.M, g.N, g.K, g.lower)) gemm_tn_partials(ex, g);
-    else gemm_launch<double, double, double>(ex, g, false);
+    else gemm_partials<double, double, double>(ex, g);
 }
-void gemm_f32(Exec& ex, const GemmArgs& g) { gemm_launch<float, float, float>(ex, g, true); }
-void gemm_f32_partials(Exec& ex, const GemmArgs& g) { gemm_launch<float, float, float>(ex, g, false); }
-void gemm_ddf(Exec& ex, const GemmArgs& g) { gemm_launch<double, double, float>(ex, g, true); }
+void gemm_f32(Exec& ex, const GemmArgs& g) { gemm_whole<float, float, float>(ex, g); }
+void gemm_ddf(Exec& ex, const GemmArgs& g)
+{
+    if (g.splits > 1) {
+        gemm_partials<double, double, float>(ex, g);
+        gemm_reduce_launch<float>(ex, g);
+    } else {
+        gemm_whole<double, double, float>(ex, g);
+    }
+}
 
 }  // namespace pne

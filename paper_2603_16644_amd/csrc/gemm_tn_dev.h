@@ -277,7 +277,7 @@ __device__ __forceinline__ void GemmTn<TI, WIDE>::run(const GemmArgs& g, int bx,
         }
         __syncthreads();
         if (w == 0) take();
-        __syncthreads();   // (a persistent work-group reuses the buffer)
+        __syncthreads();   // (keeps the last sums apart from the stores: mixed by the compiler, they spill 20 registers)
         if (w != 0) return;
     }
 

@@ -84,7 +84,7 @@ struct GemmArgs {
     int diag_roles;   // set by the launcher: split the diagonal tiles' work over all wavefronts
 };
 // element types: d = double, f = float; "ddf" = A, B stored double, computed in float
-void gemm_f64(Exec& ex, const GemmArgs& g);           // full path incl. reduce
+void gemm_f64(Exec& ex, const GemmArgs& g);           // not split over K
 void gemm_f64_partials(Exec& ex, const GemmArgs& g);  // partials only (no reduce)
 void gemm_f64_reduce(Exec& ex, const GemmArgs& g);    // reduce of the partials
 // A^T B in 64 x 64 tiles with the operands loaded straight into registers
@@ -94,7 +94,6 @@ int64_t tn_tiles(int64_t M, int64_t N, int lower);
 void gemm_tn_partials(Exec& ex, const GemmArgs& g);
 bool gemm_tile_is_64(int64_t M, int64_t N, int64_t K, int lower);
 void gemm_f32(Exec& ex, const GemmArgs& g);
-void gemm_f32_partials(Exec& ex, const GemmArgs& g);
 void gemm_ddf(Exec& ex, const GemmArgs& g);           // fl32(A)^T fl32(B) etc.
 // split-K plan: splits and kchunk for a long-K product with `tiles` output
 // tiles (kchunk_fixed > 0: fixed chunk length, for batches)
@@ -227,9 +226,6 @@ int build_groups(const Recorder& rec, GroupSeq* out);
 // Enqueue grouped launches whose tables sit at dtables (kernel launches
 // only; phase marks when `marks`).
 void enqueue_groups(const std::vector<LaunchGroup>& groups, const char* dtables, hipStream_t st, bool marks);
-// build_groups, copy the tables to dtables (cap bytes; one wait for the
-// copy) and enqueue them on st (batched.hip).
-int run_recorded(const Recorder& rec, char* dtables, size_t cap, hipStream_t st);
 
 // ---------------------------------------------------------------- condition estimate
 size_t condest_workspace_bytes(int64_t m, int64_t n, int64_t kchunk_fixed = 0);
