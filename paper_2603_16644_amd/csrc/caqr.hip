@@ -154,10 +154,13 @@ __device__ __forceinline__ void caqr_step(int it, int wv, int g, int c, double (
     const double dot = rk + s * inv;                // v^T x(:, c); for c < k without V's scale
     const double f = c > k ? tau * dot : 0.0;
     const double fi = f * inv;
+    // (not c <= k with f = 0: a column k that is not finite would spread to the
+    // finite ones before it)
+    if (c > k)
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
+        for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[q][t] -= fi * xb[q][t];
+            for (int t = 0; t < 4; ++t) x[q][t] -= fi * xb[q][t];
     if (owner) x[0][J] = c == k ? beta : x[0][J] - f;
     if (w0 && g == 0) {
         if (c < k) sh.G[k][c] = ivc * dot;

@@ -292,3 +292,21 @@ def test_partial_sums(pne, hpne, m, n):
     err = np.abs(C - A.T @ A)
     assert np.all((err if hpne else np.tril(err)) <= 2 * tol * (np.abs(A).T @ np.abs(A)))
     assert np.all(np.abs(c - A.T @ b) <= 2 * tol * (np.abs(A).T @ np.abs(b)))
+
+
+@pytest.mark.parametrize("m", [50, 1100, 9000, 70000])                     # one block to three levels
+@pytest.mark.parametrize("col", [0, 3, 15, 16, 18, 33, 39])
+@pytest.mark.parametrize("bad", [0.0, np.nan, np.inf, -np.inf])
+def test_qr_info_names_the_column(pne, m, col, bad):
+    """A zero column stays exactly zero, and a NaN or infinity in one entry (of
+    the first or the last row) stays in its column and those right of it: the
+    info word is 1000 + that column, whatever the panel and the level."""
+    rng = np.random.default_rng(m + col)
+    b = torch.from_numpy(rng.standard_normal(m)).cuda()
+    for row in (0, m - 1):
+        A = rng.standard_normal((m, 40))
+        A[slice(None) if bad == 0.0 else row, col] = bad
+        x, info = pne.qr_ls_solve(dev(A), b)
+        torch.cuda.synchronize()
+        assert int(info.item()) == 1000 + col + 1
+        assert bool(torch.isnan(x).all())
