@@ -294,6 +294,27 @@ def test_partial_sums(pne, hpne, m, n):
     assert np.all(np.abs(c - A.T @ b) <= 2 * tol * (np.abs(A).T @ np.abs(b)))
 
 
+@pytest.mark.parametrize("s,n", [
+    (305, 100), (1413, 471), (535, 107), (1140, 380), (405, 135), (1432, 716),   # 160 x 128, 192 x 128, 160 x 192
+    (990, 198), (702, 702), (641, 212), (1334, 667)])                            # 256 x 256, 192 x 256
+def test_fp32_sketch_sums(pne, s, n):
+    """FP32 sketches through every tile of the wide product, of a matrix that
+    FP32 holds exactly, against the FP64 sketch of the same Omega: what is left
+    is the rounding of FP32 sums.  Terms of size 1 leave partial sums of size
+    sqrt(k), each rounded with an error uniform in u of it at most: after m of
+    them u m / sqrt(6) root mean square (one chain; less where the sum is
+    split), six times that for the largest of the entries."""
+    m = 20000
+    g = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn(n, m, dtype=torch.float32, device="cuda", generator=g).double().t()
+    got, ref = pne.pne_sketch(A, s, seed=4, prec="fp32"), pne.pne_sketch(A, s, seed=4, prec="fp64")
+    torch.cuda.synchronize()
+    err = (got - ref).abs()
+    rms = 2.0 ** -24 * m / np.sqrt(6 * s)
+    assert float(err.square().mean().sqrt()) <= rms
+    assert float(err.max()) <= 6 * rms
+
+
 @pytest.mark.parametrize("m", [50, 1100, 9000, 70000])                     # one block to three levels
 @pytest.mark.parametrize("col", [0, 3, 15, 16, 18, 33, 39])
 @pytest.mark.parametrize("bad", [0.0, np.nan, np.inf, -np.inf])
