@@ -45,7 +45,7 @@ struct CaqrArgs {
     double* Tm;          // 16 x 16 triangular factor per block
     int64_t rstride;     // rows between two chunks of the level
     int32_t nch, cb;     // chunks of the level, chunks per block
-    int32_t w, top;      // columns of the panel; a level above the first
+    int32_t w, wr, top;  // columns of the panel, those of them that are factored; a level above the first
 };
 
 // DPP move within every row of 16 lanes
@@ -79,7 +79,8 @@ struct CaqrShared {
 // beta)].  Column k is left unscaled; ivc is the scale of the lane's own
 // column.
 template <int J, int Q>
-__device__ __forceinline__ void caqr_step(int it, int wv, int g, int c, double (&x)[Q][4], double& ivc, CaqrShared& sh)
+__device__ __forceinline__ void caqr_step(int it, int wv, int g, int c, int wr, double (&x)[Q][4], double& ivc,
+                                          CaqrShared& sh)
 {
     const int k = 4 * it + J;
     const bool w0 = wv == 0, owner = w0 && g == it;   // (owner: holds row k, as x[0][J])
@@ -148,7 +149,7 @@ __device__ __forceinline__ void caqr_step(int it, int wv, int g, int c, double (
         tau = (beta - alpha) / beta;
         inv = 1.0 / (alpha - beta);
     }
-    if (sigma == 0.0) {
+    if (sigma == 0.0 || k >= wr) {
         beta = alpha; tau = 0.0; inv = 0.0;
     }
     const double dot = rk + s * inv;                // v^T x(:, c); for c < k without V's scale
@@ -203,10 +204,10 @@ __device__ __forceinline__ void caqr_panel(const CaqrArgs& a, int bx)
 #pragma unroll 1
     for (int it = 0; it < 4; ++it) {
         // (columns past w are zero, and so are their reflectors)
-        caqr_step<0, Q>(it, wv, g, col, x, ivc, sh);
-        caqr_step<1, Q>(it, wv, g, col, x, ivc, sh);
-        caqr_step<2, Q>(it, wv, g, col, x, ivc, sh);
-        caqr_step<3, Q>(it, wv, g, col, x, ivc, sh);
+        caqr_step<0, Q>(it, wv, g, col, a.wr, x, ivc, sh);
+        caqr_step<1, Q>(it, wv, g, col, a.wr, x, ivc, sh);
+        caqr_step<2, Q>(it, wv, g, col, a.wr, x, ivc, sh);
+        caqr_step<3, Q>(it, wv, g, col, a.wr, x, ivc, sh);
         col = (col + 4) & 15;
         ivc = row_next4(ivc);
 #pragma unroll
@@ -450,12 +451,14 @@ int64_t caqr_mats(int64_t s)
 size_t caqr_workspace_bytes(int64_t s) { return (size_t)caqr_mats(s) * CW * CW * sizeof(double); }
 
 // R of the s x n matrix W (s >= n), in place: its upper triangle is R, the
-// rest is overwritten.
-void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* work)
+// rest is overwritten.  Only the first nr columns (n or n - 1) are factored: of a
+// right-hand side in column n - 1 rows 0 .. n - 2 of the result are wanted, and
+// its norm may overflow where they do not.
+void caqr_factor(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t ldw, double* work)
 {
-    for (int64_t c0 = 0; c0 < n; c0 += CW) {
+    for (int64_t c0 = 0; c0 < nr; c0 += CW) {
         ex.iter((uint32_t)(c0 / CW));
-        const int w = (int)(n - c0 < CW ? n - c0 : CW);
+        const int w = (int)(n - c0 < CW ? n - c0 : CW), wr = (int)(nr - c0 < CW ? nr - c0 : CW);
         CaqrLevel lv[CMAXLEV];
         const int nl = caqr_levels(s - c0, lv);
         CaqrArgs a[CMAXLEV];
@@ -465,7 +468,7 @@ void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double*
             double* Tm = mem;
             mem += lv[l].nblk * (CW * CW);
             a[l] = CaqrArgs{s - c0, n - c0 - w, W + c0 + c0 * ldw, ldw, mem, Tm, lv[l].rstride,
-                            (int32_t)lv[l].nch, (int32_t)lv[l].cb, w, top};
+                            (int32_t)lv[l].nch, (int32_t)lv[l].cb, w, wr, top};
             mem += (top ? lv[l].nch : lv[l].nblk) * (CW * CW);
         }
         if (a[0].cb <= 8) launch<CaqrPanel<1>>(ex, lv[0].nblk, 1, a[0]);

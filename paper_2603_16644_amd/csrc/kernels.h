@@ -36,7 +36,7 @@ inline int64_t opk_bytes(int op)
 struct SketchPlan {
     int op;
     int64_t chunk, nchunks, ldk, splits, kchunk;
-    int wm, wn;     // wide product tiles of 32 wm x 64 wn (one large unscaled sketch; 0: not)
+    int wm, wn;     // wide product tiles of 32 wm x 64 wn (one large sketch; 0: not)
     size_t bytes;
 };
 // kchunk_fixed > 0: split the product over rows of A in chunks of this
@@ -148,11 +148,12 @@ size_t qr_workspace_bytes(int64_t s, int64_t n, int prec);
 int qr_r(Exec& ex, int64_t s, int64_t n, void* W, int64_t ldw, int prec, double* R, int64_t ldr,
          int32_t* info, void* work, size_t work_bytes);
 bool qr_supported(int64_t s, int prec);
-// FP64, any height (qr_r: up to the heights of qr_supported).
-int qr_f64(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info, void* work,
-           size_t work_bytes);
+// FP64, any height (qr_r: up to the heights of qr_supported); W's last column
+// may be left unfactored (nr = n - 1).
+int qr_f64(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info,
+           void* work, size_t work_bytes);
 size_t caqr_workspace_bytes(int64_t s);
-void caqr_factor(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* work);
+void caqr_factor(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t ldw, double* work);
 // W rounded to BF16 or (scaled; amax one word) FP16; FP32: as it is.
 void qr_round(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, uint32_t* amax);
 // The factor of qr_r up to the signs of its rows, for FP32, BF16 and FP16, from

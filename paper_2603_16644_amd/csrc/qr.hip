@@ -821,15 +821,15 @@ void check_r_diag(Exec& ex, int64_t n, const double* R, int64_t ldr, int32_t* in
 }
 
 // FP64 (any height): the Householder QR of caqr.hip.
-int qr_f64(Exec& ex, int64_t s, int64_t n, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info, void* work,
-           size_t work_bytes)
+int qr_f64(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info,
+           void* work, size_t work_bytes)
 {
     if (work_bytes < caqr_workspace_bytes(s)) return PNE_EWORKSPACE;
     ex.stage(ST_QR);
-    caqr_factor(ex, s, n, W, ldw, (double*)work);
+    caqr_factor(ex, s, n, nr, W, ldw, (double*)work);
     ex.stage(ST_QR_EXTRACT);
     launch<ExtractR<double>>(ex, ceil_div(n * n, 256), 1, ExtractRArgs{n, W, ldw, PNE_PREC_FP64, R, ldr, nullptr, s});
-    launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
+    launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{nr, R, ldr, info});
     return launch_status(ex);
 }
 
@@ -838,7 +838,7 @@ int qr_r(Exec& ex, int64_t s, int64_t n, void* W, int64_t ldw, int prec, double*
 {
     if (work_bytes < qr_workspace_bytes(s, n, prec)) return PNE_EWORKSPACE;
     if (!qr_supported(s, prec)) return PNE_ENOTSUP;
-    if (prec == PNE_PREC_FP64) return qr_f64(ex, s, n, (double*)W, ldw, R, ldr, info, work, work_bytes);
+    if (prec == PNE_PREC_FP64) return qr_f64(ex, s, n, n, (double*)W, ldw, R, ldr, info, work, work_bytes);
     return qr_f32(ex, s, n, (float*)W, ldw, prec, R, ldr, info, work);
 }
 

@@ -2,7 +2,8 @@
 // paper compares PNE/HPNE against (Section 7.4, a QR solver built from
 // geqrf, orgqr and trsm).  Here Q is never formed: the QR of the augmented
 // matrix [A b] yields R and Q^T b together, and
-//   [A b] = Q [R_A  c; 0  rho]   =>   x = R_A^{-1} c,  rho = ||b - A x||.
+//   [A b] = Q [R_A  c; 0  rho]   =>   x = R_A^{-1} c
+// (rho = ||b - A x|| is not formed: b takes A's reflectors and has none).
 // The tall QR is the communication-avoiding FP64 Householder QR of caqr.hip;
 // R_A x = c uses the block-parallel triangular solve.
 #include "common.h"
@@ -40,7 +41,7 @@ int64_t qrls_rows(int64_t m, int64_t n) { return m > n ? m : n + 1; }
 
 struct QrlsBuffers {
     double *W, *R, *DR;
-    int32_t *flags, *linfo;
+    int32_t* flags;
     char* qrws;
 };
 
@@ -53,7 +54,6 @@ size_t qrls_layout(int64_t m, int64_t n, void* base, size_t cap, QrlsBuffers* ou
     b.R = ar.take<double>((size_t)N1 * N1);
     b.DR = ar.take<double>(dinv_elems(n));
     b.flags = ar.take<int32_t>(lb_flag_words(n));
-    b.linfo = ar.take<int32_t>(1);
     b.qrws = ar.take<char>(caqr_workspace_bytes(h));
     if (out) *out = b;
     return ar.used;
@@ -97,9 +97,8 @@ pne_status qr_ls_solve(int64_t m, int64_t n, const double* dA, int64_t lda, cons
     // R of [A b]: R_A = R(0:n, 0:n), c = R(0:n, n)
     const int64_t ldr = n + 1;
     const double* R = b.R;
-    const int rc = qr_f64(ex, h, n + 1, b.W, h, b.R, ldr, b.linfo, b.qrws, caqr_workspace_bytes(h));
+    const int rc = qr_f64(ex, h, n + 1, n, b.W, h, b.R, ldr, dinfo, b.qrws, caqr_workspace_bytes(h));
     if (rc) return (pne_status)rc;
-    check_r_diag(ex, n, R, ldr, dinfo);
     inv_diag64(ex, n, InvTriMat{R, ldr, 0, 0, b.DR, nullptr});
     upper_solve_lb(ex, n, R, ldr, b.DR, R + n * ldr, dx, b.flags, dinfo);
     fill_nan_on_info(ex, n, dx, dinfo);

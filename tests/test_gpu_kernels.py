@@ -331,3 +331,21 @@ def test_qr_info_names_the_column(pne, m, col, bad):
         torch.cuda.synchronize()
         assert int(info.item()) == 1000 + col + 1
         assert bool(torch.isnan(x).all())
+
+
+@pytest.mark.parametrize("m", [50, 1100, 9000, 70000])
+@pytest.mark.parametrize("n", [31, 32, 40])
+def test_qr_large_right_hand_side(pne, m, n):
+    """x is linear in b, bit for bit under powers of two, also where b's norm
+    overflows, and with one large entry."""
+    rng = np.random.default_rng(m + n)
+    A, b = dev(rng.standard_normal((m, n))), torch.from_numpy(rng.standard_normal(m)).cuda()
+    x, info = pne.qr_ls_solve(A, b)
+    big, binfo = pne.qr_ls_solve(A, b * 2.0 ** 900)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0 and int(binfo.item()) == 0
+    assert torch.equal(big * 2.0 ** -900, x)
+    b[m // 3] = 1e300
+    x, info = pne.qr_ls_solve(A, b)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0 and bool(torch.isfinite(x).all())
