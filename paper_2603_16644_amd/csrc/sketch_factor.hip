@@ -114,31 +114,57 @@ struct SketchEnd {
         for (int64_t j = j0; j < j0 + FILL && j < n; ++j)
             a.X[i + j * a.ldx] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(0x1p-49 * a.gd[j]) : 0.0);
     }
-    static __device__ __forceinline__ void tile(const Args& a, int64_t e, bool again)
+    static __device__ __forceinline__ double upper(const double* M, int64_t n, int64_t r, int64_t c)
+    {
+        return r <= c && c < n ? M[r + c * n] : 0.0;
+    }
+    // a tile of R2 R1
+    static __device__ __forceinline__ void tile(const Args& a, int64_t e)
     {
         __shared__ double l[T][T + 1], u[T][T + 1];   // l[k][i] of R2, u[j][k] of R1
         const int64_t n = a.n, nt = tiles(n), ti = e % nt, tj = e / nt;
         const int i = thread() % T, q = thread() / T;
         double v[4] = {0, 0, 0, 0};
-        auto entry = [&](const double* M, int64_t r, int64_t c) { return r <= c && c < n ? M[r + c * n] : 0.0; };
-        if (again) {
-            for (int64_t k0 = T * ti; k0 <= T * tj; k0 += T) {
-                __syncthreads();
+        for (int64_t k0 = T * ti; k0 <= T * tj; k0 += T) {
+            __syncthreads();
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    l[q + 8 * x][i] = entry(a.R2, T * ti + i, k0 + q + 8 * x);
-                    u[q + 8 * x][i] = entry(a.R1, k0 + i, T * tj + q + 8 * x);
-                }
-                __syncthreads();
-#pragma unroll 8
-                for (int k = 0; k < T; ++k)
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) v[x] += l[k][i] * u[q + 8 * x][k];
+            for (int x = 0; x < 4; ++x) {
+                l[q + 8 * x][i] = upper(a.R2, n, T * ti + i, k0 + q + 8 * x);
+                u[q + 8 * x][i] = upper(a.R1, n, k0 + i, T * tj + q + 8 * x);
             }
-        } else {
+            __syncthreads();
+#pragma unroll 8
+            for (int k = 0; k < T; ++k)
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = entry(a.R1, T * ti + i, T * tj + q + 8 * x);
+                for (int x = 0; x < 4; ++x) v[x] += l[k][i] * u[q + 8 * x][k];
         }
+        store(a, ti, tj, v);
+    }
+    // R1 rounded, TILES tiles at a time (one work-group to a CU: with one
+    // tile at a time its loads leave the memory idle: 64 members of a batch 102 us,
+    // now 67)
+    static constexpr int TILES = 4;
+    static __device__ __forceinline__ void copy(const Args& a, int64_t e0, int64_t step)
+    {
+        const int64_t n = a.n, nt = tiles(n);
+        const int i = thread() % T, q = thread() / T;
+        double v[TILES][4];
+#pragma unroll
+        for (int y = 0; y < TILES; ++y) {
+            const int64_t e = e0 + y * step, ti = e % nt, tj = e / nt;   // (columns past n: zero)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[y][x] = upper(a.R1, n, T * ti + i, T * tj + q + 8 * x);
+        }
+#pragma unroll
+        for (int y = 0; y < TILES; ++y) {
+            const int64_t e = e0 + y * step;
+            store(a, e % nt, e / nt, v[y]);
+        }
+    }
+    static __device__ __forceinline__ void store(const Args& a, int64_t ti, int64_t tj, const double (&v)[4])
+    {
+        const int64_t n = a.n;
+        const int i = thread() % T, q = thread() / T;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
             const int64_t r = T * ti + i, c = T * tj + q + 8 * x;
@@ -221,7 +247,7 @@ struct SketchEnd {
                 const CholStepArgs p{n, k, a.C, n, nullptr, 0, a.R2, n, a.tab, a.gd, a.t, nullptr, nullptr, nullptr};
                 CholStep<true, true>::run(p, e, 0);
             } else {
-                tile(a, e, true);
+                tile(a, e);
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             __syncthreads();
@@ -238,7 +264,7 @@ struct SketchEnd {
             return;
         }
         const int64_t nt = tiles(a.n);
-        for (int64_t e = bx; e < nt * nt; e += a.wgs) tile(a, e, false);
+        for (int64_t e = bx; e < nt * nt; e += TILES * (int64_t)a.wgs) copy(a, e, a.wgs);
     }
 };
 
@@ -267,9 +293,10 @@ int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     ex.stage(ST_SKFACTOR_CHOL);
     cholesky64_shifted(ex, n, C, n, R1, n, tab, gd, t, state, work);
     ex.stage(ST_SKFACTOR_END);
-    // one work-group per CU at most (LDS)
+    // one work-group per CU at most (LDS); in a batch as many as the copy of R1 needs
     const int64_t nt = SketchEnd::tiles(n), most = nt * nt > ceil_div(s, 64) ? nt * nt : ceil_div(s, 64);
-    const int32_t wgs = (int32_t)(most < 256 ? most : 256);
+    const int64_t want = ex.recording() ? ceil_div(nt * nt, SketchEnd::TILES) : most;
+    const int32_t wgs = (int32_t)(want < 256 ? want : 256);
     launch<SketchEnd>(ex, wgs, 1, SketchEndArgs{s, n, W, ldw, X, sketch_ld(s, n), pack, R1, P, C, tab, gd, t, state, work,
                                                 R, ldr, prec, amax, wgs, info});
     check_r_diag(ex, n, R, ldr, info);
