@@ -579,7 +579,6 @@ struct pne_batch_plan_s {
     std::vector<pne::LaunchGroup> ce_groups;    // condition estimate (AUTO)
     std::vector<pne::LaunchGroup> main_groups;  // the solves
     pne::TuneParams tune;
-    uint64_t launches = 0;   // hash of the launch sequence, its arguments and which of it is persistent
     bool rerun_ce = false;   // some member takes its sketch from the estimate
     hipGraphExec_t gexec = nullptr;
     ~pne_batch_plan_s()
@@ -609,10 +608,11 @@ uint64_t launch_hash(const GroupSeq& s, uint64_t h)
 
 // Builds a plan: records, groups and uploads the launch sequence (one wait
 // for the upload; with AUTO the estimate runs once and its picks are read
-// back).  Runs under the tuned parameters of the workload.
+// back).  Runs under the tuned parameters of the workload.  launches: the
+// sequence's hash (250 us for 64 members), if asked for.
 pne_status plan_create(int64_t batch, const pne_problem_desc* hd, const double* dA_base, const double* db_base,
                        double* dx_base, const pne_opts* o, int hpne, void* dwork, size_t work_bytes, int32_t* dinfo,
-                       hipStream_t st, const TuneParams& tp, pne_batch_plan_s** out)
+                       hipStream_t st, const TuneParams& tp, pne_batch_plan_s** out, uint64_t* launches = nullptr)
 {
     *out = nullptr;
     pne_status chk = check_batch(batch, hd, o, hpne);
@@ -663,7 +663,7 @@ pne_status plan_create(int64_t batch, const pne_problem_desc* hd, const double* 
     plan->main_groups = mainseq.groups;
     for (LaunchGroup& g : plan->main_groups) g.off += toff;
     plan->tune = tp;
-    plan->launches = launch_hash(ce, launch_hash(mainseq, 1469598103934665603ull));
+    if (launches) *launches = launch_hash(ce, launch_hash(mainseq, 1469598103934665603ull));
     for (int64_t i = 0; i < batch; ++i)
         if (sketch_from_condest(L.prob[i], o, sk[i], qr[i])) plan->rerun_ce = true;
     *out = plan;
@@ -1072,18 +1072,20 @@ pne_status pne_autotune_batched(int64_t batch, const pne_problem_desc* hdesc, co
     double best_ms = -1.0;
     pne_status rc = PNE_OK;
     std::vector<uint64_t> timed;
+    uint64_t launches = 0;
     for (const TuneParams& p : tune_candidates()) {
         pne_batch_plan_s* plan = nullptr;
-        rc = plan_create(batch, hdesc, dA_base, db_base, dx_base, o, hpne, dwork, work_bytes, dinfo, st, p, &plan);
+        rc = plan_create(batch, hdesc, dA_base, db_base, dx_base, o, hpne, dwork, work_bytes, dinfo, st, p, &plan,
+                         &launches);
         if (rc == PNE_EWORKSPACE) { rc = PNE_OK; continue; }   // needs more than the caller gave
         if (rc) break;
         // a candidate that launches what an earlier one did is that one (timed
         // again, it would be picked by noise)
-        if (std::find(timed.begin(), timed.end(), plan->launches) != timed.end()) {
+        if (std::find(timed.begin(), timed.end(), launches) != timed.end()) {
             delete plan;
             continue;
         }
-        timed.push_back(plan->launches);
+        timed.push_back(launches);
         // one warm-up execution, then the median of three timed ones
         rc = plan_execute(plan, st, plan->rerun_ce);
         double t[3] = {0, 0, 0};
