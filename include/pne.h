@@ -31,7 +31,8 @@
  *     Cholesky of the PNE matrix broke down at column k; 3000+k: zero or
  *     non-finite pivot in the LU of the HPNE matrix at column k (k 1-based);
  *     4000+k: a block of the parallel triangular solves gave up waiting for
- *     block k (a scheduling failure; the result is invalid); 5000: A or b
+ *     block k, or (4001) part of the sketch's factor for another (a
+ *     scheduling failure; the result is invalid); 5000: A or b
  *     holds a non-finite entry (only with pne_opts.check_finite, see there).  R_s(k,k) counts
  *     as zero when it is not finite.  On failure x is filled with NaN; no
  *     silent fallback to another precision is taken.
@@ -115,9 +116,12 @@ size_t pne_workspace_size(int64_t m, int64_t n, const pne_opts* opts, int hpne);
  *      from (seed, problem_id, row, column) (Algorithm 1 "Sketch");
  *   3. triangular factor of A_s, R_s promoted to FP64: Householder QR in
  *      FP64 for qr_prec FP64; otherwise A_s and R_s rounded to qr_prec and
- *      the factor between them from the Cholesky factor of the FP64 Gram
- *      matrix A_s^T A_s (the QR factor up to the signs of its rows, which
- *      cancel; a pivot below FP32 roundoff of its column is raised to it);
+ *      the factor between them (the QR factor up to the signs of its rows,
+ *      which cancel) from the Cholesky factor R1 of the FP64 Gram matrix
+ *      A_s^T A_s + 8 n 2^-53 D^2, D = diag of the columns' norms; where its
+ *      pivots come near that shift, taken again, of [A_s; 2^-24.5 D] R1^{-1}.
+ *      Householder QR in FP32 arithmetic where the workspace does not hold
+ *      that (m below about s + 2.5 n);
  *   4. A_p = A R_s^{-1} (FP64, blocked substitution);
  *   5. C = A_p^T A_p, c = A_p^T b (FP64);
  *   6. Cholesky C = L L^T, L L^T y = c, R_s x = y (FP64);
@@ -141,9 +145,11 @@ pne_status hpne_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const
 
 /* sketch_precond: the preconditioner alone (Algorithm 1 steps "Sketch",
  * "Thin QR", "Promote R_s"; Section 6.2), by Householder QR in every
- * precision.  Writes the upper triangle of the
- * n x n FP64 matrix R_s into dR (ldr >= n); the strict lower triangle is set
- * to zero.  Workspace: sketch_precond_workspace_size. */
+ * precision.  Writes the upper triangle of the n x n FP64 matrix R_s into dR
+ * (ldr >= n); the strict lower triangle is set to zero.  R_s is determined up
+ * to the signs of its rows; which they are is not specified (in FP64 blocks of
+ * 1024 rows are factored first, then their R factors).
+ * Workspace: sketch_precond_workspace_size. */
 size_t sketch_precond_workspace_size(int64_t m, int64_t n, const pne_opts* opts);
 pne_status sketch_precond(int64_t m, int64_t n, const double* dA, int64_t lda, const pne_opts* opts,
                           double* dR, int64_t ldr, void* dwork, size_t work_bytes, int32_t* dinfo,
@@ -193,7 +199,7 @@ pne_status nne_solve(int64_t m, int64_t n, const double* dA, int64_t lda, const 
 /* qr_ls_solve: least squares by FP64 Householder QR on the GPU -- the
  * direct QR solver the paper measures PNE/HPNE against (Section 7.4), with
  * Q never formed: the QR of the augmented matrix [A b] = Q [R_A c; 0 rho]
- * gives x = R_A^{-1} c.  Communication-avoiding QR: 16 columns at a time,
+ * gives x = R_A^{-1} c (rho is not formed).  Communication-avoiding QR: 16 columns at a time,
  * row blocks of at most 1024 rows factored side by side, then their stacked
  * R factors, until one R remains.  n <= 3071.  dA: m x n (lda >= m); db: m;
  * dx: n (output); dinfo: one device int32 (1000+k for a zero or non-finite

@@ -17,8 +17,9 @@
 // replaces, runs three levels one after the other, each a chain of n / 8 or
 // n / 16 panels in one work-group with two passes over the rest of the block.
 // Here the chain is one of n / 16 panels whatever the height.  Measured:
-// 60000 x 601 24.9 -> 5.4 ms (panel 33 us, first apply 86 us on average and
-// 3 TB/s at its widest, upper levels 21 us, times 38); 3000 x 1000 5.6 -> 3.3
+// 60000 x 601 24.9 -> 5.55 ms (panel 33 us, first apply 87 us on average and
+// 3 TB/s at its widest, upper levels 22 us, times 38; 5.43 with V Z added to W
+// product by product, at 1.8 times the error); 3000 x 1000 5.6 -> 3.3
 // ms (27 + 18 + 6 us, times 63).
 #include "common.h"
 #include "kernels.h"

@@ -10,8 +10,9 @@
 // the instruction's A, op(A)^T as its B) so that lane l owns output rows
 // i = l % 16: consecutive lanes write consecutive addresses of the
 // column-major result.  Output layout of the 16x16 result in lane l,
-// register r: FP32 row 4*(l/16) + r, FP64 row l/16 + 4*r, column l % 16.  Split-K writes fixed partial buffers that a separate
-// kernel reduces in a fixed order.
+// register r: FP32 row 4*(l/16) + r, FP64 row l/16 + 4*r, column l % 16.
+// Split-K writes fixed partial buffers that a separate kernel reduces in a
+// fixed order.
 #include "common.h"
 #include "kernels.h"
 #include "tune.h"

@@ -13,9 +13,11 @@
 //           the triangular factor T (H_1..H_NB = I - V T V^T);
 //   update: Y = V^T W_trail, Z = T^T Y, W_trail -= V Z in one kernel (a
 //           wavefront per trailing column).
-// Working precision FP32.  For BF16 and FP16 the input is rounded to the format before the factorization and R_s
-// after it (FP32 arithmetic in between); FP16 input is first scaled by a
-// power of two that keeps R_s inside the FP16 range (qr_scale).
+// Working precision FP32.  For BF16 and FP16 the input is rounded to the format
+// before the factorization and R_s after it (FP32 arithmetic in between);
+// FP16 input is first scaled by a power of two that keeps R_s inside the FP16
+// range (qr_scale).  Runs where R itself is the result (sketch_precond,
+// cond_est_qr) and in solves too small for sketch_factor.hip.
 #include "common.h"
 #include "convert.h"
 #include "kernels.h"
