@@ -121,7 +121,7 @@ size_t pne_workspace_size(int64_t m, int64_t n, const pne_opts* opts, int hpne);
  *      A_s^T A_s + 8 n 2^-53 D^2, D = diag of the columns' norms; where its
  *      pivots come near that shift, taken again, of [A_s; 2^-24.5 D] R1^{-1}.
  *      Householder QR in FP32 arithmetic where the workspace does not hold
- *      that (m below about s + 2.5 n);
+ *      that (with s = 3 n: m below 2.1 n, or of a few hundred);
  *   4. A_p = A R_s^{-1} (FP64, blocked substitution);
  *   5. C = A_p^T A_p, c = A_p^T b (FP64);
  *   6. Cholesky C = L L^T, L L^T y = c, R_s x = y (FP64);

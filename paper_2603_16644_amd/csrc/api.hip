@@ -201,8 +201,14 @@ int64_t gram_slots(const Problem& p, size_t bytes)
 
 // Whether the solvers' FP32, BF16 and FP16 factors of the sketch come from its
 // Gram matrix: where A_p's memory, free until the solve, holds what its second
-// pass works on (m of about s + 2.5 n and more); else from Householder QR.
-bool gram_factor(const Problem& p) { return sketch_factor_doubles(p.s, p.n) <= (size_t)(ap_ld(p.m) * p.n); }
+// pass works on (m of about 2.1 n and more at s = 3 n, and of a few hundred)
+// and, for the estimate, a copy of the sketch; else from Householder QR (5000 x
+// 2000: 12 ms for 0.9).
+size_t ap_doubles(const Problem& p) { return (size_t)(ap_ld(p.m) * p.n); }
+bool gram_factor(const Problem& p)
+{
+    return sketch_factor_chunk(p.s, p.n, ap_doubles(p)) > 0 && (size_t)(p.s * p.n) <= 2 * ap_doubles(p);
+}
 
 // The condition estimate of one problem into b.k0 / b.choice: the FP32 Gram
 // estimate of Section 6.1, or (cond_method 1, no known kappa) the estimate
@@ -270,7 +276,7 @@ pne_status run_precond(Exec& ex, const Problem& p, const double* dA, uint64_t se
     if (rc) return (pne_status)rc;
     if (gram)
         rc = sketch_factor(ex, p.s, p.n, (float*)b.W, p.s, qr, b.R, p.n, b.C, (double*)b.scratch, gram_slots(p, cap),
-                           b.dinv1, b.c, (uint32_t*)b.y, (int32_t*)b.d, b.Ap, dinfo);
+                           b.dinv1, b.c, (uint32_t*)b.y, (int32_t*)b.d, b.Ap, ap_doubles(p), dinfo);
     else
         rc = qr_r(ex, p.s, p.n, b.W, p.s, qr, b.R, p.n, dinfo, b.scratch, cap);
     mark(ex, PH_QR);

@@ -36,11 +36,12 @@ template <typename TI, bool WIDE>
 struct GemmTn {
     typedef GemmArgs Args;
     static constexpr int NTH = 256, WPE = WIDE ? 1 : 2;   // (64-bit addresses: 440 registers)
-    static __device__ void run(const GemmArgs& g, int bx, int by);
+    static __device__ __forceinline__ void run(const GemmArgs& g, int bx, int by) { tile(g, bx, by, threadIdx.x); }
+    static __device__ void tile(const GemmArgs& g, int bx, int by, int tid);   // (tid: the thread's index)
 };
 
 template <typename TI, bool WIDE>
-__device__ __forceinline__ void GemmTn<TI, WIDE>::run(const GemmArgs& g, int bx, int by)
+__device__ __forceinline__ void GemmTn<TI, WIDE>::tile(const GemmArgs& g, int bx, int by, int tid)
 {
     constexpr int BM = 64;
     constexpr int E = 16 / sizeof(TI);       // K values of a lane's 16 bytes
@@ -49,7 +50,7 @@ __device__ __forceinline__ void GemmTn<TI, WIDE>::run(const GemmArgs& g, int bx,
     typedef TI vin __attribute__((ext_vector_type(E), aligned(sizeof(TI))));
     typedef const __attribute__((address_space(1))) TI* gpi;
     typedef const __attribute__((address_space(1))) vin* gpvi;
-    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t M = g.M, N = g.N;
     const int64_t tiles_m = (M + BM - 1) / BM;

@@ -158,10 +158,10 @@ void caqr_factor(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t 
 void qr_round(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, uint32_t* amax);
 // The factor of qr_r up to the signs of its rows, for FP32, BF16 and FP16, from
 // the FP64 Gram matrix of the sketch and its Cholesky factor (sketch_factor.hip).
-size_t sketch_factor_doubles(int64_t s, int64_t n);   // of X
+int64_t sketch_factor_chunk(int64_t s, int64_t n, size_t doubles);   // rows per chunk in X
 int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
                   double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, int32_t* work, double* X,
-                  int32_t* info);
+                  size_t xcap, int32_t* info);
 void gram_f32(Exec& ex, int64_t rows, int64_t n, const float* W, int64_t ldw, double* G, double* P, int64_t pslots);
 
 // ---------------------------------------------------------------- vectors

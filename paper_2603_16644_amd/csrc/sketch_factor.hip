@@ -49,8 +49,8 @@ struct SketchEndArgs {
     int64_t s, n;
     const float* W;
     int64_t ldw;
-    double* X;           // second pass: (s + n) x n, ld ldx
-    int64_t ldx;
+    double* X;           // second pass: chunk rows of (s + n) x n at a time, ld chunk (even)
+    int64_t chunk, nchunks;
     double* pack;        // packed R1
     const double* R1;    // ld n, like R2 and C
     double* R2;
@@ -73,9 +73,10 @@ struct SketchEndArgs {
 // out), zero below; 32 x 32 entries per tile, four per thread.
 //
 // The second pass runs where *state is 1.  Its work items are numbered in the
-// order of its phases: pack R1 and form [W; 2^-24.5 D]; substitution, 64 rows an item;
+// order of its phases: pack R1; for every chunk of rows that X's memory holds form
+// the chunk of [W; 2^-24.5 D], substitute, 64 rows an item, and add its part of the
 // Gram matrix, a tile of 64 x 64 an item; the steps of the Cholesky
-// factorization; tiles of R.  A work-group takes the next number from a
+// factorization; tiles of R.  (The first chunk is formed while R1 is packed.)  A work-group takes the next number from a
 // counter and waits until all items of the earlier phases are done.  Those
 // have lower numbers, so other work-groups took them and are working on them
 // or waiting for lower ones yet: whatever number of work-groups is on the
@@ -100,19 +101,20 @@ struct SketchEnd {
         asm volatile("" : "+v"(t));
         return t;
     }
-    static __device__ __forceinline__ void fill(const Args& a, int64_t e)
+    static __device__ __forceinline__ void pack(const Args& a, int64_t e)
     {
-        const int64_t n = a.n, nblk = (n + TB16 - 1) / TB16, np = pack_items(n);
-        if (e < np) {
-            const TrsmPack::Args p{n, a.R1, n, a.pack};
-            for (int c = 0; c < FILL; ++c) TrsmPack::run(p, (int)(e / nblk) * FILL + c, (int)(e % nblk));
-            return;
-        }
-        const int64_t rows = a.s + n, rt = (rows + NTH - 1) / NTH;
-        const int64_t i = (e - np) % rt * NTH + thread(), j0 = (e - np) / rt * FILL;
-        if (i >= rows) return;
+        const int64_t n = a.n, nblk = (n + TB16 - 1) / TB16;
+        const TrsmPack::Args p{n, a.R1, n, a.pack};
+        for (int c = 0; c < FILL; ++c) TrsmPack::run(p, (int)(e / nblk) * FILL + c, (int)(e % nblk));
+    }
+    // rows r0 .. r0 + rows - 1 of [W; 2^-24.5 D]
+    static __device__ __forceinline__ void fill(const Args& a, int64_t e, int64_t r0, int64_t rows)
+    {
+        const int64_t n = a.n, rt = (a.chunk + NTH - 1) / NTH;
+        const int64_t l = e % rt * NTH + thread(), i = r0 + l, j0 = e / rt * FILL;
+        if (l >= rows) return;
         for (int64_t j = j0; j < j0 + FILL && j < n; ++j)
-            a.X[i + j * a.ldx] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(0x1p-49 * a.gd[j]) : 0.0);
+            a.X[l + j * a.chunk] = i < a.s ? (double)a.W[i + j * a.ldw] : (i - a.s == j ? sqrt(0x1p-49 * a.gd[j]) : 0.0);
     }
     static __device__ __forceinline__ double upper(const double* M, int64_t n, int64_t r, int64_t c)
     {
@@ -190,12 +192,6 @@ struct SketchEnd {
     static __device__ __forceinline__ void second_pass(const Args& a)
     {
         __shared__ int32_t next;
-        const int64_t n = a.n, rows = a.s + n, nb = (n + CB - 1) / CB, nt = tiles(n);
-        const int64_t fills = pack_items(n) + (rows + NTH - 1) / NTH * ((n + FILL - 1) / FILL);
-        const int64_t subst = (rows + 63) / 64, gram = nb * (nb + 1) / 2;
-        // (Cholesky step k = 0 .. nb - 2 has r (r + 1) / 2 tiles, r = nb - 1 - k)
-        const int64_t chol = 1 + (nb - 1) * nb * (nb + 1) / 6;
-        const int64_t total = fills + subst + gram + chol + nt * nt;
         // (Thread 0 has one block of its own per turn, between two barriers.  With
         // one at each end of the turn the compiler joins the two into a path
         // for thread 0 alone, and the other lanes of its wavefront pass the
@@ -204,45 +200,64 @@ struct SketchEnd {
         for (;;) {
             __syncthreads();
             const int32_t it = __builtin_amdgcn_readfirstlane(next);
-            if (it >= total) break;
-            // the item's phase: its first item, and (Cholesky) its step
-            int64_t first = 0, k = -1;
-            int phase = 0;
-            if (it >= fills) { phase = 1; first = fills; }
-            if (it >= fills + subst) { phase = 2; first = fills + subst; }
-            if (it >= fills + subst + gram) {
+            // (the sizes formed anew every turn, not kept in registers across
+            // the phases)
+            int32_t n = (int32_t)a.n, chunk = (int32_t)a.chunk;
+            asm volatile("" : "+s"(n), "+s"(chunk));
+            const int32_t rows = (int32_t)a.s + n, nb = (n + CB - 1) / CB, nt = (int32_t)tiles(n);
+            const int32_t packs = (int32_t)pack_items(n), fills = (chunk + NTH - 1) / NTH * ((n + FILL - 1) / FILL);
+            const int32_t subst = (chunk + 63) / 64, gram = nb * (nb + 1) / 2, per = fills + subst + gram;
+            const int32_t gram_end = packs + (int32_t)a.nchunks * per;
+            // (Cholesky step k = 0 .. nb - 2 has r (r + 1) / 2 tiles, r = nb - 1 - k)
+            const int32_t chol = 1 + (nb - 1) * nb * (nb + 1) / 6;
+            if (it >= gram_end + chol + nt * nt) break;
+            // the item's phase: its first item, and its chunk's rows or (Cholesky)
+            // its step
+            int32_t first = 0, k = -1, r0 = 0;
+            int phase = -1;
+            if (it >= packs && it < gram_end) {
+                // (in a scalar register, which the division leaves)
+                const int32_t h = __builtin_amdgcn_readfirstlane((it - packs) / per), r = it - packs - h * per;
+                r0 = h * chunk;
+                phase = r < fills ? 0 : (r < fills + subst ? 1 : 2);
+                first = packs + h * per + (phase > 0 ? fills : 0) + (phase > 1 ? subst : 0);
+            } else if (it >= gram_end) {
                 phase = 3;
-                first = fills + subst + gram;
-                for (int64_t c = 1; k + 1 < nb; ++k) {
+                first = gram_end;
+                for (int32_t c = 1; k + 1 < nb; ++k) {
                     if (it < first + c) break;
                     first += c;
-                    const int64_t r = nb - 2 - k;   // of step k + 1
+                    const int32_t r = nb - 2 - k;   // of step k + 1
                     c = r * (r + 1) / 2;
                 }
                 if (k + 1 >= nb) phase = 4;
             }
-            if (threadIdx.x == 0 && first > 0) wait(a, first);
+            const int32_t crows = rows - r0 < chunk ? rows - r0 : chunk;
+            if (threadIdx.x == 0 && first > packs) wait(a, first);   // (the first chunk waits for nothing)
             __syncthreads();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            const int e = (int)(it - first);
-            if (phase == 0) {
-                fill(a, e);
+            const int e = it - first;
+            if (phase < 0) {
+                pack(a, e);
+            } else if (phase == 0) {
+                fill(a, e, r0, crows);
             } else if (phase == 1) {
                 // (in place: a lane loads its entries of a panel's columns
                 // before it stores there, and keeps nothing it loads of
                 // another's row)
-                const TrsmArgs p{rows, n, a.X, a.ldx, a.pack, a.X, a.ldx};
-                TrsmRows<false>::run(p, e, 0);
+                const TrsmArgs p{crows, n, a.X, chunk, a.pack, a.X, chunk};
+                if (64 * e < crows) TrsmRows<false>::rows(p, e, thread());
             } else if (phase == 2) {
                 GemmArgs g{};
-                g.M = n; g.N = n; g.K = rows;
-                g.A = a.X; g.lda = a.ldx;
-                g.B = a.X; g.ldb = a.ldx;
+                g.M = n; g.N = n; g.K = crows;
+                g.A = a.X; g.lda = chunk;
+                g.B = a.X; g.ldb = chunk;
                 g.lower = 1;
                 g.splits = 1;
-                g.kchunk = (rows + 15) / 16 * 16;
+                g.kchunk = (crows + 15) / 16 * 16;
                 g.P = a.C;
-                GemmTn<double, false>::run(g, e, 0);
+                g.accumulate_partials = r0 > 0;
+                GemmTn<double, false>::tile(g, e, 0, thread());
             } else if (phase == 3) {
                 const CholStepArgs p{n, k, a.C, n, nullptr, 0, a.R2, n, a.tab, a.gd, a.t, nullptr, nullptr, nullptr};
                 CholStep<true, true>::run(p, e, 0);
@@ -268,23 +283,32 @@ struct SketchEnd {
     }
 };
 
-static int64_t sketch_ld(int64_t s, int64_t n) { return (s + n + 1) & ~(int64_t)1; }
+static size_t own_doubles(int64_t n) { return trsm_pack_bytes(n) / sizeof(double) + (size_t)(n * n); }   // pack, R1
 
-size_t sketch_factor_doubles(int64_t s, int64_t n)
+// Rows of [W; 2^-24.5 D] that the second pass takes at a time in a scratch of so
+// many doubles: all, or a multiple of 64 that makes no more than eight chunks (each
+// costs three waits of the whole launch, some 30 us); else none (0).
+int64_t sketch_factor_chunk(int64_t s, int64_t n, size_t doubles)
 {
-    return (size_t)(sketch_ld(s, n) * n) + trsm_pack_bytes(n) / sizeof(double) + (size_t)(n * n);
+    const size_t own = own_doubles(n);
+    if (doubles <= own) return 0;
+    const int64_t rows = s + n, fit = (int64_t)((doubles - own) / (size_t)n), even = (rows + 1) & ~(int64_t)1;
+    if (fit >= even) return even;
+    const int64_t chunk = fit / 64 * 64;
+    return 8 * chunk >= rows ? chunk : 0;
 }
 
 // C: n x n scratch; P: scratch of pslots n x n FP64 matrices (at least one);
 // tab: dinv_elems(n), gd: n, words: two (FP16: scale; state), work: two; X:
-// scratch of sketch_factor_doubles(s, n), 16-byte aligned.
+// scratch of xcap doubles, 16-byte aligned, in which sketch_factor_chunk is not 0.
 int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int prec, double* R, int64_t ldr, double* C,
                   double* P, int64_t pslots, double* tab, double* gd, uint32_t* words, int32_t* work, double* X,
-                  int32_t* info)
+                  size_t xcap, int32_t* info)
 {
     uint32_t* amax = words;
     int32_t* state = (int32_t*)words + 1;
-    double* pack = X + sketch_ld(s, n) * n;
+    const int64_t chunk = sketch_factor_chunk(s, n, xcap);
+    double* pack = X + chunk * n;
     double* R1 = pack + trsm_pack_bytes(n) / sizeof(double);
     const double t = 8.0 * (double)n * 0x1p-53;
     ex.stage(ST_SKFACTOR);
@@ -297,7 +321,7 @@ int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     const int64_t nt = SketchEnd::tiles(n), most = nt * nt > ceil_div(s, 64) ? nt * nt : ceil_div(s, 64);
     const int64_t want = ex.recording() ? ceil_div(nt * nt, SketchEnd::TILES) : most;
     const int32_t wgs = (int32_t)(want < 256 ? want : 256);
-    launch<SketchEnd>(ex, wgs, 1, SketchEndArgs{s, n, W, ldw, X, sketch_ld(s, n), pack, R1, P, C, tab, gd, t, state, work,
+    launch<SketchEnd>(ex, wgs, 1, SketchEndArgs{s, n, W, ldw, X, chunk, ceil_div(s + n, chunk), pack, R1, P, C, tab, gd, t, state, work,
                                                 R, ldr, prec, amax, wgs, info});
     check_r_diag(ex, n, R, ldr, info);
     return launch_status(ex);

@@ -98,15 +98,16 @@ template <bool WIDE>
 struct TrsmRows {
     typedef TrsmArgs Args;
     static constexpr int NTH = 256, WPE = 3;
-    static __device__ void run(const TrsmArgs& a, int bx, int);
+    static __device__ __forceinline__ void run(const TrsmArgs& a, int bx, int) { rows(a, bx, threadIdx.x); }
+    static __device__ void rows(const TrsmArgs& a, int bx, int tid);   // (tid: the thread's index)
 };
 
 template <bool WIDE>
-__device__ __forceinline__ void TrsmRows<WIDE>::run(const TrsmArgs& a, int bx, int)
+__device__ __forceinline__ void TrsmRows<WIDE>::rows(const TrsmArgs& a, int bx, int tid)
 {
     __shared__ __attribute__((aligned(16))) v2d sr[2][PANEL * BLK / 2];
     __shared__ __attribute__((aligned(16))) v2d sd[2][DTAB / 2];
-    const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
+    const int lane = tid & 63, r16 = lane & 15, g4 = lane >> 4;
     const int w = tid >> 6;
     const int64_t m = a.m, n = a.n;
     const int nblk = (int)((n + TB16 - 1) / TB16);

@@ -108,6 +108,22 @@ def test_second_factor_sizes(pne, n, qr):
     assert np.linalg.norm(x - xs) <= 10 * np.linalg.cond(A) * U * np.linalg.norm(xs)
 
 
+@pytest.mark.parametrize("m,n,s", [
+    (240, 70, 0), (400, 130, 0), (650, 257, 0), (800, 257, 0), (1100, 257, 0), (1300, 257, 0), (1560, 257, 0),
+    (1088, 512, 0), (1600, 700, 0), (2600, 700, 0), (3800, 700, 0), (500, 257, 257), (700, 257, 300), (2150, 1000, 0)])
+def test_second_factor_in_chunks(pne, m, n, s):
+    """A_p's memory holds eighths to all of what the second factor works on (s =
+    3 n where 0); inputs and tolerance as above, with the estimate of AUTO too."""
+    rng = np.random.default_rng(m + n)
+    A = rng.standard_normal((m, n))
+    A[:, n - 2:] = A[:, :1] + 1e-9 * rng.standard_normal((m, 2))
+    A /= np.linalg.norm(A, axis=0)
+    xs = rng.standard_normal(n)
+    for opts in (dict(sketch_prec="fp32", qr_prec="fp32"), dict(sketch_prec="auto", qr_prec="fp32", cond_method=1)):
+        x = solve(pne, False, A, A @ xs, s=s, seed=3, refine_steps=3, **opts)
+        assert np.linalg.norm(x - xs) <= 10 * np.linalg.cond(A) * U * np.linalg.norm(xs)
+
+
 def test_second_factor_in_batches_and_replays(pne):
     """Members that need the second factor beside members that do not: each
     solves as it does alone, bit for bit, and a plan replayed from a graph, with
