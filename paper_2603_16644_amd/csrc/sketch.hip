@@ -803,13 +803,16 @@ static void launch_chunk(Exec& ex, const SketchPlan& p, const double* A, int64_t
     } else {
         if constexpr (SC) {
             const QuantArgs q{A, lda, k0, kc, p.ldk, br, n, Aq, sc};
-            // QuantizeScaled's work-groups: four to a CU and more, or those of a
-            // whole batch (2000 x 30 in blocks of 128 rows 5.3 and 2.3 us with a
-            // work-group per block, 20,000 x 200 13.6 and 23.6 us), and blocks of
-            // up to 384 rows (400,000 x 500 in blocks of 320 0.62 ms, 0.69 with a
-            // work-group per block, of 512 0.57 and 0.48)
+            // QuantizeScaled takes blocks of up to 384 rows (400,000 x 500 in
+            // blocks of 320 0.62 ms, 0.69 with a work-group per block, of 512 0.57
+            // and 0.48) where there are many: launching a work-group per block
+            // costs 0.5 us per thousand, against the few that QuantizeScaled has
+            // for few blocks, each for longer the longer its blocks are (scaled and
+            // block, us: blocks of 128, 2000 x 30 4.6 and 2.2, 30,000 x 16 4.7 and
+            // 4.0, 30,000 x 32 5.1 and 6.5; of 256, 30,000 x 100 12.4 and 10.9, x 160
+            // 14.9 and 16.8; of 64, 4096 x 48 3.8 and 3.4, x 64 3.9 and 4.0)
             const int64_t blocks = ceil_div(p.ldk, br), wgs = ceil_div(blocks, 4 * QS_BLKS);
-            const bool many = wgs * n >= 1024 || ex.recording();
+            const bool many = blocks * n >= 40 * br || ex.recording();
             if (many && br <= 256) launch<QuantizeScaled<OP, 4>>(ex, wgs, n, q);
             else if (many && br <= 384) launch<QuantizeScaled<OP, 8>>(ex, wgs, n, q);
             else launch<QuantizeBlock<OP>>(ex, blocks, n, q);

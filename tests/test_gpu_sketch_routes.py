@@ -44,3 +44,14 @@ def test_scaled_sketch_routes(pne, prec, u, m, n, s, br):
     a1, a2 = np.abs(A).sum(axis=0), np.sqrt((A * A).sum(axis=0))
     mean = 2 * u * np.sqrt(np.pi / 2) * float((a2 / np.where(a1 > 0, a1, 1)).max())
     assert float(np.sum(err)) <= mean * float(np.sum(ab))
+
+
+@pytest.mark.parametrize("prec,u", [("fp8", 2.0 ** -4), ("fp16", 2.0 ** -11)])
+@pytest.mark.parametrize("m,n,s,br", [
+    (63, 2560, 4, 64), (65, 1280, 4, 64), (1025, 569, 8, 128), (1500, 1100, 8, 192), (2700, 1100, 8, 256),
+    (3700, 1100, 8, 320), (5500, 1100, 8, 384)])
+def test_scaled_sketch_many_blocks(pne, prec, u, m, n, s, br):
+    """As above, with blocks enough for wavefronts of several blocks each, for
+    each length in registers (the first ones at the number of blocks where that
+    begins)."""
+    test_scaled_sketch_routes(pne, prec, u, m, n, s, br)
