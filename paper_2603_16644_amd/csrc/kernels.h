@@ -188,8 +188,6 @@ void lu_solve_lb(Exec& ex, int64_t n, const double* LU, int64_t ld, const int32_
 // flags: lb_flag_words(n) int32; c and x may alias.
 void upper_solve_lb(Exec& ex, int64_t n, const double* U, int64_t ld, const double* DU, const double* c, double* x,
                     int32_t* flags, int32_t* info);
-// *info = 1000 + k + 1 for the first zero or non-finite R(k, k) (if still 0)
-void check_r_diag(Exec& ex, int64_t n, const double* R, int64_t ldr, int32_t* info);
 bool lu_supported(int64_t n);
 // r = b - A x
 void residual(Exec& ex, int64_t m, int64_t n, const double* A, int64_t lda, const double* b, const double* x,

@@ -817,11 +817,6 @@ static int qr_f32(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     return launch_status(ex);
 }
 
-void check_r_diag(Exec& ex, int64_t n, const double* R, int64_t ldr, int32_t* info)
-{
-    launch<RDiagCheck>(ex, 1, 1, RDiagCheck::Args{n, R, ldr, info});
-}
-
 // FP64 (any height): the Householder QR of caqr.hip.
 int qr_f64(Exec& ex, int64_t s, int64_t n, int64_t nr, double* W, int64_t ldw, double* R, int64_t ldr, int32_t* info,
            void* work, size_t work_bytes)

@@ -65,12 +65,13 @@ struct SketchEndArgs {
     int prec;
     const uint32_t* amax;
     int32_t wgs;
-    int32_t* info;       // 4001 where a wait gives up
+    int32_t* info;       // 1000 + first column whose diagonal entry is bad; 4001 where a wait gives up
 };
 
 // R = R1, or R2 R1 after a second pass (upper triangles), rounded to the
 // precision of the factor (FP32, BF16, or FP16 with the input scale divided
-// out), zero below; 32 x 32 entries per tile, four per thread.
+// out), zero below, and its diagonal checked; 32 x 32 entries per tile, four per
+// thread.
 //
 // The second pass runs where *state is 1.  Its work items are numbered in the
 // order of its phases: pack R1; for every chunk of rows that X's memory holds form
@@ -119,6 +120,14 @@ struct SketchEnd {
     static __device__ __forceinline__ double upper(const double* M, int64_t n, int64_t r, int64_t c)
     {
         return r <= c && c < n ? M[r + c * n] : 0.0;
+    }
+    // (the lowest code stays, whichever comes first)
+    static __device__ __forceinline__ void bad_column(int32_t* info, int32_t code)
+    {
+        int32_t old = __hip_atomic_load(info, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while ((old == 0 || old > code) &&
+               !__hip_atomic_compare_exchange_strong(info, &old, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT)) {}
     }
     // a tile of R2 R1
     static __device__ __forceinline__ void tile(const Args& a, int64_t e)
@@ -177,6 +186,7 @@ struct SketchEnd {
             if (a.prec == PNE_PREC_FP16)
                 w = (double)(float)__builtin_bit_cast(_Float16, f32_to_f16_bits(f)) / (double)qr_scale(a.amax, a.s);
             a.R[r + c * a.ldr] = w;
+            if (r == c && (w == 0.0 || !isfinite(w))) bad_column(a.info, 1000 + (int32_t)r + 1);
         }
     }
     static __device__ __forceinline__ void wait(const Args& a, int64_t items)
@@ -323,7 +333,6 @@ int sketch_factor(Exec& ex, int64_t s, int64_t n, float* W, int64_t ldw, int pre
     const int32_t wgs = (int32_t)(want < 256 ? want : 256);
     launch<SketchEnd>(ex, wgs, 1, SketchEndArgs{s, n, W, ldw, X, chunk, ceil_div(s + n, chunk), pack, R1, P, C, tab, gd, t, state, work,
                                                 R, ldr, prec, amax, wgs, info});
-    check_r_diag(ex, n, R, ldr, info);
     return launch_status(ex);
 }
 

@@ -156,3 +156,19 @@ def test_second_factor_in_batches_and_replays(pne):
             assert float(junk) == float(junk) and not bool(info.any())
             assert torch.equal(x, ref)
     plan.close()
+
+
+@pytest.mark.parametrize("cols", [(0, 129), (5, 40, 97), (31, 32, 33), (64, 65), (128,), (129,)])
+@pytest.mark.parametrize("bad", [0.0, np.nan])
+def test_first_bad_column(pne, cols, bad):
+    """Zero columns and columns with a NaN in several tiles of R: the first of
+    them is reported."""
+    A = np.random.default_rng(9).standard_normal((3000, 130))
+    for c in cols:
+        A[slice(None) if bad == 0.0 else 7 * c, c] = bad
+    b = torch.ones(3000, dtype=torch.float64, device="cuda")
+    for hpne in (False, True):
+        fn = pne.hpne_solve if hpne else pne.pne_solve
+        x, info, _ = fn(dev(A), b, opts=pne.make_opts(seed=3, sketch_prec="fp32", qr_prec="fp32"))
+        assert int(info.item()) == 1000 + cols[0] + 1
+        assert bool(torch.isnan(x).all())
