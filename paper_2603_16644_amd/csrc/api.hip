@@ -464,12 +464,12 @@ void batch_layout(int64_t batch, const pne_problem_desc* hd, const pne_opts* o, 
 }
 
 // Upper bound of the group-table bytes of a recording: every record adds its
-// arguments and two int32 entries, and at most one group header, one
-// alignment pad and one 256-byte table alignment.
+// arguments and two int32 entries, and at most one group header, two pads to
+// 16 bytes, the work counters and one table alignment.
 size_t table_bound(const Recorder& rec)
 {
     size_t b = 256;
-    for (const LaunchRec& r : rec.recs) b += r.args_size + 8 + 4 + 16 + 256 + 32;
+    for (const LaunchRec& r : rec.recs) b += r.args_size + 8 + 4 + 2 * 16 + GROUP_COUNTER_BYTES + GROUP_ALIGN;
     return b;
 }
 

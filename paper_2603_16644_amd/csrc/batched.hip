@@ -67,7 +67,7 @@ int build_groups(const Recorder& rec, GroupSeq* out)
         const LaunchRec& r0 = R[idx[i]];
         while (j < idx.size() && R[idx[j]].key == r0.key && R[idx[j]].fn == r0.fn) ++j;
         const int count = (int)(j - i);
-        const size_t off = (blob.size() + 255) & ~(size_t)255;
+        const size_t off = (blob.size() + GROUP_ALIGN - 1) & ~(size_t)(GROUP_ALIGN - 1);
         const size_t aoff = (size_t)group_args_offset(count);
         // arguments, then the two work counters of a persistent launch (zero)
         blob.resize(off + (size_t)group_counter_offset(count, r0.args_size) + GROUP_COUNTER_BYTES, 0);

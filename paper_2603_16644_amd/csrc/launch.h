@@ -43,6 +43,7 @@ __host__ __device__ inline int64_t group_counter_offset(int count, int64_t args_
     return (group_args_offset(count) + (int64_t)count * args_size + 15) & ~(int64_t)15;
 }
 constexpr int64_t GROUP_COUNTER_BYTES = 16;
+constexpr int64_t GROUP_ALIGN = 64;   // of a table in the workspace
 
 // Locate work-group b's member in a group table and run its share.
 template <class K>

@@ -67,3 +67,18 @@ def test_sketch_takes_the_size_it_names(pne, prec, br, m, n, s):
     p = ctypes.c_void_p(0x100000)
     assert size > 0
     assert L.pne_sketch(m, n, p, m, s, 1, 0, prec, br, p, s, p, size, None) == -3
+
+
+@pytest.mark.parametrize("shapes,prec,hpne,cond,size", [
+    ([(838, 1)], "auto", 0, 0, 150880), ([(838, 1)], "auto", 0, 1, 163016), ([(240, 4)], "auto", 1, 1, 128284),
+    ([(838, 1)], "bf16", 0, 0, 133320), ([(240, 4)], "fp16", 0, 0, 131508), ([(1, 1)], "fp64", 0, 0, 115688),
+    ([(9, 1), (13, 1)], "fp64", 1, 0, 164728), ([(240, 4)], "fp8", 0, 0, 126692),
+])
+def test_batch(pne, shapes, prec, hpne, cond, size):
+    """Small members: their launch tables are the most of it."""
+    arr = (pne._lib.ProblemDesc * len(shapes))()
+    for i, (m, n) in enumerate(shapes):
+        arr[i] = pne._lib.ProblemDesc(m, n, m, 0, 0, 0, i)
+    o = pne.make_opts(sketch_prec=prec, qr_prec="fp32" if prec in ("bf16", "fp8") else prec, cond_method=cond)
+    got = pne.lib().pne_batched_workspace_size(len(shapes), ctypes.cast(arr, ctypes.c_void_p), ctypes.byref(o), hpne)
+    assert 0 < got <= size
